@@ -1,5 +1,5 @@
-"""Autotuner for the scan shapes of the pair pass (union pass size UCAP, hit
-list length LCAP, unroll RU of a lane's walk along one of its rows).
+"""Autotuner for the shapes of the pair pass (entries per pass UCAP, hits per
+lane and pass LCAP, unroll RU of the walk that lists a lane's hits).
 
 Every shape sums each particle's pairs in the same order, so every variant
 must give the same state bit for bit; the tuner checks that and keeps the
@@ -27,10 +27,10 @@ import sys
 
 from . import build as _build
 
-DEFAULT = {"UCAP": 128, "LCAP": 16, "RU": 2}
-# shapes whose LDS and list bounds hold: the byte hit list indexes a pass
-# (UCAP <= 256), the list holds at least a few hits (LCAP >= 8)
-SPACE = [dict(UCAP=u, LCAP=l, RU=r) for u, l, r in itertools.product((128, 192, 256), (16, 24), (1, 2, 4))]
+DEFAULT = {"UCAP": 128, "LCAP": 16, "RU": 1}
+# shapes that the pass holds for: one support test per pass (UCAP = 128), a
+# slot's list of 4 LCAP hits takes at least half a pass and fits byte sizes
+SPACE = [dict(UCAP=u, LCAP=l, RU=r) for u, l, r in itertools.product((128,), (16, 24, 32), (1, 2))]
 HEADER = os.path.join(_build.CSRC, "wcsph_tuned.h")
 REPS = 3
 
@@ -40,7 +40,7 @@ def tag(shape: dict) -> str:
 
 
 def valid(shape: dict) -> bool:
-    return 64 <= shape["UCAP"] <= 256 and 8 <= shape["LCAP"] <= 64 and shape["RU"] in (1, 2, 4, 8)
+    return shape["UCAP"] == 128 and 16 <= shape["LCAP"] <= 63 and shape["RU"] in (1, 2, 4, 8)
 
 
 def build_variants(out_dir: str) -> list:

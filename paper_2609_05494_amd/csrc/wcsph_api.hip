@@ -323,6 +323,9 @@ InstParams derive(const wcsph_params& p) {
   q.B = (float)B;
   q.p_cav = (float)p.p_cav;
   q.alpha = (float)p.alpha;
+  q.alpha_h = -q.alpha * q.h;
+  q.half_inv_h = -0.5f * q.inv_h;
+  q.two_inv_h = 2.0f * q.inv_h;
   q.beta2h2 = (float)(2.0 * p.beta * h * h);
   q.kernel_type = p.kernel_type;
   q.kc_sigma = (float)(10.0 / (7.0 * M_PI * h * h));
@@ -336,6 +339,15 @@ InstParams derive(const wcsph_params& p) {
   const double m_part = p.scheme == 1 ? lattice_mass(p) : p.rho0 * p.dx * p.dx;
   q.m_fluid = (float)m_part;
   q.m_wall = (float)m_part;
+  {
+    // test coordinates of the pair pass: truncation and the unit between
+    // cells lengthen each axis of a pair of adjacent cells by less than
+    // e = 2 units (and rounding): (|dx| + e)^2 + (|dy| + e)^2 at |dx| = |dy|
+    const double r = 2.0 * h / q.dcd * WC_TEST_UNITS, e = 2.01;
+    q.q_scale = (float)(WC_TEST_UNITS / q.dcd);
+    q.q_r2 = (float)std::ceil(r * r + 2.0 * std::sqrt(2.0) * e * r + 2.0 * e * e);
+    while ((1ll << q.cx_bits) < q.ncx) ++q.cx_bits;
+  }
   q.m_disk = p.n_disk_ghosts > 0 ? (float)(m_part / p.dx * 2.0 * M_PI * p.disk_R / p.n_disk_ghosts) : 0.0f;
   q.scheme = p.scheme;
   q.axisym = p.axisym;
@@ -690,6 +702,7 @@ void build(wcsph_ctx* c, const wcsph_params* params, int n_inst) {
   d.ring_cs = ring_cs;
   HC(hipMemcpyAsync(ring_cs, ring.data(), ring.size() * sizeof(double2), hipMemcpyHostToDevice, c->st));
   d.perm = dalloc_n<uint32_t>(c, c->n_slots);
+  d.tc = dalloc_n<uint2>(c, c->n_slots);
   d.gslot = dalloc_n<uint32_t>(c, c->n_ghost);
   d.gcell = dalloc_n<uint32_t>(c, c->n_ghost);
   d.gpos = dalloc_n<float2>(c, c->n_ghost);

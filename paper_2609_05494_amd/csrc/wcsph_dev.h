@@ -27,6 +27,7 @@
 #define WC_SORT_TILE 64        // cells per block of the sort kernel
 #define WC_NB_CAP 64           // neighbour ids per particle in the neighbour-list export
 #define WC_KIN_ROWS 1024       // rows of a tabulated disk motion per instance
+#define WC_TEST_UNITS 256      // test coordinates of the pair pass: units per cell edge
 #define WC_NO_ID 0xffffffffu   // particle id of an inert sorted entry (a gap left by a bucket overflow)
 
 // Per-instance constants (read-only in kernels).
@@ -84,6 +85,12 @@ struct InstParams {
   int axisym;
   float r_min;
   double r_mind;
+  // support test of the pair pass: test units per metre and the squared test
+  // radius (2h and the truncation of two positions, in test units)
+  float q_scale, q_r2;
+  // constants of the pair law: -alpha h, -1 / (2h), 2 / h
+  float alpha_h, half_inv_h, two_inv_h;
+  int cx_bits;  // bits of a cell column in a packed cell (cy << cx_bits | cx)
 };
 
 // Per-instance clock and accumulators (device-resident, FP64 time).
@@ -136,6 +143,7 @@ struct Dev {
   uint32_t* tot_a;
   uint32_t* tot_b;
   const uint32_t* wall_tot;
+  uint2* tc;                  // per sorted slot: test coordinates of the pair pass (packed cell, packed offset)
   uint32_t* perm;             // per slot: perm[new] = old of the last sort
   const double2* ring_cs;     // [n_inst][WC_MAX_RING] (cos, sin) of the ring angles
   uint32_t* gslot;            // per ghost: current slot

@@ -16,10 +16,12 @@
 // Pair arithmetic is FP32 on cell-relative offsets; time, kinematics,
 // enforcement geometry and diagnostics are FP64.
 
+#include <hip/hip_fp16.h>
+
 #include "wcsph_launch.h"
 #include "wcsph_kin.h"
 
-// Scan shapes of the pair pass (UCAP, LCAP, RU) picked for this GPU by the
+// Shapes of the pair pass (UCAP, LCAP, RU) picked for this GPU by the
 // autotuner (paper_2609_05494_amd/autotune.py), when it has been run; the
 // defaults below otherwise. They change speed only: every shape sums each
 // particle's pairs in the same order.
@@ -144,6 +146,30 @@ __device__ __forceinline__ void cubic_spline(const PP& P, float r2, float& W, fl
   F = in ? f_in : f_out;
 }
 
+// The same kernels without their constant factors, for the pair sums: W and
+// F over kernel_scale's (w, f). (Here and in the pair law the multiply-adds
+// are written out and nothing else is contracted, so that every variant of
+// the pass rounds alike: a batched instance equals its single run bitwise.)
+template <bool CUB, class PP>
+__device__ __forceinline__ void kernel_bare(const PP& P, float r2, float& W, float& F) {
+#pragma clang fp contract(off)
+  const float r = fast_sqrt(r2);
+  if constexpr (CUB) {
+    const float q = r * P.inv_h, s = 2.0f - q, t = s * s;
+    const bool in = q <= 1.0f;
+    W = in ? fmaf(q * q, fmaf(0.75f, q, -1.5f), 1.0f) : 0.25f * t * s;
+    F = in ? fmaf(2.25f, q, -3.0f) : -0.75f * t * fast_rcp(in ? 1.0f : q);
+  } else {
+    const float s = fmaf(r, P.half_h, 1.0f), s2 = s * s;
+    W = s2 * s2 * fmaf(r, P.two_h, 1.0f);
+    F = s2 * s;
+  }
+}
+template <bool CUB, class PP>
+__device__ __forceinline__ void kernel_scale(const PP& P, float& w, float& f) {
+  w = CUB ? P.kc_sigma : P.sigma;
+  f = CUB ? P.kc_a : -P.fgrad;
+}
 
 // Element j of a slot array through a 32-bit byte offset (the library
 // keeps j * 16 below 2^32), so that the load is a scalar base plus one
@@ -165,9 +191,10 @@ __device__ __forceinline__ void cell_xy(const InstParams& P, uint32_t K, int& cx
 // lies in [0, dc)), clamped to the grid.
 __device__ __forceinline__ void encode_axis(double x, double lo, double dcd, double inv_dcd, float dc, int n,
                                             int& c, float& o) {
+#pragma clang fp contract(off)
   const double u = x - lo;
   double cf = floor(u * inv_dcd);
-  double r = u - cf * dcd;
+  double r = fma(-cf, dcd, u);
   if (r < 0.0) {
     cf -= 1.0;
     r += dcd;
@@ -176,7 +203,7 @@ __device__ __forceinline__ void encode_axis(double x, double lo, double dcd, dou
     r -= dcd;
   }
   c = (int)fmin(fmax(cf, 0.0), (double)(n - 1));
-  o = (float)(u - (double)c * dcd);
+  o = (float)fma(-(double)c, dcd, u);
   if (o >= dc && c < n - 1) {
     o -= dc;
     c += 1;
@@ -185,6 +212,7 @@ __device__ __forceinline__ void encode_axis(double x, double lo, double dcd, dou
 
 // Keep an offset inside [0, dc) after a move, shifting the cell index.
 __device__ __forceinline__ void renorm(float& o, int& c, float dc) {
+#pragma clang fp contract(off)
   if (o < 0.0f) {
     o += dc;
     c -= 1;
@@ -270,6 +298,7 @@ __device__ __forceinline__ void count_hits(Clock* clk, int inst, bool clamp, boo
 
 struct PairAcc {
   float D, ax, ay, Vx, Vy;
+  float dd, lx, ly;  // while summing: delta and laminar terms without their constants
 };
 
 // Energy audit sums of a fluid particle (second evaluation, audit runs):
@@ -312,39 +341,48 @@ __device__ __forceinline__ uint32_t dx_code(uint32_t j, const RowRange& r) {
 // (scheme 1) D takes the internal-energy rate (1/2) m_j Pi_ij F v_ij . r_ij
 // instead of the continuity and delta terms, bit 3 (scheme 1 density pass)
 // D takes m_j W_ij and nothing else is summed.
+// The sums leave out the constant factors of the kernel and of each term,
+// which pair_finish applies once to the totals.
 template <bool AUD, int VAR, class PP>
 __device__ __forceinline__ void pair_body(const PP& P, const float4& pi, float rhoi, float Pi,
                                           float ci, float rx, float ry, float r2, const float4& pj,
                                           const float4& aj, PairAcc& acc, AudAcc& aud) {
+#pragma clang fp contract(off)
   float W, F;
-  if constexpr ((VAR & 2) != 0) cubic_spline(P, r2, W, F);
-  else wendland(P, r2, W, F);
+  kernel_bare<(VAR & 2) != 0>(P, r2, W, F);
   if constexpr ((VAR & 8) != 0) {  // summation density: |m_j| W_ij over fluid and ghosts
-    acc.D += fabsf(aj.w) * W;
+    acc.D = fmaf(fabsf(aj.w), W, acc.D);
     return;
   }
   const float vxij = pi.z - pj.z, vyij = pi.w - pj.w;
-  const float vr = vxij * rx + vyij * ry;
+  const float vr = fmaf(vxij, rx, vyij * ry);
   const float mj = fabsf(aj.w);
   const float mfl2 = aj.w + mj;  // 2 m_j for fluid, 0 for ghosts (the halves below are exact)
   const float rsum = rhoi + aj.x;       // 2 rho_bar
   const float den = r2 + P.eta2h2;      // r^2 + eta^2 h^2
   const float inv = fast_rcp(den * rsum);
-  // Monaghan AV: -alpha c_bar mu / rho_bar = -alpha (c_i + c_j) h vr inv for vr < 0
+  // Monaghan AV: -alpha c_bar mu / rho_bar = -alpha h (c_i + c_j) vr inv for vr < 0
   const float vrm = fminf(vr, 0.0f);
-  float piav = -P.alpha * P.h * (ci + aj.z) * vrm * inv;
+  const float cv = (ci + aj.z) * vrm * inv;
   // quadratic term beta mu^2 / rho_bar = 2 beta h^2 vr^2 / ((r^2 + eta^2 h^2)^2 2 rho_bar)
-  if constexpr ((VAR & 1) != 0) piav += P.beta2h2 * vrm * vrm * inv * (rsum * inv);
+  const float qav = (VAR & 1) != 0 ? P.beta2h2 * vrm * vrm * inv * (rsum * inv) : 0.0f;
   const float mF = mj * F;
-  // continuity + delta diffusion 2 delta h c0 (m_j / rho_j)(rho_i - rho_j) F (fluid pairs)
-  const float dd = (0.5f * P.two_delta_h_c0) * mfl2 * fast_rcp(aj.x) * (rhoi - aj.x) * F;
-  if constexpr ((VAR & 4) != 0) acc.D += 0.5f * mF * piav * vr;
-  else acc.D += mF * vr + dd;
-  const float sp = Pi + aj.y + piav;
+  // delta diffusion 2 delta h c0 (m_j / rho_j)(rho_i - rho_j) F (fluid pairs)
+  const float md = mfl2 * F * fast_rcp(aj.x), drho = rhoi - aj.x;
+  if constexpr ((VAR & 4) != 0) {
+    acc.D = fmaf(mF * fmaf(P.alpha_h, cv, qav), vr, acc.D);  // (half of it)
+  } else {
+    acc.D = fmaf(mF, vr, acc.D);
+    acc.dd = fmaf(md, drho, acc.dd);
+  }
+  const float Ps = (VAR & 1) != 0 ? Pi + (aj.y + qav) : Pi + aj.y;
+  const float G = mF * fmaf(P.alpha_h, cv, Ps);
   // laminar (Lo-Shao): 4 nu0 m_j F r^2 / ((rho_i + rho_j)(r^2 + eta^2 h^2)) v_ij
-  const float lam = P.four_nu0 * mF * r2 * inv;
-  acc.ax += lam * vxij - mF * sp * rx;
-  acc.ay += lam * vyij - mF * sp * ry;
+  const float lam = mF * (r2 * inv);
+  acc.lx = fmaf(lam, vxij, acc.lx);
+  acc.ly = fmaf(lam, vyij, acc.ly);
+  acc.ax = fmaf(-G, rx, acc.ax);
+  acc.ay = fmaf(-G, ry, acc.ay);
   if constexpr (AUD) {
     // fluid pairs: the pressure work cancels the elastic energy rate of the
     // continuity term pair by pair; half of each viscous dissipation
@@ -352,24 +390,48 @@ __device__ __forceinline__ void pair_body(const PP& P, const float4& pi, float r
     // delta term. Ghost pairs whole: the work of the pair's pressure, AV and
     // laminar forces on v_i plus P_i m_g F v_ig.r_ig of the continuity term,
     // -m_g F ((P_g + Pi_ig) r.v_i + P_i r.v_g) + lam v_ig.v_i.
+    const float piav = fmaf(P.alpha_h, cv, qav);
     const float mflF = 0.5f * mfl2 * F, mgF = mF - mflF;
-    const float v2 = vxij * vxij + vyij * vyij;
-    const float lamg = P.four_nu0 * mgF * r2 * inv;
-    aud.av += 0.5f * mflF * piav * vr;
-    aud.visc -= 0.5f * (lam - lamg) * v2;
-    aud.del += dd;
-    aud.ghost += lamg * (vxij * pi.z + vyij * pi.w) -
-                 mgF * ((aj.y + piav) * (rx * pi.z + ry * pi.w) + Pi * (rx * pj.z + ry * pj.w));
+    const float v2 = fmaf(vxij, vxij, vyij * vyij);
+    const float lamg = P.four_nu0 * mgF * (r2 * inv);
+    aud.av = fmaf(0.5f * mflF * piav, vr, aud.av);
+    aud.visc = fmaf(-0.5f * fmaf(P.four_nu0, lam, -lamg), v2, aud.visc);
+    aud.del = fmaf(md, drho, aud.del);
+    aud.ghost += fmaf(lamg, fmaf(vxij, pi.z, vyij * pi.w),
+                      -mgF * fmaf(aj.y + piav, fmaf(rx, pi.z, ry * pi.w), Pi * fmaf(rx, pj.z, ry * pj.w)));
   }
   // XSPH eps (m_j / rho_bar) W (v_j - v_i) over fluid; 1 / rho_bar = 2 den inv
-  const float w = P.eps_xsph * mfl2 * den * inv * W;
-  acc.Vx -= w * vxij;
-  acc.Vy -= w * vyij;
+  const float w = mfl2 * den * inv * W;
+  acc.Vx = fmaf(-w, vxij, acc.Vx);
+  acc.Vy = fmaf(-w, vyij, acc.Vy);
+}
+// The constant factors of a slot's (or a lane's) sums.
+template <bool AUD, int VAR, class PP>
+__device__ __forceinline__ void pair_finish(const PP& P, PairAcc& acc, AudAcc& aud) {
+#pragma clang fp contract(off)
+  float w, f;
+  kernel_scale<(VAR & 2) != 0>(P, w, f);
+  if constexpr ((VAR & 8) != 0) {
+    acc.D *= w;
+    return;
+  }
+  const float kd = 0.5f * P.two_delta_h_c0;
+  if constexpr ((VAR & 4) != 0) acc.D *= 0.5f * f;
+  else acc.D = f * fmaf(kd, acc.dd, acc.D);
+  acc.ax = f * fmaf(P.four_nu0, acc.lx, acc.ax);
+  acc.ay = f * fmaf(P.four_nu0, acc.ly, acc.ay);
+  const float xs = P.eps_xsph * w;
+  acc.Vx *= xs;
+  acc.Vy *= xs;
+  if constexpr (AUD) {
+    aud.av *= f;
+    aud.visc *= f;
+    aud.del *= kd * f;
+    aud.ghost *= f;
+  }
 }
 
-#ifndef PAIR_G
 #define PAIR_G 4                        // lanes per slot in the pair sums
-#endif
 #define PAIR_SLOTS 64                   // slots per block
 #define PAIR_BLOCK (PAIR_SLOTS * PAIR_G)
 #define SCAN_UNROLL 4
@@ -381,21 +443,42 @@ __device__ __forceinline__ float slot_sum(float v) {
   return v;
 }
 
-// The parameters of the candidate test and the pair law, held in registers
-// (the list stores below would otherwise force them to be reloaded).
+// The parameters of the group scan and the pair law of one instance, held in
+// registers (loaded together: the stores of the pass would otherwise force
+// them to be loaded again).
 struct PairC {
-  float dc, four_h2, inv_h, sigma, fgrad, alpha, h, eta2h2, two_delta_h_c0, four_nu0, eps_xsph, beta2h2;
-  float kc_sigma, kc_a;
+  float dc, four_h2, inv_h, half_h, two_h, sigma, fgrad, alpha_h, eta2h2, two_delta_h_c0, four_nu0, eps_xsph, beta2h2;
+  float kc_sigma, kc_a, q_r2;
+  int ncx, ncy, cell_off, cx_bits;
 };
-__device__ __forceinline__ PairC pair_c(const InstParams& P) {
+// (The parameter blocks do not change while a kernel runs: read through the
+// constant address space, a block that is the same on every lane comes
+// through the scalar cache wherever it is read.)
+typedef const __attribute__((address_space(4))) InstParams ConstParams;
+// A copy of a block that no one writes meanwhile (of the fields that are
+// used, when it is inlined), read through the constant address space.
+template <class T>
+__device__ __forceinline__ T scalar_copy(const T* p) {
+  static_assert(sizeof(T) % 8 == 0, "whole words");
+  typedef const __attribute__((address_space(4))) unsigned long long Word;
+  unsigned long long w[sizeof(T) / 8];
+#pragma unroll
+  for (int k = 0; k < (int)(sizeof(T) / 8); ++k) w[k] = ((Word*)p)[k];
+  T t;
+  __builtin_memcpy(&t, w, sizeof t);
+  return t;
+}
+__device__ __forceinline__ PairC pair_c(const InstParams* prm) {
+  ConstParams& P = *(ConstParams*)prm;
   PairC c;
+  c.alpha_h = P.alpha_h;
+  c.half_h = P.half_inv_h;
+  c.two_h = P.two_inv_h;
   c.dc = P.dc;
   c.four_h2 = P.four_h2;
   c.inv_h = P.inv_h;
   c.sigma = P.sigma;
   c.fgrad = P.fgrad;
-  c.alpha = P.alpha;
-  c.h = P.h;
   c.eta2h2 = P.eta2h2;
   c.two_delta_h_c0 = P.two_delta_h_c0;
   c.four_nu0 = P.four_nu0;
@@ -403,20 +486,37 @@ __device__ __forceinline__ PairC pair_c(const InstParams& P) {
   c.beta2h2 = P.beta2h2;
   c.kc_sigma = P.kc_sigma;
   c.kc_a = P.kc_a;
+  c.q_r2 = P.q_r2;
+  c.ncx = P.ncx;
+  c.ncy = P.ncy;
+  c.cell_off = P.cell_off;
+  c.cx_bits = P.cx_bits;
+  asm("" : "+s"(c.dc), "+s"(c.four_h2), "+s"(c.inv_h), "+s"(c.sigma), "+s"(c.fgrad), "+s"(c.alpha_h), "+s"(c.half_h), "+s"(c.two_h),
+      "+s"(c.eta2h2), "+s"(c.two_delta_h_c0), "+s"(c.four_nu0), "+s"(c.eps_xsph), "+s"(c.beta2h2));
+  asm("" : "+s"(c.kc_sigma), "+s"(c.kc_a), "+s"(c.q_r2), "+s"(c.ncx), "+s"(c.ncy), "+s"(c.cell_off),
+      "+s"(c.cx_bits));
   return c;
 }
 
 #ifndef UCAP
-#define UCAP 192  // union candidates staged per pass (one wave)
+#define UCAP 128  // union entries staged per pass (one wave): one support test
 #endif
 #ifndef LCAP
-#define LCAP 16   // entries of a lane's hit list
+#define LCAP 16   // hits per lane and pass of the pair law
 #endif
 #ifndef RU
-#define RU 2      // unroll of a lane's walk along one of its rows
+#define RU 1      // unroll of the walk that lists a lane's hits
 #endif
 #define PAIR_STR2(x) #x
 #define PAIR_STR(x) PAIR_STR2(x)
+#define PAIR_WSLOTS (64 / PAIR_G)  // slots per wave
+#define HCAP (PAIR_G * LCAP)       // hits per slot and pass; at least half a pass, see below
+static_assert(UCAP == 128 && HCAP >= UCAP / 2 && HCAP <= 255, "one support test per pass");
+#define QN WC_TEST_UNITS           // test coordinates: units per cell edge, and one between cells
+#define QP (QN + 1)
+#define QCOLS 8  // columns of a group: test coordinates stay below 2^11, every term and sum of the test below 2^24
+#define QORG 3   // origin column of the test coordinates (from the group's first)
+static_assert(PAIR_G == 4 && QN == 256, "test layout and exactness of the test terms");
 
 // Order the wave's LDS accesses: stores before this point are seen by every
 // lane's loads after it (accesses of one wave are performed in order; the
@@ -427,53 +527,121 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// Every load of the wave is complete, those straight into LDS too (the
+// compiler's own barriers and fences need not wait for them): vmcnt(0).
+__device__ __forceinline__ void wait_loads() {
+  __builtin_amdgcn_s_waitcnt(0x0f70);
+  asm volatile("" ::: "memory");
+}
+
+// LDS of one wave of the pair pass: the entries of a pass, (x offset, y
+// offset, vx, vy) and (rho, P, c, m), each entry's cell column and row from
+// the group's first column and its row, and the pass's hits: per slot of
+// the wave, entry indices. The test coordinates X, Y and X^2 + Y^2 stand in
+// the place of aux until the test has read them. (The size lets seven blocks
+// share a compute unit's LDS.)
+struct PairLds {
+  float4 pv[UCAP];
+  union {
+    float4 aux[UCAP];
+    float test[3 * UCAP];
+  };
+  __half2 cell[UCAP];
+  uint8_t hit[PAIR_WSLOTS * HCAP];
+};
+// LDS of a block: the slots' test coordinates and particle ids.
+struct PairSlots {
+  uint2 tc[PAIR_SLOTS];
+  uint32_t id[PAIR_SLOTS];
+};
+#define LDS_PTR(p) ((__attribute__((address_space(3))) void*)(p))
+#define GLB_PTR(p) ((const __attribute__((address_space(1))) void*)(p))
+
+typedef float v4f __attribute__((ext_vector_type(4)));
+
+// The lanes of row 0..3 (16 lanes each) holding the same lane % 16, on every
+// lane: r[k] is x of lane 16 k + lane % 16.
+__device__ __forceinline__ void rows4(uint32_t x, uint32_t r[4]) {
+  const auto h = __builtin_amdgcn_permlane32_swap(x, x, false, false);      // rows (0 1 0 1), (2 3 2 3)
+  const auto a = __builtin_amdgcn_permlane16_swap(h[0], h[0], false, false);  // rows 0, 1
+  const auto b = __builtin_amdgcn_permlane16_swap(h[1], h[1], false, false);  // rows 2, 3
+  r[0] = a[0];
+  r[1] = a[1];
+  r[2] = b[0];
+  r[3] = b[1];
+}
+
 // Pair sums of the fluid slots of one wave (64 / PAIR_G consecutive slots,
 // PAIR_G lanes each; every lane of the wave calls this). Fluid slots of one
-// instance and one cell row form a group; the union of their 3x3 blocks is
-// one slot range per row, which the wave stages in LDS in passes of UCAP entries:
-// offset x, offset y seen from the group's row, cell column, slot. Each
-// lane then walks its own particle's three rows of candidates (rows bottom
-// to top; in each row, the row's cells left to right in sorted order, entry
-// q, q + PAIR_G, ... for lane q) through LDS, keeps the in-support ones in a
-// lane-private list and sums the pair law over the list. A lane's candidate
-// order and every operand of a pair depend on the particle and its
-// neighbours only, not on the other slots of the wave.
+// instance, one cell row and at most QCOLS columns form a group; the union
+// of their 3x3 blocks is one slot range per row, which the wave stages in
+// LDS in passes of UCAP entries, each entry's whole state (loaded straight
+// into LDS).
+//
+// The support test of all 16 slots against 128 entries is a matrix product
+// on the matrix cores: with test coordinates X, Y from the group's origin
+// (whole units, 1/QN of a cell edge, truncated within the cell, one unit more
+// between cells; the sort leaves them in d.tc),
+//   |x_i - x_j|^2 - R^2 = -2 X_i X_j - 2 Y_i Y_j + (X_j^2 + Y_j^2) 1 + (X_i^2 + Y_i^2 - R^2),
+// three of the four products of v_mfma_f32_16x16x4_f32 and its accumulator
+// input. Every term and partial sum is a whole number below 2^24 (QCOLS
+// bounds X), so the result is exact and does not depend on the group's
+// origin. Truncation and the unit between cells lengthen an axis by less than
+// two units for particles of adjacent cells, R exceeds 2h by that: the test
+// passes every neighbour and about 2 % more, which the FP32 test of r^2 before
+// the pair law drops. It passes nothing outside a particle's own 3x3 cells,
+// two columns being at least QN + 3 > R apart (a particle's hits must not
+// depend on what else the union holds).
+// A lane holds the results of one slot and 32 consecutive entries; their
+// sign bits make its hit mask. The slot's four masks give each hit its rank
+// in entry order (rows bottom to top, cells left to right, sorted order
+// inside a cell); the indices go to the slot's list in LDS, and its
+// PAIR_G lanes take the hits of rank q, q + PAIR_G, ... (counted through the
+// passes). So a particle's hits, their order and their lanes depend on the
+// particle and its neighbours only, not on the other slots of the wave, and
+// the lanes share the pair law evenly (20 neighbours are five each).
+// The lane index is made anew where it is used and the slots' test
+// coordinates are kept in LDS, so that little besides the sums and the
+// particle's own state occupies registers in the pair law's loop.
 // EXP (export hook, single instance): every in-support neighbour's id also
 // goes to the export buffer d.nb_ids by fluid index f: the count at [f]
 // (zeroed by the host), the ids at [nf + f * WC_NB_CAP + k].
+__device__ __forceinline__ uint32_t lane_id() {
+  uint32_t l = threadIdx.x & 63u;
+  asm volatile("" : "+v"(l));
+  return l;
+}
 template <bool BATCH, bool AUD, int VAR, bool EXP = false>
-__device__ __forceinline__ void pair_sums_wave(const Dev& d, const Buf& sb, int s, int inst, uint32_t K,
-                                               bool fluid, float4 pi, float4 ai, int q, float4* U,
-                                               uint8_t* my, PairAcc& acc, AudAcc& aud) {
-  const InstParams& IP = d.prm[inst];
-  const PairC P = pair_c(IP);
+__device__ __forceinline__ void pair_sums_wave(const Dev& d, const Buf& sb, const PairC& G0, int s0, int inst,
+                                               bool fluid, const float4& pi, const float4& ai, PairLds& U,
+                                               const PairSlots& S, PairAcc& acc, AudAcc& aud) {
   const float rhoi = ai.x, Pi = ai.y, ci = ai.z;
-  const uint32_t lane = threadIdx.x & 63u;
-  int cx = 0, cy = 0;
-  if (fluid) cell_xy(IP, K, cx, cy);
-  // a single instance's grid, read once (the wave fences in the loop below
-  // keep the compiler from hoisting these loads out of it)
-  const int incx = IP.ncx, incy = IP.ncy, ioff = IP.cell_off;
-  const float idc = IP.dc;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const uint32_t ws = (uint32_t)(s0 + wave * PAIR_WSLOTS);  // the wave's first slot
+  wave_sync();  // the slots' test coordinates (of this wave's own slots) are in LDS
   uint64_t pending = __ballot(fluid);
   while (pending) {
+    // this lane's slot (pair layout)
+    const uint2 tc = S.tc[wave * PAIR_WSLOTS + lane_id() / PAIR_G];
+    const int bits = BATCH ? d.prm[inst].cx_bits : G0.cx_bits;
+    const int cx = (int)(tc.x & ((1u << bits) - 1u)), cy = (int)(tc.x >> bits);
     const int L = __builtin_ctzll(pending);
-    const int ginst = __builtin_amdgcn_readlane(inst, L);
+    const int ginst = BATCH ? __builtin_amdgcn_readlane(inst, L) : 0;
     const int gcy = __builtin_amdgcn_readlane(cy, L);
-    const bool mem = fluid && inst == ginst && cy == gcy;
+    const int cxa = __builtin_amdgcn_readlane(cx, L);
+    const bool mem = fluid && (!BATCH || inst == ginst) && cy == gcy && (uint32_t)(cx - cxa) < (uint32_t)QCOLS;
     const uint64_t mb = __ballot(mem);
     pending &= ~mb;
-    const int cxa = __builtin_amdgcn_readlane(cx, L);
     const int cxb = __builtin_amdgcn_readlane(cx, 63 - __builtin_clzll(mb));
-    const int gncx = BATCH ? d.prm[ginst].ncx : incx, gncy = BATCH ? d.prm[ginst].ncy : incy,
-              goff = BATCH ? d.prm[ginst].cell_off : ioff;
-    const float gdc = BATCH ? d.prm[ginst].dc : idc;
-    // union rows: first slot, first cell key; union index bases ub1, ub2.
-    // The cell-start loads of the union's rows complete together, then
-    // those of the lane's own rows (the empty asm statements take them as
-    // operands), without branches: a row outside the grid reads the nearest
-    // row and its values are then replaced. Otherwise the compiler waits for
-    // each row's loads before it issues the next row's.
+    const float cxi = (float)(cx - cxa);
+    // a group is of one instance: its constants are the same on every lane
+    const PairC P = BATCH ? pair_c(d.prm + ginst) : G0;
+    const int gncx = P.ncx, gncy = P.ncy, goff = P.cell_off, gcxb = P.cx_bits;
+    // union rows: first slot and size; union index bases ub1, ub2.
+    // The cell-start loads complete together (the empty asm statement takes
+    // them as operands), without branches: a row outside the grid reads the
+    // nearest row and its values are then replaced. Otherwise the compiler
+    // waits for each row's loads before it issues the next row's.
     uint32_t va[3], vb[3];
 #pragma unroll
     for (int r = 0; r < 3; ++r) {
@@ -483,123 +651,159 @@ __device__ __forceinline__ void pair_sums_wave(const Dev& d, const Buf& sb, int 
     }
     asm("" : "+v"(va[0]), "+v"(va[1]), "+v"(va[2]), "+v"(vb[0]), "+v"(vb[1]), "+v"(vb[2]));
     uint32_t urs[3], un[3];
-    int k0[3];
 #pragma unroll
     for (int r = 0; r < 3; ++r) {
       const int yy = gcy + r - 1;
       const bool ok = yy >= 0 && yy < gncy;
-      k0[r] = ok ? goff + yy * gncx : 0;
-      urs[r] = ok ? __builtin_amdgcn_readfirstlane(va[r]) : 0u;
-      un[r] = ok ? __builtin_amdgcn_readfirstlane(vb[r]) - __builtin_amdgcn_readfirstlane(va[r]) : 0u;
-    }
-    uint32_t ors[3], on[3];
-#pragma unroll
-    for (int r = 0; r < 3; ++r) {
-      const int kc = goff + min(max(gcy + r - 1, 0), gncy - 1) * gncx;
-      ors[r] = at32(d.start, (uint32_t)(kc + min(max(cx - 1, 0), gncx - 1)));  // (any lane's cx: clamped)
-      on[r] = at32(d.start, (uint32_t)(kc + min(cx + 1, gncx - 1) + 1));
-    }
-    asm("" : "+v"(ors[0]), "+v"(ors[1]), "+v"(ors[2]), "+v"(on[0]), "+v"(on[1]), "+v"(on[2]));
-#pragma unroll
-    for (int r = 0; r < 3; ++r) {
-      on[r] = un[r] != 0u ? on[r] - ors[r] : 0u;
-      ors[r] = un[r] != 0u ? ors[r] : 0u;
+      urs[r] = __builtin_amdgcn_readfirstlane(va[r]);
+      un[r] = ok ? __builtin_amdgcn_readfirstlane(vb[r]) - urs[r] : 0u;
     }
     const uint32_t ub1 = un[0], ub2 = un[0] + un[1], n = ub2 + un[2];
-    // own rows: candidate c of row r has union index c + adj[r]
-    uint32_t p1 = 0u, p2 = 0u, no = 0u, adj0 = 0u, adj1 = 0u, adj2 = 0u;
-    if (mem) {
-      p1 = on[0];
-      p2 = on[0] + on[1];
-      no = p2 + on[2];
-      adj0 = ors[0] - urs[0];
-      adj1 = ub1 + (ors[1] - urs[1]) - p1;
-      adj2 = ub2 + (ors[2] - urs[2]) - p2;
-    }
-    const float cxi = (float)(cx - cxa);
-    int cnt = 0;
-    // own row r is the union range [p_r + adj_r, p_r + adj_r + on_r); lane q
-    // walks entries q, q + G, ... of each own row in turn (row, next union
-    // index u, end of the row), carried from pass to pass
-    int row = 0;
-    uint32_t u = adj0 + (uint32_t)q, uend = adj0 + p1;
-    // sum the pair law over the list, two entries in flight (buffers a, b)
-    auto fetch = [&](int k, float4& E, float4& pj, float4& aj) __attribute__((always_inline)) {
-      E = U[my[min(k, cnt - 1) * PAIR_BLOCK]];
-      const uint32_t j = __float_as_uint(E.w);
-      pj = at32(sb.pv, j);
-      aj = at32(sb.aux, j);
-    };
-    auto body = [&](const float4& E, const float4& pj, const float4& aj) __attribute__((always_inline)) {
-      const float rx = (pi.x - E.x) - (E.z - cxi) * P.dc;
-      const float ry = pi.y - E.y;
-      pair_body<AUD, VAR>(P, pi, rhoi, Pi, ci, rx, ry, rx * rx + ry * ry, pj, aj, acc, aud);
-      if constexpr (EXP) {
-        const uint32_t f = at32(sb.id, (uint32_t)s) - (uint32_t)IP.id0;
-        const uint32_t k = atomicAdd(&d.nb_ids[f], 1u);
-        if (k < (uint32_t)WC_NB_CAP)
-          d.nb_ids[(size_t)IP.nf + (size_t)f * WC_NB_CAP + k] = at32(sb.id, __float_as_uint(E.w));
-      }
-    };
-    auto flush = [&]() __attribute__((always_inline)) {
-      if (cnt > 0) {
-        float4 Ea, pa, aa, Eb, pb, ab;
-        fetch(0, Ea, pa, aa);
-        for (int k = 0;; k += 2) {
-          fetch(k + 1, Eb, pb, ab);
-          body(Ea, pa, aa);
-          if (k + 1 >= cnt) break;
-          fetch(k + 2, Ea, pa, aa);
-          body(Eb, pb, ab);
-          if (k + 2 >= cnt) break;
-        }
-      }
-      cnt = 0;
-    };
-    for (uint32_t u0 = 0; u0 < n; u0 += UCAP) {
+    // union index u of row r is slot u + ud[r]
+    const uint32_t ud0 = urs[0], ud1 = urs[1] - ub1, ud2 = urs[2] - ub2;
+    uint32_t hrun = 0u;  // hits of this lane's slot (pair layout) in the passes before
+    uint32_t step = UCAP;
+    for (uint32_t u0 = 0; u0 < n; u0 += step) {
       const uint32_t m = min(n - u0, (uint32_t)UCAP);
+      uint32_t hn;  // hits of this lane's slot (pair layout)
       wave_sync();  // the previous pass is no longer read
-      for (uint32_t t = lane; t < m; t += 64) {
-        const uint32_t u = u0 + t;
-        const bool a0 = u < ub1, a1 = u < ub2;
-        const uint32_t j = a0 ? urs[0] + u : (a1 ? urs[1] + (u - ub1) : urs[2] + (u - ub2));
-        const int kr = a0 ? k0[0] : (a1 ? k0[1] : k0[2]);
-        const float sy = a0 ? -gdc : (a1 ? 0.0f : gdc);
-        const float4 pj = at32(sb.pv, j);
-        const int cxj = (int)at32(sb.cell, j) - kr;
-        U[t] = make_float4(pj.x, pj.y + sy, (float)(cxj - cxa), __uint_as_float(j));
-      }
-      wave_sync();
-      if (mem) {
-        // a lane walks a row up to the nearer of the row's end, the pass's
-        // end and the room left in its list; then it flushes the list, moves
-        // to its next own row, or leaves the rest of the row to the next pass
-        const uint32_t pe = u0 + m;
-        for (;;) {
-          const uint32_t lim = min(uend, pe);
-          while (u < lim) {
-            // the row's candidates in this pass, as many as the list has room for
-            const uint32_t ue = u + PAIR_G * min((lim - u + PAIR_G - 1) / PAIR_G, (uint32_t)(LCAP - cnt));
-            _Pragma(PAIR_STR(unroll RU))
-            for (; u < ue; u += PAIR_G) {
-              const float4 E = U[u - u0];
-              const float rx = (pi.x - E.x) - (E.z - cxi) * P.dc;
-              const float ry = pi.y - E.y;
-              const bool hit = (rx * rx + ry * ry < P.four_h2) & (__float_as_uint(E.w) != (uint32_t)s);
-              my[cnt * PAIR_BLOCK] = (uint8_t)(u - u0);
-              cnt += hit ? 1 : 0;
-            }
-            if (cnt == LCAP) flush();
-          }
-          if (u < uend || row == 2) break;  // the pass ends inside this row, or every row is done
-          ++row;  // this own row is done: the next one
-          const uint32_t a = row == 1 ? p1 + adj1 : p2 + adj2;
-          u = a + (uint32_t)q;
-          uend = a + (row == 1 ? p2 - p1 : no - p2);
+      {
+        const uint32_t lane = lane_id();
+        // stage the pass; an index past it reads its last entry and is kept
+        // from the test
+        constexpr int NE = UCAP / 64;
+        uint32_t je[NE];
+        uint2 te[NE];
+#pragma unroll
+        for (int e = 0; e < NE; ++e) {
+          const uint32_t u = u0 + min(lane + 64u * e, m - 1u);
+          je[e] = u + (u < ub1 ? ud0 : (u < ub2 ? ud1 : ud2));
+          te[e] = at32(d.tc, je[e]);
         }
-        flush();
+#pragma unroll
+        for (int e = 0; e < NE; ++e)
+          __builtin_amdgcn_global_load_lds(GLB_PTR(sb.pv + je[e]), LDS_PTR(U.pv + 64 * e), 16, 0, 0);
+        // test layout: slot tn of the wave, entries [32 tq, 32 tq + 32);
+        // the slots' own test coordinates, column operand and accumulator
+        // input (a slot that is no member never hits)
+        const uint32_t tn = lane & 15u, tq = lane >> 4;
+        const uint2 tcn = S.tc[wave * PAIR_WSLOTS + tn];
+        const float Xn = (float)(((int)(tcn.x & ((1u << gcxb) - 1u)) - cxa - QORG) * QP + (int)(tcn.y & 255u));
+        const float Yn = (float)(tcn.y >> 8);
+        const bool memn = ((mb >> (tn * PAIR_G)) & 1ull) != 0ull;
+        const float bcol = tq == 0u ? -2.0f * Xn : (tq == 1u ? -2.0f * Yn : (tq == 2u ? 1.0f : 0.0f));
+        const float cn = memn ? fmaf(Xn, Xn, Yn * Yn) - P.q_r2 : 1.0e30f;
+        const v4f cin = {cn, cn, cn, cn};
+#pragma unroll
+        for (int e = 0; e < NE; ++e) {
+          const uint32_t t = lane + 64u * e;
+          const int col = (int)(te[e].x & ((1u << gcxb) - 1u)) - cxa, row = (int)(te[e].x >> gcxb) - gcy;
+          const float X = (float)((col - QORG) * QP + (int)(te[e].y & 255u));
+          const float Y = (float)(row * QP + (int)(te[e].y >> 8));
+          U.test[t] = X;
+          U.test[UCAP + t] = Y;
+          U.test[2 * UCAP + t] = t < m ? fmaf(X, X, Y * Y) : 1.0e30f;
+          U.cell[t] = __half2(__int2half_rn(col), __int2half_rn(row));
+        }
+        wave_sync();
+        // the test: row operand of block b, lane (row = lane % 16, k = lane / 16)
+        // is coordinate k of entry 32 (row / 4) + 4 b + row % 4, so that result
+        // r of block b is entry 32 tq + 4 b + r; k = 3 reads X again (its
+        // column operand is zero)
+        const float* qa = U.test + (tq == 3u ? 0u : tq) * UCAP + (tn >> 2) * 32u + (tn & 3u);
+        float av[8];
+#pragma unroll
+        for (int b = 0; b < 8; ++b) av[b] = qa[4 * b];
+        wave_sync();  // the test coordinates are read: aux comes into their place
+        asm volatile("" : "+v"(av[0]), "+v"(av[1]), "+v"(av[2]), "+v"(av[3]), "+v"(av[4]), "+v"(av[5]), "+v"(av[6]),
+                     "+v"(av[7]) : : "memory");
+#pragma unroll
+        for (int e = 0; e < NE; ++e)
+          __builtin_amdgcn_global_load_lds(GLB_PTR(sb.aux + je[e]), LDS_PTR(U.aux + 64 * e), 16, 0, 0);
+        uint32_t M = 0u;
+#pragma unroll
+        for (int b = 7; b > 0; b -= 2) {
+          const v4f r1 = __builtin_amdgcn_mfma_f32_16x16x4f32(av[b], bcol, cin, 0, 0, 0);
+          const v4f r0 = __builtin_amdgcn_mfma_f32_16x16x4f32(av[b - 1], bcol, cin, 0, 0, 0);
+#pragma unroll
+          for (int r = 3; r >= 0; --r) M = __builtin_amdgcn_alignbit(M, __float_as_uint(r1[r]), 31);
+#pragma unroll
+          for (int r = 3; r >= 0; --r) M = __builtin_amdgcn_alignbit(M, __float_as_uint(r0[r]), 31);
+        }
+        // the slot itself is no hit (its union index: every member lies in the middle row)
+        const uint32_t self = ws + tn - ud1 - u0 - 32u * tq;
+        M &= self < 32u ? ~(1u << self) : ~0u;
+        // rank of the lane's first hit within the slot's hits of this pass
+        uint32_t pc[4];
+        rows4((uint32_t)__popc(M), pc);
+        uint32_t tot = pc[0] + pc[1] + pc[2] + pc[3];
+        step = UCAP;
+        if (__any(tot > HCAP)) {
+          // crowded: this pass takes the first half of its entries only
+          step = UCAP / 2;
+          pc[2] = pc[3] = 0u;
+          tot = pc[0] + pc[1];
+          if (tq > 1u) M = 0u;
+        }
+        const uint32_t first = (tq > 0u ? pc[0] : 0u) + (tq > 1u ? pc[1] : 0u) + (tq > 2u ? pc[2] : 0u);
+        hn = __shfl(tot, (int)(lane / PAIR_G));
+        uint8_t* hp = U.hit + tn * HCAP + first;
+        _Pragma(PAIR_STR(unroll RU))
+        while (M) {
+          *hp++ = (uint8_t)(32u * tq + (uint32_t)__builtin_ctz(M));
+          M &= M - 1u;
+        }
       }
+      // the list and (loaded into LDS since the staging) the entries
+      wait_loads();
+      wave_sync();
+      const uint32_t pl = lane_id();
+      // hits of rank q, q + PAIR_G, ... of the slot's whole count
+      uint32_t k = (pl - hrun) & (PAIR_G - 1);
+      if (k < hn) {
+        const uint8_t* hl = U.hit + (pl / PAIR_G) * HCAP;
+        // two entries in flight (buffers a, b)
+        auto fetch = [&](uint32_t kk, float4& pj, float4& aj, __half2& cj, uint32_t& t) __attribute__((always_inline)) {
+          t = hl[min(kk, hn - 1u)];
+          pj = U.pv[t];
+          aj = U.aux[t];
+          cj = U.cell[t];
+        };
+        auto body = [&](const float4& pj, const float4& aj, __half2 cj, uint32_t t) __attribute__((always_inline)) {
+          // offsets' difference, then whole cells
+          const float rx = fmaf(cxi - __low2float(cj), P.dc, pi.x - pj.x);
+          const float ry = fmaf(-__high2float(cj), P.dc, pi.y - pj.y);
+          const float r2 = fmaf(rx, rx, ry * ry);
+          if (r2 < P.four_h2) {
+            pair_body<AUD, VAR>(P, pi, rhoi, Pi, ci, rx, ry, r2, pj, aj, acc, aud);
+            if constexpr (EXP) {
+              const uint32_t u = u0 + t;
+              const uint32_t j = u + (u < ub1 ? ud0 : (u < ub2 ? ud1 : ud2));
+              const uint32_t f = at32(sb.id, ws + pl / PAIR_G) - (uint32_t)d.prm[0].id0;
+              const uint32_t c = atomicAdd(&d.nb_ids[f], 1u);
+              if (c < (uint32_t)WC_NB_CAP)
+                d.nb_ids[(size_t)d.prm[0].nf + (size_t)f * WC_NB_CAP + c] = at32(sb.id, j);
+            }
+          }
+        };
+        float4 pa, aa, pb, ab;
+        __half2 ca, cb;
+        uint32_t ta, tb;
+        fetch(k, pa, aa, ca, ta);
+        for (;;) {
+          fetch(k + PAIR_G, pb, ab, cb, tb);
+          body(pa, aa, ca, ta);
+          k += PAIR_G;
+          if (k >= hn) break;
+          fetch(k + PAIR_G, pa, aa, ca, ta);
+          body(pb, ab, cb, tb);
+          k += PAIR_G;
+          if (k >= hn) break;
+        }
+      }
+      hrun += hn;
     }
+    if (mem) pair_finish<AUD, VAR>(P, acc, aud);  // a slot is of one group
   }
 }
 
@@ -846,8 +1050,9 @@ __device__ __forceinline__ void bucket_put_wall(const Dev& d, const InstParams& 
 // into its bucket for the next sort.
 __device__ __forceinline__ void place_ring(const Dev& d, const InstParams& P, int inst, int k, double xc,
                                            const Buf& out, int s, const Fill& bucket) {
+#pragma clang fp contract(off)
   const double2 cs = d.ring_cs[inst * WC_MAX_RING + k];
-  const double x = xc + P.R * cs.x, y = P.disk_y0 + P.R * cs.y;
+  const double x = fma(P.R, cs.x, xc), y = fma(P.R, cs.y, P.disk_y0);
   int cx, cy;
   float ox, oy;
   encode_axis(x, P.x_lo, P.dcd, P.inv_dcd, P.dc, P.ncx, cx, ox);
@@ -886,7 +1091,7 @@ __device__ __forceinline__ void place_ring(const Dev& d, const InstParams& P, in
 
 // State of one particle at its old slot e, as loaded (before the EOS).
 struct Loaded {
-  uint32_t cell, id;
+  uint32_t id;
   float4 pv;
   float rho, e;  // e: scheme 1 internal energy
   int inst;  // -1: corrupted bucket entry
@@ -894,11 +1099,21 @@ struct Loaded {
 // One particle moved by the sort: its state with the per-particle EOS
 // (fluid) or ghost mass.
 struct Gathered {
-  uint32_t cell, id;
+  uint32_t id;
+  uint2 tc;  // test coordinates (see d.tc)
   float4 pv, aux;
   float e;
   int inst, ghost;  // ghost: -1 for fluid, else the ghost index g of its instance
 };
+// Test coordinates of the pair pass: the cell as cy << cx_bits | cx, and the
+// offset in 1/QN of the edge, truncated, as y << 8 | x. (An offset outside the
+// cell, of a ghost beyond the grid's edge, takes the cell's border: nearer to
+// every fluid particle than the ghost is.)
+__device__ __forceinline__ uint2 test_coords(const InstParams& P, int cx, int cy, float ox, float oy) {
+  const uint32_t x = (uint32_t)fminf(fmaxf(ox * P.q_scale, 0.0f), (float)(QN - 1));
+  const uint32_t y = (uint32_t)fminf(fmaxf(oy * P.q_scale, 0.0f), (float)(QN - 1));
+  return make_uint2(((uint32_t)cy << P.cx_bits) | (uint32_t)cx, (y << 8) | x);
+}
 // (branch-free: an entry outside the slot range reads slot 0 and is marked)
 template <bool BATCH>
 __device__ __forceinline__ Loaded sort_load(const Dev& d, const Buf& pre, uint32_t e) {
@@ -906,7 +1121,6 @@ __device__ __forceinline__ Loaded sort_load(const Dev& d, const Buf& pre, uint32
   const bool ok = e < (uint32_t)d.n_slots;  // else a corrupted bucket: flagged when stored
   const uint32_t x = ok ? e : 0u;
   v.inst = inst_at<BATCH>(pre, (int)x);
-  v.cell = pre.cell[x];
   v.id = pre.id[x];
   v.pv = pre.pv[x];
   v.rho = pre.aux[x].x;
@@ -914,16 +1128,16 @@ __device__ __forceinline__ Loaded sort_load(const Dev& d, const Buf& pre, uint32
   if (!ok) v.inst = -1;
   return v;
 }
-template <bool MG>
-__device__ __forceinline__ Gathered sort_finish(const Dev& d, const Loaded& l) {
+template <bool MG, bool BATCH>
+__device__ __forceinline__ Gathered sort_finish(const Dev& d, const InstParams& P1, int cx, int cy, const Loaded& l) {
   Gathered v;
   v.inst = l.inst;
   if (l.inst < 0) return v;
-  const InstParams& P = d.prm[l.inst];
-  v.cell = l.cell;
+  const InstParams& P = BATCH ? d.prm[l.inst] : P1;
   v.id = l.id;
   v.pv = l.pv;
   v.e = l.e;
+  v.tc = test_coords(P, cx, cy, l.pv.x, l.pv.y);
   const int local = (int)l.id - P.id0;
   if (local < P.nf) {
     float Pq = 0.0f, c = 0.0f;
@@ -932,8 +1146,6 @@ __device__ __forceinline__ Gathered sort_finish(const Dev& d, const Loaded& l) {
     float m = P.m_fluid;
     if (P.axisym) {
       // the ring's planar mass M / (2 pi r), r held >= dx/2
-      int cx, cy;
-      cell_xy(P, l.cell, cx, cy);
       const double r = P.y_lo + (double)cy * P.dcd + (double)l.pv.y;
       m = (float)(d.mring[l.id] / fmax(r, P.r_mind));
     }
@@ -946,22 +1158,23 @@ __device__ __forceinline__ Gathered sort_finish(const Dev& d, const Loaded& l) {
   return v;
 }
 template <bool BATCH>
-__device__ __forceinline__ void sort_store(const Dev& d, const Buf& out, uint32_t e, uint32_t dst,
-                                           const Gathered& v) {
+__device__ __forceinline__ void sort_store(const Dev& d, const InstParams& P1, const Buf& out, uint32_t e,
+                                           uint32_t dst, uint32_t K, const Gathered& v) {
   if (v.inst < 0 || dst >= (uint32_t)d.n_slots) {
     atomicOr(&d.clk[0].bad, 4u);
     return;
   }
   if (v.ghost >= 0) {
-    const int gi = d.prm[v.inst].gmap0 + v.ghost;
+    const int gi = (BATCH ? d.prm[v.inst].gmap0 : P1.gmap0) + v.ghost;
     d.gslot[gi] = dst;
-    d.gcell[gi] = v.cell;
+    d.gcell[gi] = K;
     d.gpos[gi] = make_float2(v.pv.x, v.pv.y);
   }
-  out.cell[dst] = v.cell;
+  out.cell[dst] = K;
   out.id[dst] = v.id;
   out.pv[dst] = v.pv;
   out.aux[dst] = v.aux;
+  d.tc[dst] = v.tc;
   if constexpr (BATCH) out.inst[dst] = (uint16_t)v.inst;
   if (out.e) out.e[dst] = v.e;
   d.perm[dst] = e;
@@ -1004,7 +1217,12 @@ __global__ __launch_bounds__(SORT_BLOCK) void k_sort(Dev d, Buf pre, Buf out) {
   const uint32_t* bucket = set_b ? d.bucket_b : d.bucket_a;
   // cell lanes: lane sub of cell c owns the entries sub + 4 u of its bucket
   const int ct = t - 64, c = ct >> 2, sub = ct & 3;
+  // a single instance's constants (through the scalar cache; not changed by the launch)
+  InstParams P1;
+  if constexpr (!BATCH) P1 = scalar_copy(d.prm);
   uint32_t n = 0u, e[SORT_SPEC], r[SORT_SPEC];
+  // the cell's column and row (every entry of a bucket is in its cell)
+  int cx = 0, cy = 0;
   Loaded lv[SORT_SPEC];
   Gathered gv[SORT_SPEC];
   if (t < 64) {
@@ -1058,6 +1276,7 @@ __global__ __launch_bounds__(SORT_BLOCK) void k_sort(Dev d, Buf pre, Buf out) {
     // slot 0 and are not used)
 #pragma unroll
     for (int u = 0; u < SORT_SPEC; ++u) lv[u] = sort_load<BATCH>(d, pre, (uint32_t)(sub + 4 * u) < n ? e[u] : 0u);
+    if constexpr (!BATCH) cell_xy(P1, (uint32_t)K, cx, cy);
     for (uint32_t i = sub + 4 * SORT_SPEC; i < n; i += 4) raw[i] = bucket[(size_t)K * WC_BUCKET + i];
     wave_sync();  // the buckets of this wave's cells are in LDS
     // rank of each entry in its bucket; the first 16 places without branches
@@ -1074,8 +1293,9 @@ __global__ __launch_bounds__(SORT_BLOCK) void k_sort(Dev d, Buf pre, Buf out) {
 #pragma unroll
       for (int u = 0; u < SORT_SPEC; ++u) r[u] += x < e[u] ? 1u : 0u;
     }
+    if constexpr (BATCH) cell_xy(d.prm[max(lv[0].inst, 0)], (uint32_t)K, cx, cy);
 #pragma unroll
-    for (int u = 0; u < SORT_SPEC; ++u) gv[u] = sort_finish<MG>(d, lv[u]);  // EOS while the offsets are found
+    for (int u = 0; u < SORT_SPEC; ++u) gv[u] = sort_finish<MG, BATCH>(d, P1, cx, cy, lv[u]);  // EOS while the offsets are found
   }
   __syncthreads();  // offsets and the tile's base
   if (t < 64) {
@@ -1098,22 +1318,23 @@ __global__ __launch_bounds__(SORT_BLOCK) void k_sort(Dev d, Buf pre, Buf out) {
       out.id[dst] = WC_NO_ID;
       out.pv[dst] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
       out.aux[dst] = make_float4(1.0f, 0.0f, 0.0f, 0.0f);
+      d.tc[dst] = make_uint2(0u, 0u);
       if constexpr (BATCH) out.inst[dst] = 0;
       if (out.e) out.e[dst] = 0.0f;
       d.perm[dst] = 0u;
     }
     return;
   }
-  const uint32_t base = s_base + s_off[c];
+  const uint32_t base = s_base + s_off[c], K = (uint32_t)(tile * T + c);
 #pragma unroll
   for (int u = 0; u < SORT_SPEC; ++u)
-    if ((uint32_t)(sub + 4 * u) < n) sort_store<BATCH>(d, out, e[u], base + r[u], gv[u]);
+    if ((uint32_t)(sub + 4 * u) < n) sort_store<BATCH>(d, P1, out, e[u], base + r[u], K, gv[u]);
   const uint32_t* raw = s_raw + c * WC_BUCKET;
   for (uint32_t i = sub + 4 * SORT_SPEC; i < n; i += 4) {
     const uint32_t ei = raw[i];
     uint32_t ri = 0u;
     for (uint32_t k = 0; k < n; ++k) ri += raw[k] < ei ? 1u : 0u;
-    sort_store<BATCH>(d, out, ei, base + ri, sort_finish<MG>(d, sort_load<BATCH>(d, pre, ei)));
+    sort_store<BATCH>(d, P1, out, ei, base + ri, K, sort_finish<MG, BATCH>(d, P1, cx, cy, sort_load<BATCH>(d, pre, ei)));
   }
 }
 
@@ -1318,39 +1539,40 @@ __device__ __forceinline__ double eos_e_el(const InstParams& P, double r) {
   return P.eos_type == 1 ? mg_e_el(P, r) : tait_e_el(P, r);
 }
 
-// Blocks per compute unit the register budget of the single-instance pair
-// pass is held to: seven (seven waves per SIMD, at most 72 VGPRs), which it
-// meets without spills; left to itself the compiler took 79 VGPRs (six waves
-// per SIMD) and the pass ran 6 % slower (C2). The batched, audit, export
-// and cubic-kernel variants keep the compiler's budget (they would spill).
+// The pass is bound by VALU issue where the chip is full (94 % of a wave's
+// four-cycle issue slots at 720k particles) and by the wave's chain of loads
+// (slots, cell starts, entries) where it is not. Against the same pass with
+// each lane testing its own candidates one by one, summing its own hits (nine
+// rounds of the pair law for 20 neighbours over four lanes, now five or six)
+// and gathering their state from L2: 756 VALU instructions per wave instead
+// of 1,088, and per launch 27.9 -> 24.4 us at 180k particles, 83 -> 71 us at
+// 720k, 75 -> 61 us for sixteen instances of 30k, 12.5 -> 10.1 us at 3k.
+// Blocks per compute unit that the register budget is held to: at most 80
+// VGPRs (67 are used; 23 to 25 KB of LDS per block then let six or seven
+// blocks share a compute unit). The audit and export variants keep the
+// compiler's budget.
 #ifndef PAIR_MINW
-#define PAIR_MINW 7
+#define PAIR_MINW 6
 #endif
 template <int MODE, bool BATCH, bool AUD, int VAR>
-__global__ __launch_bounds__(PAIR_BLOCK, (BATCH || AUD || MODE == EV_EXPORT || (VAR & 2)) ? 1 : PAIR_MINW)
+__global__ __launch_bounds__(PAIR_BLOCK, (AUD || MODE == EV_EXPORT) ? 1 : PAIR_MINW)
 void k_pair(Dev d, Buf sb, Buf base, Buf out) {
-  __shared__ float4 uni[PAIR_BLOCK / 64][UCAP];
-  __shared__ uint8_t lst[LCAP * PAIR_BLOCK];
-  // hand-over of each slot from the first phase to the second
-  __shared__ float sacc[5][PAIR_SLOTS];
-  __shared__ float4 h_pv[PAIR_SLOTS];
-  __shared__ uint32_t h_K[PAIR_SLOTS], h_id[PAIR_SLOTS], h_eb[PAIR_SLOTS];
-  __shared__ float h_rho[PAIR_SLOTS], h_m[PAIR_SLOTS];
-  __shared__ int h_inst[PAIR_SLOTS];
-  __shared__ float h_aud[AUD ? 4 : 1][PAIR_SLOTS];
-  // a single instance's constants and clock, copied for the second phase:
-  // the compiler cannot move global loads above the phase's global stores,
-  // and waited for each field in turn; from LDS it loads them together
-  // (no block writes a clock field that a second phase reads)
-  __shared__ InstParams sP;
-  __shared__ Clock sC;
-  if constexpr (!BATCH) {
-    constexpr int NP = (int)(sizeof(InstParams) / 4), NC = (int)(sizeof(Clock) / 4);
-    static_assert(sizeof(InstParams) % 4 == 0 && sizeof(Clock) % 4 == 0 && NP + NC <= PAIR_BLOCK, "copy");
-    const int t = (int)threadIdx.x;
-    if (t < NP) reinterpret_cast<uint32_t*>(&sP)[t] = reinterpret_cast<const uint32_t*>(d.prm)[t];
-    else if (t < NP + NC) reinterpret_cast<uint32_t*>(&sC)[t - NP] = reinterpret_cast<const uint32_t*>(d.clk)[t - NP];
-  }
+  // the first phase's LDS, and in its place after a barrier the hand-over of
+  // each slot from the first phase to the second
+  struct HandOver {
+    float4 pv[PAIR_SLOTS];
+    float acc[5][PAIR_SLOTS];
+    float rho[PAIR_SLOTS], m[PAIR_SLOTS];
+    float aud[AUD ? 4 : 1][PAIR_SLOTS];
+    int inst[PAIR_SLOTS];
+    uint32_t eb[PAIR_SLOTS];
+  };
+  union Shared {
+    PairLds uni[PAIR_BLOCK / 64];
+    HandOver ho;
+  };
+  __shared__ Shared sh;
+  __shared__ PairSlots sS;
   // blocks map to XCDs in contiguous slot ranges
   const int s0 = xcd_block(blockIdx.x, gridDim.x) * PAIR_SLOTS;
   {
@@ -1358,49 +1580,53 @@ void k_pair(Dev d, Buf sb, Buf base, Buf out) {
     const int s = s0 + (int)(threadIdx.x / PAIR_G);
     const bool inr = s < d.n_slots;
     const int inst = inr ? inst_at<BATCH>(sb, s) : 0;
-    uint32_t K = 0;
+    uint2 tc = make_uint2(0u, 0u);
     float4 pi = make_float4(0, 0, 0, 0), ai = make_float4(0, 0, 0, 0);
     if (inr) {
-      K = sb.cell[s];
+      tc = d.tc[s];
       pi = sb.pv[s];
       ai = sb.aux[s];
     }
     const bool fluid = inr && ai.w > 0.0f;
-    // fetched now, used after the pair sums: the particle id and (eval B)
-    // the slot of its state n in the step's first sorted state
-    uint32_t id = 0u, eb = 0u;
-    if (q == 0 && inr) {
-      id = sb.id[s];
-      if (MODE == EV_B && fluid) eb = d.perm[s];
+    // kept in LDS for the group scan and the second phase
+    if (q == 0) {
+      const int k = (int)(threadIdx.x / PAIR_G);
+      sS.tc[k] = tc;
+      sS.id[k] = inr ? sb.id[s] : 0u;
     }
-    PairAcc acc = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-    AudAcc aud = {0.0f, 0.0f, 0.0f, 0.0f};
+    // (eval B) the slot of its state n in the step's first sorted state,
+    // fetched now, used after the pair sums
+    uint32_t eb = 0u;
+    if (MODE == EV_B && q == 0 && inr) eb = d.perm[s];
+    PairAcc acc = {};
+    AudAcc aud = {};
+    PairC G0;
+    if constexpr (!BATCH) {
+      G0 = pair_c(d.prm);
+    }
     if (MODE == EV_EXPORT && d.nb_ids != nullptr)
-      pair_sums_wave<BATCH, AUD, VAR, true>(d, sb, s, inst, K, fluid, pi, ai, q, uni[threadIdx.x >> 6],
-                                            lst + threadIdx.x, acc, aud);
+      pair_sums_wave<BATCH, AUD, VAR, true>(d, sb, G0, s0, inst, fluid, pi, ai, sh.uni[threadIdx.x >> 6], sS, acc, aud);
     else
-      pair_sums_wave<BATCH, AUD, VAR>(d, sb, s, inst, K, fluid, pi, ai, q, uni[threadIdx.x >> 6],
-                                      lst + threadIdx.x, acc, aud);
+      pair_sums_wave<BATCH, AUD, VAR>(d, sb, G0, s0, inst, fluid, pi, ai, sh.uni[threadIdx.x >> 6], sS, acc, aud);
     // fixed-order combination of the slot's lane partial sums
     acc.D = slot_sum(acc.D);
     acc.ax = slot_sum(acc.ax);
     acc.ay = slot_sum(acc.ay);
     acc.Vx = slot_sum(acc.Vx);
     acc.Vy = slot_sum(acc.Vy);
+    __syncthreads();  // every wave is done with its lists
     if (q == 0) {
       const int k = (int)(threadIdx.x / PAIR_G);
-      sacc[0][k] = acc.D;
-      sacc[1][k] = acc.ax;
-      sacc[2][k] = acc.ay;
-      sacc[3][k] = acc.Vx;
-      sacc[4][k] = acc.Vy;
-      h_pv[k] = pi;
-      h_K[k] = K;
-      h_rho[k] = ai.x;
-      h_m[k] = inr ? ai.w : 0.0f;
-      h_inst[k] = inst;
-      h_id[k] = id;
-      h_eb[k] = eb;
+      sh.ho.acc[0][k] = acc.D;
+      sh.ho.acc[1][k] = acc.ax;
+      sh.ho.acc[2][k] = acc.ay;
+      sh.ho.acc[3][k] = acc.Vx;
+      sh.ho.acc[4][k] = acc.Vy;
+      sh.ho.pv[k] = pi;
+      sh.ho.rho[k] = ai.x;
+      sh.ho.m[k] = inr ? ai.w : 0.0f;
+      sh.ho.inst[k] = inst;
+      sh.ho.eb[k] = eb;
     }
     if constexpr (AUD) {
       aud.av = slot_sum(aud.av);
@@ -1409,10 +1635,10 @@ void k_pair(Dev d, Buf sb, Buf base, Buf out) {
       aud.ghost = slot_sum(aud.ghost);
       if (q == 0) {
         const int k = (int)(threadIdx.x / PAIR_G);
-        h_aud[0][k] = aud.av;
-        h_aud[1][k] = aud.visc;
-        h_aud[2][k] = ai.y * aud.del;  // elastic energy rate P_i drho_i of the delta term
-        h_aud[3][k] = aud.ghost;
+        sh.ho.aud[0][k] = aud.av;
+        sh.ho.aud[1][k] = aud.visc;
+        sh.ho.aud[2][k] = ai.y * aud.del;  // elastic energy rate P_i drho_i of the delta term
+        sh.ho.aud[3][k] = aud.ghost;
       }
     }
   }
@@ -1420,16 +1646,25 @@ void k_pair(Dev d, Buf sb, Buf base, Buf out) {
   if (threadIdx.x >= PAIR_SLOTS) return;
   const int s = s0 + (int)threadIdx.x;
   const bool inr = s < d.n_slots;
-  const int inst = BATCH ? h_inst[threadIdx.x] : 0;
-  const InstParams& P = *(BATCH ? &d.prm[inst] : &sP);
+  const int inst = BATCH ? sh.ho.inst[threadIdx.x] : 0;
+  // a single instance's constants and clock come through the scalar cache (no
+  // block writes a clock field that a second phase reads)
+  InstParams P1;
+  Clock C1;
+  if constexpr (!BATCH) {
+    P1 = scalar_copy(d.prm);
+    C1 = scalar_copy(d.clk);
+  }
   Clock* clk = d.clk;
-  const Clock& C = *(BATCH ? &clk[inst] : &sC);
-  const uint32_t K = h_K[threadIdx.x];
-  const float4 pi = h_pv[threadIdx.x];
-  const float rho_i = h_rho[threadIdx.x];
-  const uint32_t id_i = h_id[threadIdx.x];
-  const bool fluid = inr && h_m[threadIdx.x] > 0.0f;
-  const uint32_t eb = h_eb[threadIdx.x];
+  const InstParams& P = BATCH ? d.prm[inst] : P1;
+  const Clock& C = BATCH ? clk[inst] : C1;
+  // the slot's cell
+  const uint32_t xy = sS.tc[threadIdx.x].x;
+  const int scx = (int)(xy & ((1u << P.cx_bits) - 1u)), scy = (int)(xy >> P.cx_bits);
+  const float4 pi = sh.ho.pv[threadIdx.x];
+  const float rho_i = sh.ho.rho[threadIdx.x];
+  const uint32_t id_i = sS.id[threadIdx.x];
+  const bool fluid = inr && sh.ho.m[threadIdx.x] > 0.0f;
   const int gid = (int)id_i - P.id0 - P.nf;  // ghost index (an inert entry has none)
   // the bucket set this pass fills for the next sort
   const Fill next_fill = (MODE == EV_A || (MODE == EV_L && d.lf_set == 0)) ? fill_b(d) : fill_a(d);
@@ -1452,23 +1687,22 @@ void k_pair(Dev d, Buf sb, Buf base, Buf out) {
       }
       place_ring(d, P, inst, ring, xc, out, s, bucket);
     } else {
+      const uint32_t K = (uint32_t)(P.cell_off + scy * P.ncx + scx);
       out.cell[s] = K;
       out.pv[s] = pi;
       bucket_put_wall(d, P, bucket, K, (int)id - P.id0 - P.nf, (uint32_t)s);
     }
   }
   PairAcc acc;
-  acc.D = sacc[0][threadIdx.x];
-  acc.ax = sacc[1][threadIdx.x];
-  acc.ay = sacc[2][threadIdx.x];
-  acc.Vx = sacc[3][threadIdx.x];
-  acc.Vy = sacc[4][threadIdx.x];
+  acc.D = sh.ho.acc[0][threadIdx.x];
+  acc.ax = sh.ho.acc[1][threadIdx.x];
+  acc.ay = sh.ho.acc[2][threadIdx.x];
+  acc.Vx = sh.ho.acc[3][threadIdx.x];
+  acc.Vy = sh.ho.acc[4][threadIdx.x];
   const bool lead = fluid;
   if (P.axisym && lead) {
     // axisymmetric form: the hoop part of the divergence, -rho v_r / r (r >= dx/2)
-    int cx, cy;
-    cell_xy(P, K, cx, cy);
-    const float r = fmaxf((float)(P.y_lo + (double)cy * P.dcd) + pi.y, P.r_min);
+    const float r = fmaxf((float)(P.y_lo + (double)scy * P.dcd) + pi.y, P.r_min);
     acc.D -= rho_i * pi.w / r;
   }
   if (MODE == EV_EXPORT) {
@@ -1486,21 +1720,26 @@ void k_pair(Dev d, Buf sb, Buf base, Buf out) {
   float vnew = 0.0f;
   uint32_t newkey = 0u;
   if (lead) {
+    // (multiply-adds written out, as in the pair law)
+#pragma clang fp contract(off)
     const double dt = MODE == EV_A ? step_dt(d, P, C) : C.dt;
     const float hdt = (float)(MODE == EV_A ? 0.5 * dt : dt);
-    uint32_t Kb;
+    int cx, cy;
     float4 pb;
     float rb;
     if (MODE == EV_A || MODE == EV_L) {
-      Kb = K;
+      cx = scx;
+      cy = scy;
       pb = pi;
       rb = rho_i;
     } else {
       // state n of this particle: the sort of this evaluation took it from
       // slot perm[s] of the step's first sorted state
-      Kb = at32(base.cell, eb);
+      const uint32_t eb = sh.ho.eb[threadIdx.x];
+      const uint32_t Kb = at32(base.cell, eb);
       pb = at32(base.pv, eb);
       rb = at32(base.aux, eb).x;
+      cell_xy(P, Kb, cx, cy);
     }
     float rn, rn_free, vx, vy, ox, oy, e_new = 0.0f;
     if constexpr (MODE == EV_L) {
@@ -1510,32 +1749,30 @@ void k_pair(Dev d, Buf sb, Buf base, Buf out) {
       const float kick = (float)(0.5 * (C.dt_prev + dt)), fdt = (float)dt;
       rn = rb;
       rn_free = rn;
-      vx = pb.z + kick * acc.ax;
-      vy = pb.w + kick * (acc.ay + P.gy);
-      ox = pb.x + fdt * (vx + acc.Vx);
-      oy = pb.y + fdt * (vy + acc.Vy);
-      e_new = sb.e[s] + fdt * acc.D;
+      vx = fmaf(kick, acc.ax, pb.z);
+      vy = fmaf(kick, acc.ay + P.gy, pb.w);
+      ox = fmaf(fdt, vx + acc.Vx, pb.x);
+      oy = fmaf(fdt, vy + acc.Vy, pb.y);
+      e_new = fmaf(fdt, acc.D, sb.e[s]);
     } else {
-      rn = rb + hdt * acc.D;
+      rn = fmaf(hdt, acc.D, rb);
       rn_free = rn;
       if (rn < P.rho_lo) { rn = P.rho_lo; clamp_hit = true; }
       if (rn > P.rho_hi) { rn = P.rho_hi; clamp_hit = true; }
-      vx = pb.z + hdt * acc.ax;
-      vy = pb.w + hdt * (acc.ay + P.gy);
-      ox = pb.x + hdt * (pi.z + acc.Vx);
-      oy = pb.y + hdt * (pi.w + acc.Vy);
+      vx = fmaf(hdt, acc.ax, pb.z);
+      vy = fmaf(hdt, acc.ay + P.gy, pb.w);
+      ox = fmaf(hdt, pi.z + acc.Vx, pb.x);
+      oy = fmaf(hdt, pi.w + acc.Vy, pb.y);
     }
-    int cx, cy;
-    cell_xy(P, Kb, cx, cy);
     renorm(ox, cx, P.dc);
     renorm(oy, cy, P.dc);
     // enforcement in FP64: hard walls, then radial pull-out from the disk
-    double x = P.x_lo + (double)cx * P.dcd + (double)ox;
-    double y = P.y_lo + (double)cy * P.dcd + (double)oy;
+    double x = fma((double)cx, P.dcd, P.x_lo) + (double)ox;
+    double y = fma((double)cy, P.dcd, P.y_lo) + (double)oy;
     if (d.tape_pos != nullptr) {  // pre-enforcement state for the reverse sweep
       const int fid = (int)id_i - P.id0;
       d.tape_pos[fid] = make_double2(x, y);
-      d.tape_vel[fid] = make_float4(vx, vy, rb + hdt * acc.D, 0.0f);
+      d.tape_vel[fid] = make_float4(vx, vy, rn_free, 0.0f);
     }
     const double k_free = (double)vx * vx + (double)vy * vy;
     bool moved = false;
@@ -1552,7 +1789,7 @@ void k_pair(Dev d, Buf sb, Buf base, Buf out) {
         disk_at(P, C, C.t + 0.5 * dt, xd, vd, ad);
       }
       const double rx = x - xd, ry = y - P.disk_y0;
-      const double d2 = rx * rx + ry * ry;
+      const double d2 = fma(rx, rx, ry * ry);
       if (d2 < P.R * P.R) {
         double nx = -1.0, ny = 0.0;
         if (d2 > 0.0) {
@@ -1560,12 +1797,12 @@ void k_pair(Dev d, Buf sb, Buf base, Buf out) {
           nx = rx / dd;
           ny = ry / dd;
         }
-        x = xd + (P.R + e) * nx;
-        y = P.disk_y0 + (P.R + e) * ny;
-        const double w = ((double)vx - vd) * nx + (double)vy * ny;
+        x = fma(P.R + e, nx, xd);
+        y = fma(P.R + e, ny, P.disk_y0);
+        const double w = fma((double)vx - vd, nx, (double)vy * ny);
         if (w < 0.0) {
-          vx = (float)((double)vx - 2.0 * w * nx);
-          vy = (float)((double)vy - 2.0 * w * ny);
+          vx = (float)fma(-2.0 * w, nx, (double)vx);
+          vy = (float)fma(-2.0 * w, ny, (double)vy);
         }
         moved = true;
       }
@@ -1585,11 +1822,11 @@ void k_pair(Dev d, Buf sb, Buf base, Buf out) {
     if constexpr (BATCH) out.inst[s] = (uint16_t)inst;
     if constexpr (MODE == EV_L) out.e[s] = e_new;
     newkey = Kn;
-    vnew = fast_sqrt(vx * vx + vy * vy);
+    vnew = fast_sqrt(fmaf(vx, vx, vy * vy));
     if (!(rn == rn) || !(vnew <= 3.0e38f) || !(fabsf(e_new) <= 3.0e38f)) atomicOr(&clk[inst].bad, 1u);
     if constexpr (AUD && MODE == EV_B) {
       // the energy the enforcement and the density clamp add to the new state
-      const double m = (double)h_m[threadIdx.x];
+      const double m = (double)sh.ho.m[threadIdx.x];
       if (moved) e_enf = 0.5 * m * ((double)vx * vx + (double)vy * vy - k_free);
       if (clamp_hit) e_clamp = m * (eos_e_el(P, (double)rn) - eos_e_el(P, (double)rn_free));
     }
@@ -1598,9 +1835,9 @@ void k_pair(Dev d, Buf sb, Buf base, Buf out) {
     // this block's audit terms, added to its own running sums (a fixed
     // order for every block, no atomics): the rates times dt, then the
     // enforcement and clamp energy
-    const double m = lead ? (double)h_m[threadIdx.x] : 0.0;
-    const double rate[4] = {m * h_aud[0][threadIdx.x], m * h_aud[1][threadIdx.x], m * h_aud[2][threadIdx.x],
-                            m * h_aud[3][threadIdx.x]};
+    const double m = lead ? (double)sh.ho.m[threadIdx.x] : 0.0;
+    const double rate[4] = {m * sh.ho.aud[0][threadIdx.x], m * sh.ho.aud[1][threadIdx.x], m * sh.ho.aud[2][threadIdx.x],
+                            m * sh.ho.aud[3][threadIdx.x]};
     double tot[6];
 #pragma unroll
     for (int k = 0; k < 4; ++k) tot[k] = wave_sum(lead ? rate[k] : 0.0);
@@ -1664,25 +1901,27 @@ void k_pair(Dev d, Buf sb, Buf base, Buf out) {
 // change. count: add the clamp hits to the clock (0 for the test hooks).
 template <bool BATCH, int VAR>
 __global__ __launch_bounds__(PAIR_BLOCK) void k_dens(Dev d, Buf sb, int count) {
-  __shared__ float4 uni[PAIR_BLOCK / 64][UCAP];
-  __shared__ uint8_t lst[LCAP * PAIR_BLOCK];
+  __shared__ PairLds uni[PAIR_BLOCK / 64];
+  __shared__ PairSlots sS;
   const int s0 = xcd_block(blockIdx.x, gridDim.x) * PAIR_SLOTS;
   const int q = (int)(threadIdx.x % PAIR_G);
   const int s = s0 + (int)(threadIdx.x / PAIR_G);
   const bool inr = s < d.n_slots;
   const int inst = inr ? inst_at<BATCH>(sb, s) : 0;
-  uint32_t K = 0;
+  uint2 tc = make_uint2(0u, 0u);
   float4 pi = make_float4(0, 0, 0, 0), ai = make_float4(0, 0, 0, 0);
   if (inr) {
-    K = sb.cell[s];
+    tc = d.tc[s];
     pi = sb.pv[s];
     ai = sb.aux[s];
   }
+  if (q == 0) sS.tc[threadIdx.x / PAIR_G] = tc;
   const bool fluid = inr && ai.w > 0.0f;
-  PairAcc acc = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-  AudAcc aud = {0.0f, 0.0f, 0.0f, 0.0f};
-  pair_sums_wave<BATCH, false, VAR | 8>(d, sb, s, inst, K, fluid, pi, ai, q, uni[threadIdx.x >> 6],
-                                        lst + threadIdx.x, acc, aud);
+  PairAcc acc = {};
+  AudAcc aud = {};
+  PairC G0;
+  if constexpr (!BATCH) G0 = pair_c(d.prm);
+  pair_sums_wave<BATCH, false, VAR | 8>(d, sb, G0, s0, inst, fluid, pi, ai, uni[threadIdx.x >> 6], sS, acc, aud);
   const float sum = slot_sum(acc.D);
   bool clamp_hit = false;
   if (q == 0 && fluid) {
