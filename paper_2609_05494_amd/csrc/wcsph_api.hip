@@ -66,6 +66,43 @@ void* scratch_address() {
   return g_scratch_ptr[dev];
 }
 
+// Page-locked host memory through which the short reads of a context come
+// (the GPU writes it), one block per context. Blocks of closed contexts are
+// kept for the next ones, at most WC_PIN_SPARE of them.
+#define WC_PIN_BYTES (1u << 20)
+#define WC_PIN_HEAD 1024  // the clocks in front of the data
+#define WC_PIN_SPARE 4
+static_assert(2 * sizeof(Clock) <= WC_PIN_HEAD, "clocks in front of the data");
+std::mutex g_pin_mu;
+void* g_pin_spare[WC_PIN_SPARE] = {};
+void* pin_take() {
+  {
+    std::lock_guard<std::mutex> lk(g_pin_mu);
+    for (void*& q : g_pin_spare)
+      if (q) {
+        void* p = q;
+        q = nullptr;
+        return p;
+      }
+  }
+  void* p = nullptr;
+  if (hipHostMalloc(&p, WC_PIN_BYTES, hipHostMallocPortable) != hipSuccess || p == nullptr)
+    throw WcError{WCSPH_E_OOM, "page-locked host allocation failed"};
+  return p;
+}
+void pin_give(void* p) {
+  if (!p) return;
+  {
+    std::lock_guard<std::mutex> lk(g_pin_mu);
+    for (void*& q : g_pin_spare)
+      if (!q) {
+        q = p;
+        return;
+      }
+  }
+  (void)hipHostFree(p);
+}
+
 // Host-side geometry of one instance (FP64).
 struct HostInst {
   std::vector<double> fx, fy, frho;  // fluid lattice (id order)
@@ -117,6 +154,8 @@ struct wcsph_ctx {
   double* d_dt = nullptr;
   size_t d_dt_cap = 0;
   double* d_disk = nullptr;  // disk state query output (3 doubles)
+  char* hpin = nullptr;      // page-locked host block of the short reads: two clocks, then the data
+  char* d_read = nullptr;    // device side of a short read of the fluid state (WC_PIN_BYTES)
   bool audit = false;        // energy audit in the second pair pass (single instance)
   bool dead = false;
   // reverse sweep
@@ -448,10 +487,7 @@ void sync(wcsph_ctx* c) { HC(hipStreamSynchronize(c->st)); }
 // state (this instance); on instance 0 for the whole context: 4 corrupted
 // permutation, 8 a cell holds more than WC_BUCKET particles. Sets the error text and returns true when
 // any is set; the outputs already written stay for inspection.
-bool state_invalid(wcsph_ctx* ctx, int inst) {
-  Clock k, k0;
-  HC(hipMemcpy(&k, ctx->d_clk + inst, sizeof k, hipMemcpyDeviceToHost));
-  HC(hipMemcpy(&k0, ctx->d_clk, sizeof k0, hipMemcpyDeviceToHost));
+bool clocks_invalid(wcsph_ctx* ctx, const Clock& k, const Clock& k0) {
   const unsigned bad = k.bad | (k0.bad & ~1u);
   if (!bad) return false;
   std::string m;
@@ -461,6 +497,16 @@ bool state_invalid(wcsph_ctx* ctx, int inst) {
   ctx->err = "state invalid (flags " + std::to_string(bad) + "):" + m;
   return true;
 }
+
+bool state_invalid(wcsph_ctx* ctx, int inst) {
+  Clock k, k0;
+  HC(hipMemcpy(&k, ctx->d_clk + inst, sizeof k, hipMemcpyDeviceToHost));
+  HC(hipMemcpy(&k0, ctx->d_clk, sizeof k0, hipMemcpyDeviceToHost));
+  return clocks_invalid(ctx, k, k0);
+}
+// The same from the clocks that a packed read has brought along.
+Clock* pin_clocks(wcsph_ctx* c) { return reinterpret_cast<Clock*>(c->hpin); }
+bool pin_invalid(wcsph_ctx* c) { return clocks_invalid(c, pin_clocks(c)[0], pin_clocks(c)[1]); }
 
 // Refill the buckets of the next sort from the state in X (after the state,
 // the clocks or the disk law changed from the host).
@@ -718,6 +764,8 @@ void build(wcsph_ctx* c, const wcsph_params* params, int n_inst) {
   d.diag_part = dalloc_n<double>(c, (size_t)n_inst * WC_DIAG_BLOCKS * WC_DIAG_PARTS);
   d.wb_part = dalloc_n<double>(c, (size_t)n_inst * WC_MAX_RING);
   c->d_disk = dalloc_n<double>(c, 3);
+  c->d_read = dalloc_n<char>(c, WC_PIN_BYTES);
+  c->hpin = static_cast<char*>(pin_take());
   d.var = params[0].kernel_type == 1 ? 2 : 0;
   for (int i = 0; i < n_inst; ++i) {
     if (params[i].beta > 0) d.var |= 1;
@@ -784,6 +832,8 @@ void release(wcsph_ctx* c) {
     else hipFree(p);
   }
   c->blocks.clear();
+  pin_give(c->hpin);
+  c->hpin = nullptr;
 }
 
 wcsph_status create_impl(const wcsph_params* params, int n_inst, const wcsph_allocator* alloc,
@@ -1225,31 +1275,26 @@ wcsph_status wcsph_read_probes(wcsph_ctx* ctx, int inst, double* t, double* dt, 
   API_BEGIN(ctx)
   require(inst >= 0 && inst < ctx->n_inst, "instance out of range");
   require(max_rows >= 0 && rows_out != nullptr, "rows_out required");
-  sync(ctx);
   long long& rd = ctx->hist_read[inst];
   if (ctx->steps - rd > WC_HIST_CAP) rd = ctx->steps - WC_HIST_CAP;
   const long long rows = std::min<long long>(ctx->steps - rd, max_rows);
   const int np = ctx->hp[inst].n_probes;
-  const size_t base = (size_t)inst * WC_HIST_CAP;
-  // the rows are at most two contiguous runs of the ring
-  std::vector<float> rowbuf;
-  for (long long r = 0; r < rows;) {
-    const size_t k0 = (size_t)((rd + r) % WC_HIST_CAP);
-    const long long run = std::min<long long>(rows - r, (long long)(WC_HIST_CAP - k0));
-    if (t) HC(hipMemcpy(t + r, ctx->d.hist_t + base + k0, (size_t)run * 8, hipMemcpyDeviceToHost));
-    if (dt) HC(hipMemcpy(dt + r, ctx->d.hist_dt + base + k0, (size_t)run * 8, hipMemcpyDeviceToHost));
-    if (p && np) {
-      rowbuf.resize((size_t)run * WC_MAX_PROBES);
-      HC(hipMemcpy(rowbuf.data(), ctx->d.hist_p + (base + k0) * WC_MAX_PROBES, rowbuf.size() * 4,
-                   hipMemcpyDeviceToHost));
-      for (long long q = 0; q < run; ++q)
-        std::copy(rowbuf.begin() + q * WC_MAX_PROBES, rowbuf.begin() + q * WC_MAX_PROBES + np, p + (r + q) * np);
-    }
-    r += run;
+  // the rows packed by the GPU into the page-locked block, as many as it holds at once
+  const long long per = (long long)((WC_PIN_BYTES - WC_PIN_HEAD) / (2 * sizeof(double) + (size_t)np * sizeof(float)));
+  for (long long r = 0; r < rows || r == 0; r += per) {
+    const int n = (int)std::min(per, rows - r);
+    double* pt = reinterpret_cast<double*>(ctx->hpin + WC_PIN_HEAD);
+    float* pp = reinterpret_cast<float*>(pt + 2 * n);
+    wc_enqueue_read_probes(ctx->d, inst, rd + r, n, p ? np : 0, pt, pt + n, pp, pin_clocks(ctx), ctx->st);
+    HC(hipGetLastError());
+    sync(ctx);
+    if (t) std::copy(pt, pt + n, t + r);
+    if (dt) std::copy(pt + n, pt + 2 * n, dt + r);
+    if (p) std::copy(pp, pp + (size_t)n * np, p + r * np);
   }
   rd += rows;
   *rows_out = (int)rows;
-  if (state_invalid(ctx, inst)) return WCSPH_E_UNSTABLE;
+  if (pin_invalid(ctx)) return WCSPH_E_UNSTABLE;
   API_END(ctx)
 }
 
@@ -1257,21 +1302,18 @@ wcsph_status wcsph_read_diagnostics(wcsph_ctx* ctx, int inst, wcsph_diag* out, i
   API_BEGIN(ctx)
   require(inst >= 0 && inst < ctx->n_inst, "instance out of range");
   require(max >= 0 && n_out != nullptr, "n_out required");
-  sync(ctx);
   long long& rd = ctx->diag_read[inst];
   if (ctx->diag_rows[inst] - rd > WC_DIAG_CAP) rd = ctx->diag_rows[inst] - WC_DIAG_CAP;
   const long long rows = std::min<long long>(ctx->diag_rows[inst] - rd, max);
-  // the rows are at most two contiguous runs of the ring
-  std::vector<double> all((size_t)rows * WC_NDIAG);
-  for (long long r = 0; r < rows;) {
-    const size_t k0 = (size_t)((rd + r) % WC_DIAG_CAP);
-    const long long run = std::min<long long>(rows - r, (long long)(WC_DIAG_CAP - k0));
-    HC(hipMemcpy(all.data() + (size_t)r * WC_NDIAG, ctx->d.diag + ((size_t)inst * WC_DIAG_CAP + k0) * WC_NDIAG,
-                 (size_t)run * WC_NDIAG * sizeof(double), hipMemcpyDeviceToHost));
-    r += run;
-  }
+  // the records packed by the GPU into the page-locked block (the whole ring of them fits)
+  static_assert((size_t)WC_DIAG_CAP * WC_NDIAG * sizeof(double) + WC_PIN_HEAD <= WC_PIN_BYTES, "records of a read");
+  const double* all = reinterpret_cast<const double*>(ctx->hpin + WC_PIN_HEAD);
+  wc_enqueue_read_diag(ctx->d, inst, rd, (int)rows, reinterpret_cast<double*>(ctx->hpin + WC_PIN_HEAD), pin_clocks(ctx),
+                       ctx->st);
+  HC(hipGetLastError());
+  sync(ctx);
   for (long long r = 0; r < rows; ++r) {
-    const double* v = all.data() + (size_t)r * WC_NDIAG;
+    const double* v = all + (size_t)r * WC_NDIAG;
     wcsph_diag& o = out[r];
     o.t = v[0];
     o.dt = v[1];
@@ -1298,7 +1340,7 @@ wcsph_status wcsph_read_diagnostics(wcsph_ctx* ctx, int inst, wcsph_diag* out, i
   }
   rd += rows;
   *n_out = (int)rows;
-  if (state_invalid(ctx, inst)) return WCSPH_E_UNSTABLE;
+  if (pin_invalid(ctx)) return WCSPH_E_UNSTABLE;
   API_END(ctx)
 }
 
@@ -1308,29 +1350,33 @@ wcsph_status wcsph_get_fluid(wcsph_ctx* ctx, int inst, double* t, double* x, dou
   require(inst >= 0 && inst < ctx->n_inst, "instance out of range");
   const InstParams& q = ctx->hp[inst];
   if (n < q.nf) throw WcError{WCSPH_E_RANGE, "output arrays shorter than the fluid count"};
-  sync(ctx);
-  const size_t N = ctx->n_slots;
-  auto cell = d2h(ctx, ctx->b.X.cell, N);
-  auto id = d2h(ctx, ctx->b.X.id, N);
-  auto pv = d2h(ctx, ctx->b.X.pv, N);
-  auto aux = d2h(ctx, ctx->b.X.aux, N);
-  for (size_t s = 0; s < N; ++s) {
-    const int k = (int)id[s] - q.id0;
-    if (k < 0 || k >= q.nf) continue;
-    double xx, yy;
-    decode(q, cell[s], pv[s].x, pv[s].y, xx, yy);
-    if (x) x[k] = xx;
-    if (y) y[k] = yy;
-    if (vx) vx[k] = pv[s].z;
-    if (vy) vy[k] = pv[s].w;
-    if (rho) rho[k] = aux[s].x;
+  // decoded in id order on the GPU; a short state through the page-locked
+  // block in one copy, a long one from work buffers that hold nothing between
+  // steps (the sorted and the predicted state) straight to the caller's arrays
+  const size_t nf = (size_t)q.nf, bytes = nf * sizeof(double);
+  double* const host[5] = {x, y, vx, vy, rho};
+  if (5 * bytes + WC_PIN_HEAD <= WC_PIN_BYTES) {
+    double* dv = reinterpret_cast<double*>(ctx->d_read);
+    double* const out[5] = {dv, dv + nf, dv + 2 * nf, dv + 3 * nf, dv + 4 * nf};
+    wc_enqueue_read_fluid(ctx->d, ctx->b, inst, out, pin_clocks(ctx), ctx->st);
+    HC(hipGetLastError());
+    HC(hipMemcpyAsync(ctx->hpin + WC_PIN_HEAD, dv, 5 * bytes, hipMemcpyDeviceToHost, ctx->st));
+    sync(ctx);
+    const double* pv = reinterpret_cast<const double*>(ctx->hpin + WC_PIN_HEAD);
+    for (int k = 0; k < 5; ++k)
+      if (host[k]) std::copy(pv + k * nf, pv + (k + 1) * nf, host[k]);
+  } else {
+    double* const out[5] = {reinterpret_cast<double*>(ctx->b.Y.pv), reinterpret_cast<double*>(ctx->b.Y.pv) + nf,
+                            reinterpret_cast<double*>(ctx->b.Y.aux), reinterpret_cast<double*>(ctx->b.Y.aux) + nf,
+                            reinterpret_cast<double*>(ctx->b.Z.pv)};
+    wc_enqueue_read_fluid(ctx->d, ctx->b, inst, out, pin_clocks(ctx), ctx->st);
+    HC(hipGetLastError());
+    for (int k = 0; k < 5; ++k)
+      if (host[k]) HC(hipMemcpyAsync(host[k], out[k], bytes, hipMemcpyDeviceToHost, ctx->st));
+    sync(ctx);
   }
-  if (t) {
-    Clock k;
-    HC(hipMemcpy(&k, ctx->d_clk + inst, sizeof k, hipMemcpyDeviceToHost));
-    *t = k.t_next;
-  }
-  if (state_invalid(ctx, inst)) return WCSPH_E_UNSTABLE;
+  if (t) *t = pin_clocks(ctx)[0].t_next;
+  if (pin_invalid(ctx)) return WCSPH_E_UNSTABLE;
   API_END(ctx)
 }
 
@@ -1340,18 +1386,26 @@ wcsph_status wcsph_get_internal_energy(wcsph_ctx* ctx, int inst, double* e, int 
   require(e != nullptr, "e required");
   const InstParams& q = ctx->hp[inst];
   if (n < q.nf) throw WcError{WCSPH_E_RANGE, "output array shorter than the fluid count"};
-  sync(ctx);
-  for (int k = 0; k < q.nf; ++k) e[k] = 0.0;
-  if (ctx->b.X.e) {
-    const size_t N = ctx->n_slots;
-    auto id = d2h(ctx, ctx->b.X.id, N);
-    auto ev = d2h(ctx, ctx->b.X.e, N);
-    for (size_t s = 0; s < N; ++s) {
-      const int k = (int)id[s] - q.id0;
-      if (k >= 0 && k < q.nf) e[k] = ev[s];
-    }
+  if (!ctx->b.X.e) {
+    sync(ctx);
+    for (int k = 0; k < q.nf; ++k) e[k] = 0.0;
+    if (state_invalid(ctx, inst)) return WCSPH_E_UNSTABLE;
+    return WCSPH_OK;
   }
-  if (state_invalid(ctx, inst)) return WCSPH_E_UNSTABLE;
+  double* dv = reinterpret_cast<double*>(ctx->b.Y.pv);  // (holds nothing between steps)
+  const size_t bytes = (size_t)q.nf * sizeof(double);
+  wc_enqueue_read_energy(ctx->d, ctx->b, inst, dv, pin_clocks(ctx), ctx->st);
+  HC(hipGetLastError());
+  if (bytes + WC_PIN_HEAD <= WC_PIN_BYTES) {
+    HC(hipMemcpyAsync(ctx->hpin + WC_PIN_HEAD, dv, bytes, hipMemcpyDeviceToHost, ctx->st));
+    sync(ctx);
+    const double* pv = reinterpret_cast<const double*>(ctx->hpin + WC_PIN_HEAD);
+    std::copy(pv, pv + q.nf, e);
+  } else {
+    HC(hipMemcpyAsync(e, dv, bytes, hipMemcpyDeviceToHost, ctx->st));
+    sync(ctx);
+  }
+  if (pin_invalid(ctx)) return WCSPH_E_UNSTABLE;
   API_END(ctx)
 }
 

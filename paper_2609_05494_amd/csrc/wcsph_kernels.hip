@@ -18,6 +18,8 @@
 
 #include <hip/hip_fp16.h>
 
+#include <algorithm>
+
 #include "wcsph_launch.h"
 #include "wcsph_kin.h"
 
@@ -2154,6 +2156,71 @@ __global__ __launch_bounds__(64) void k_diag_final(Dev d) {
   if (tot[7] > 0.0 || !(tot[3] == tot[3])) C.bad |= 1u;
 }
 
+// What the host reads of a context, packed by one launch so that a read costs
+// one wait and not a blocking copy per field (about 15 us each). `clk`: the
+// clocks of instance i and of instance 0 (the validity flags), written by the
+// first block straight into host memory, as are the short rows.
+__device__ __forceinline__ void read_clocks(const Dev& d, int i, Clock* clk) {
+  constexpr int N = (int)(sizeof(Clock) / 8);
+  const int t = (int)threadIdx.x;
+  if (blockIdx.x != 0 || t >= 2 * N) return;
+  const Clock* src = t < N ? d.clk + i : d.clk;
+  reinterpret_cast<unsigned long long*>(clk)[t] = reinterpret_cast<const unsigned long long*>(src)[t < N ? t : t - N];
+}
+
+// The fluid state of instance i in particle-id order, decoded to FP64. One
+// pass over the slots at 24 B read and 40 B written per particle, in place of
+// copying the slot arrays and decoding them on one host core.
+__global__ __launch_bounds__(WC_BLOCK) void k_read_fluid(Dev d, Buf X, int i, double* x, double* y, double* vx,
+                                                         double* vy, double* rho, Clock* clk) {
+#pragma clang fp contract(off)
+  read_clocks(d, i, clk);
+  const int s = blockIdx.x * WC_BLOCK + threadIdx.x;
+  if (s >= d.n_slots) return;
+  const InstParams& P = d.prm[i];
+  const int k = (int)X.id[s] - P.id0;
+  if (k < 0 || k >= P.nf) return;
+  int cx, cy;
+  cell_xy(P, X.cell[s], cx, cy);
+  const float4 pv = X.pv[s];
+  x[k] = P.x_lo + (double)cx * P.dcd + (double)pv.x;
+  y[k] = P.y_lo + (double)cy * P.dcd + (double)pv.y;
+  vx[k] = (double)pv.z;
+  vy[k] = (double)pv.w;
+  rho[k] = (double)X.aux[s].x;
+}
+
+// Specific internal energy of instance i by particle id (scheme 1).
+__global__ __launch_bounds__(WC_BLOCK) void k_read_energy(Dev d, Buf X, int i, double* e, Clock* clk) {
+  read_clocks(d, i, clk);
+  const int s = blockIdx.x * WC_BLOCK + threadIdx.x;
+  if (s >= d.n_slots) return;
+  const InstParams& P = d.prm[i];
+  const int k = (int)X.id[s] - P.id0;
+  if (k >= 0 && k < P.nf) e[k] = (double)X.e[s];
+}
+
+// Rows first, first + 1, ... of instance i's probe history (t, dt, np pressures each).
+__global__ __launch_bounds__(WC_BLOCK) void k_read_probes(Dev d, int i, long long first, int rows, int np, double* t,
+                                                          double* dt, float* p, Clock* clk) {
+  read_clocks(d, i, clk);
+  const long long base = (long long)i * WC_HIST_CAP;
+  for (int r = blockIdx.x * WC_BLOCK + threadIdx.x; r < rows; r += gridDim.x * WC_BLOCK) {
+    const long long k = base + (first + r) % WC_HIST_CAP;
+    t[r] = d.hist_t[k];
+    dt[r] = d.hist_dt[k];
+    for (int j = 0; j < np; ++j) p[(size_t)r * np + j] = d.hist_p[k * WC_MAX_PROBES + j];
+  }
+}
+
+// Records first, first + 1, ... of instance i's diagnostics.
+__global__ __launch_bounds__(WC_BLOCK) void k_read_diag(Dev d, int i, long long first, int rows, double* out,
+                                                        Clock* clk) {
+  read_clocks(d, i, clk);
+  for (int u = blockIdx.x * WC_BLOCK + threadIdx.x; u < rows * WC_NDIAG; u += gridDim.x * WC_BLOCK)
+    out[u] = d.diag[((long long)i * WC_DIAG_CAP + (first + u / WC_NDIAG) % WC_DIAG_CAP) * WC_NDIAG + u % WC_NDIAG];
+}
+
 // Test hook: in-support neighbour count and id sum per sorted slot.
 __global__ __launch_bounds__(WC_BLOCK) void k_neigh(Dev d, Buf sb) {
   const int s = blockIdx.x * WC_BLOCK + threadIdx.x;
@@ -2323,6 +2390,21 @@ void wc_enqueue_export_pair(const Dev& d, const Bufs& b, hipStream_t st) {
 void wc_enqueue_pair_a(const Dev& d, const Bufs& b, bool batch, hipStream_t st) {
   if (batch) launch_pair<EV_A, true>(d, b.Y, b.Y, b.Z, st);
   else launch_pair<EV_A, false>(d, b.Y, b.Y, b.Z, st);
+}
+
+static_assert(2 * (sizeof(Clock) / 8) <= WC_BLOCK && sizeof(Clock) % 8 == 0, "clocks of a read");
+void wc_enqueue_read_fluid(const Dev& d, const Bufs& b, int i, double* const out[5], Clock* clk, hipStream_t st) {
+  k_read_fluid<<<NB(d.n_slots), WC_BLOCK, 0, st>>>(d, b.X, i, out[0], out[1], out[2], out[3], out[4], clk);
+}
+void wc_enqueue_read_energy(const Dev& d, const Bufs& b, int i, double* e, Clock* clk, hipStream_t st) {
+  k_read_energy<<<NB(d.n_slots), WC_BLOCK, 0, st>>>(d, b.X, i, e, clk);
+}
+void wc_enqueue_read_probes(const Dev& d, int i, long long first, int rows, int np, double* t, double* dt, float* p,
+                            Clock* clk, hipStream_t st) {
+  k_read_probes<<<std::min(std::max(NB(rows), 1), 64), WC_BLOCK, 0, st>>>(d, i, first, rows, np, t, dt, p, clk);
+}
+void wc_enqueue_read_diag(const Dev& d, int i, long long first, int rows, double* out, Clock* clk, hipStream_t st) {
+  k_read_diag<<<std::min(std::max(NB(rows * WC_NDIAG), 1), 64), WC_BLOCK, 0, st>>>(d, i, first, rows, out, clk);
 }
 
 void wc_enqueue_neigh(const Dev& d, const Bufs& b, hipStream_t st) {

@@ -29,6 +29,15 @@ void wc_enqueue_export_ghosts(const Dev& d, const Bufs& b, int n_gblk, hipStream
 void wc_enqueue_export_pair(const Dev& d, const Bufs& b, hipStream_t st);
 void wc_enqueue_pair_a(const Dev& d, const Bufs& b, bool batch, hipStream_t st);
 void wc_enqueue_neigh(const Dev& d, const Bufs& b, hipStream_t st);
+// Reads of the host, packed on the device; clk: the clocks of instance i and
+// of instance 0 (host memory the GPU can write).
+// Fluid state of instance i in id order, FP64: x, y, vx, vy, rho (device).
+void wc_enqueue_read_fluid(const Dev& d, const Bufs& b, int i, double* const out[5], Clock* clk, hipStream_t st);
+void wc_enqueue_read_energy(const Dev& d, const Bufs& b, int i, double* e, Clock* clk, hipStream_t st);
+// Probe-history rows / diagnostic records from `first` on.
+void wc_enqueue_read_probes(const Dev& d, int i, long long first, int rows, int np, double* t, double* dt, float* p,
+                            Clock* clk, hipStream_t st);
+void wc_enqueue_read_diag(const Dev& d, int i, long long first, int rows, double* out, Clock* clk, hipStream_t st);
 
 // One evaluation (A: sort of X into Y, ghosts, pair sums + predictor into Z;
 // B: sort of Z into W with state n into X, ghosts, pair sums + corrector)
