@@ -21,6 +21,7 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 # the library built in-tree; WCSPH_LIB names another build of it (e.g. a tuner variant)
 LIB_PATH = os.environ.get("WCSPH_LIB", os.path.join(PKG, "libwcsph.so"))
 MAX_PROBES = 16
+HIST_CAP = 65536  # steps that the library's probe-history ring holds
 
 OK, E_INVALID, E_OOM, E_HIP, E_STATE, E_UNSTABLE, E_RANGE = range(7)
 _STATUS = {0: "OK", 1: "E_INVALID", 2: "E_OOM", 3: "E_HIP", 4: "E_STATE", 5: "E_UNSTABLE", 6: "E_RANGE"}
@@ -82,6 +83,9 @@ class Diag(C.Structure):
                 ("n_enforce", C.c_longlong), ("d_av", C.c_double), ("d_visc", C.c_double),
                 ("w_delta", C.c_double), ("w_ghost", C.c_double), ("w_enforce", C.c_double),
                 ("w_clamp", C.c_double), ("e_th", C.c_double)]
+
+
+DIAG_DTYPE = np.dtype(Diag)
 
 
 class Info(C.Structure):
@@ -151,7 +155,7 @@ def lib():
             "wcsph_export_density": [_V, _F, _F, C.c_int],
             "wcsph_set_fluid": [_V, C.c_double, _D, _D, _D, _D, _D, C.c_int],
             "wcsph_save_state": [_V, _V, C.c_size_t, C.POINTER(C.c_size_t)],
-            "wcsph_load_state": [_V, _V, C.c_size_t],
+            "wcsph_load_state": [_V, C.c_char_p, C.c_size_t],
             "wcsph_export_cells": [_V, _U, _U, _D, _D, _U, _U, _U, C.c_size_t, C.c_size_t],
             "wcsph_export_rates": [_V, _F, _F, _F, _F, _F, _F, _F, _F, _F, C.c_int, C.c_int],
             "wcsph_export_neighbours": [_V, _U, _I, _LL, _D, _D, C.c_size_t],
@@ -294,6 +298,8 @@ class Solver:
     def read_probes(self, inst: int = 0, max_rows: int = 1 << 20):
         np_ = self.n_probes[inst]
         rows = C.c_int()
+        if max_rows > HIST_CAP:  # the device ring holds no more
+            max_rows = HIST_CAP
         t = np.empty(max_rows)
         dt = np.empty(max_rows)
         p = np.empty((max_rows, max(np_, 1)), dtype=np.float32)
@@ -308,13 +314,13 @@ class Solver:
         """Diagnostic records since the last read. A flagged state raises
         WcsphUnstable (with the records as .result), or with check=False
         returns them with out["unstable"] = True."""
-        buf = (Diag * max_rows)()
+        buf = np.empty(max_rows, DIAG_DTYPE)
         n = C.c_int()
-        st = lib().wcsph_read_diagnostics(self.handle, inst, buf, max_rows, C.byref(n))
-        rows = [buf[k] for k in range(n.value)]
-        out = {k: np.array([getattr(r, k) for r in rows]) for k, _ in Diag._fields_ if k != "mom"}
-        out["momx"] = np.array([r.mom[0] for r in rows])
-        out["momy"] = np.array([r.mom[1] for r in rows])
+        st = lib().wcsph_read_diagnostics(self.handle, inst, buf.ctypes.data_as(C.POINTER(Diag)), max_rows, C.byref(n))
+        rows = buf[:n.value]
+        out = {k: rows[k].copy() if n.value else np.array([]) for k, _ in Diag._fields_ if k != "mom"}
+        out["momx"] = rows["mom"][:, 0].copy()
+        out["momy"] = rows["mom"][:, 1].copy()
         if st == E_UNSTABLE and not check:
             out["unstable"] = True
             return out
@@ -367,8 +373,10 @@ class Solver:
         return buf.raw
 
     def load_state(self, blob: bytes):
-        buf = C.create_string_buffer(blob, len(blob))
-        self._check(lib().wcsph_load_state(self.handle, buf, len(blob)))
+        if not isinstance(blob, bytes):  # (as the buffer constructor has it)
+            raise TypeError("bytes expected")
+        # the blob itself is read, not a copy of it
+        self._check(lib().wcsph_load_state(self.handle, blob, len(blob)))
 
     # -- test hooks -----------------------------------------------------------
     def export_cells(self):

@@ -510,10 +510,7 @@ bool pin_invalid(wcsph_ctx* c) { return clocks_invalid(c, pin_clocks(c)[0], pin_
 
 // Refill the buckets of the next sort from the state in X (after the state,
 // the clocks or the disk law changed from the host).
-void arm_counts(wcsph_ctx* c) {
-  HC(hipMemcpyAsync(c->d.count, c->d_wallcount, (size_t)c->n_cells * 4, hipMemcpyDeviceToDevice, c->st));
-  HC(hipMemcpyAsync(c->d.tot_a, c->d_wall_tot, c->n_tiles * 4, hipMemcpyDeviceToDevice, c->st));
-}
+void arm_counts(wcsph_ctx* c) { wc_enqueue_arm(c->d, c->st); }
 void rearm(wcsph_ctx* c) {
   arm_counts(c);
   wc_enqueue_init(c->d, c->b, c->batch, c->st);
@@ -1510,29 +1507,60 @@ wcsph_status wcsph_load_state(wcsph_ctx* ctx, const void* buf, size_t n) {
                     (size_t)ctx->n_ghost * 4 + audit_bytes(ctx) + energy_bytes(ctx);
   require(n >= sz, "state blob truncated");
   sync(ctx);
-  const char* o = static_cast<const char*>(buf) + sizeof h;
-  auto get = [&](void* dev, size_t bytes) {
-    HC(hipMemcpy(dev, o, bytes, hipMemcpyHostToDevice));
-    o += bytes;
-  };
-  get(ctx->d_clk, ctx->n_inst * sizeof(Clock));
-  get(ctx->b.X.cell, N * 4);
-  get(ctx->b.X.id, N * 4);
-  get(ctx->b.X.pv, N * 16);
-  get(ctx->b.X.aux, N * 16);
-  if (ctx->batch) get(ctx->b.X.inst, N * 2);
-  else o += N * 2;
-  get(ctx->d.gslot, (size_t)ctx->n_ghost * 4);
-  if (ctx->d.audit_part) get(ctx->d.audit_part, audit_bytes(ctx));
-  if (ctx->b.X.e) get(ctx->b.X.e, energy_bytes(ctx));
-  rearm(ctx);
-  sync(ctx);
+  const char* const body = static_cast<const char*>(buf) + sizeof h;
+  // the arrays of the blob, one after the other
+  const size_t len[9] = {ctx->n_inst * sizeof(Clock), N * 4, N * 4, N * 16, N * 16, N * 2,
+                         (size_t)ctx->n_ghost * 4, audit_bytes(ctx), energy_bytes(ctx)};
+  const bool use[9] = {true, true, true, true, true, ctx->batch, true, len[7] != 0, len[8] != 0};
+  size_t packed = 0;
+  for (int k = 0; k < 9; ++k)
+    if (use[k]) packed += (len[k] + 15) & ~size_t(15);
+  if (packed + WC_PIN_HEAD <= WC_PIN_BYTES) {
+    // a short state: through the page-locked block in one copy, then one launch
+    char* const pin = ctx->hpin + WC_PIN_HEAD;
+    const char *at[9] = {}, *o = body;
+    size_t off = 0;
+    for (int k = 0; k < 9; ++k) {
+      if (use[k]) {
+        std::memcpy(pin + off, o, len[k]);
+        at[k] = ctx->d_read + off;
+        off += (len[k] + 15) & ~size_t(15);
+      }
+      o += len[k];
+    }
+    HC(hipMemcpyAsync(ctx->d_read, pin, packed, hipMemcpyHostToDevice, ctx->st));
+    StatePack p;
+    p.clk = reinterpret_cast<const Clock*>(at[0]);
+    p.cell = reinterpret_cast<const uint32_t*>(at[1]);
+    p.id = reinterpret_cast<const uint32_t*>(at[2]);
+    p.pv = reinterpret_cast<const float4*>(at[3]);
+    p.aux = reinterpret_cast<const float4*>(at[4]);
+    p.inst = reinterpret_cast<const uint16_t*>(at[5]);
+    p.gslot = reinterpret_cast<const uint32_t*>(at[6]);
+    p.audit = reinterpret_cast<const double*>(at[7]);
+    p.n_audit = (int)(len[7] / sizeof(double));
+    p.e = reinterpret_cast<const float*>(at[8]);
+    wc_enqueue_load_state(ctx->d, ctx->b, p, ctx->st);
+    wc_enqueue_init(ctx->d, ctx->b, ctx->batch, ctx->st);
+    HC(hipGetLastError());
+    ctx->lf_set = 0;
+  } else {
+    void* const dev[9] = {ctx->d_clk, ctx->b.X.cell, ctx->b.X.id, ctx->b.X.pv, ctx->b.X.aux, ctx->b.X.inst,
+                          ctx->d.gslot, ctx->d.audit_part, ctx->b.X.e};
+    const char* o = body;
+    for (int k = 0; k < 9; ++k) {
+      if (use[k]) HC(hipMemcpyAsync(dev[k], o, len[k], hipMemcpyHostToDevice, ctx->st));
+      o += len[k];
+    }
+    rearm(ctx);
+  }
+  sync(ctx);  // (the blob is no longer read)
   ctx->steps = h.steps;
-  std::vector<Clock> clk(ctx->n_inst);
-  HC(hipMemcpy(clk.data(), ctx->d_clk, clk.size() * sizeof(Clock), hipMemcpyDeviceToHost));
   for (int i = 0; i < ctx->n_inst; ++i) {
+    Clock k;
+    std::memcpy(&k, body + i * sizeof(Clock), sizeof k);
     ctx->hist_read[i] = ctx->steps;
-    ctx->diag_rows[i] = clk[i].diag_row;
+    ctx->diag_rows[i] = k.diag_row;
     ctx->diag_read[i] = ctx->diag_rows[i];
   }
   API_END(ctx)

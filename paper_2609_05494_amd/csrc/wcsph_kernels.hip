@@ -2156,6 +2156,33 @@ __global__ __launch_bounds__(64) void k_diag_final(Dev d) {
   if (tot[7] > 0.0 || !(tot[3] == tot[3])) C.bad |= 1u;
 }
 
+// The sort counters of an unfilled bucket set a: the static wall-ghost entries.
+__device__ __forceinline__ void arm_a(const Dev& d, int u) {
+  if (u < d.n_cells) d.count[u] = d.wallcount[u];
+  if (u < (d.n_cells + WC_SORT_TILE - 1) / WC_SORT_TILE) d.tot_a[u] = d.wall_tot[u];
+}
+__global__ __launch_bounds__(WC_BLOCK) void k_arm(Dev d) { arm_a(d, blockIdx.x * WC_BLOCK + threadIdx.x); }
+
+// A short checkpoint, copied to the device in one piece, into the state's
+// arrays, and the sort counters armed with it (one launch in place of a
+// blocking copy per array).
+__global__ __launch_bounds__(WC_BLOCK) void k_load_state(Dev d, Buf X, StatePack b) {
+  const int u = blockIdx.x * WC_BLOCK + threadIdx.x;
+  if (u < d.n_slots) {
+    X.cell[u] = b.cell[u];
+    X.id[u] = b.id[u];
+    X.pv[u] = b.pv[u];
+    X.aux[u] = b.aux[u];
+    if (b.inst) X.inst[u] = b.inst[u];
+    if (b.e) X.e[u] = b.e[u];
+  }
+  if (u < d.n_ghost) d.gslot[u] = b.gslot[u];
+  if (u < b.n_audit) d.audit_part[u] = b.audit[u];
+  if (u < d.n_inst * (int)(sizeof(Clock) / 8))
+    reinterpret_cast<unsigned long long*>(d.clk)[u] = reinterpret_cast<const unsigned long long*>(b.clk)[u];
+  arm_a(d, u);
+}
+
 // What the host reads of a context, packed by one launch so that a read costs
 // one wait and not a blocking copy per field (about 15 us each). `clk`: the
 // clocks of instance i and of instance 0 (the validity flags), written by the
@@ -2390,6 +2417,13 @@ void wc_enqueue_export_pair(const Dev& d, const Bufs& b, hipStream_t st) {
 void wc_enqueue_pair_a(const Dev& d, const Bufs& b, bool batch, hipStream_t st) {
   if (batch) launch_pair<EV_A, true>(d, b.Y, b.Y, b.Z, st);
   else launch_pair<EV_A, false>(d, b.Y, b.Y, b.Z, st);
+}
+
+void wc_enqueue_arm(const Dev& d, hipStream_t st) { k_arm<<<NB(d.n_cells), WC_BLOCK, 0, st>>>(d); }
+void wc_enqueue_load_state(const Dev& d, const Bufs& b, const StatePack& p, hipStream_t st) {
+  const int n = std::max(std::max(std::max(d.n_slots, d.n_cells), std::max(d.n_ghost, p.n_audit)),
+                         d.n_inst * (int)(sizeof(Clock) / 8));
+  k_load_state<<<NB(n), WC_BLOCK, 0, st>>>(d, b.X, p);
 }
 
 static_assert(2 * (sizeof(Clock) / 8) <= WC_BLOCK && sizeof(Clock) % 8 == 0, "clocks of a read");

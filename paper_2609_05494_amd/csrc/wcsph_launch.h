@@ -29,6 +29,20 @@ void wc_enqueue_export_ghosts(const Dev& d, const Bufs& b, int n_gblk, hipStream
 void wc_enqueue_export_pair(const Dev& d, const Bufs& b, hipStream_t st);
 void wc_enqueue_pair_a(const Dev& d, const Bufs& b, bool batch, hipStream_t st);
 void wc_enqueue_neigh(const Dev& d, const Bufs& b, hipStream_t st);
+// Bucket set a's counters armed with the static wall ghosts (before a fill).
+void wc_enqueue_arm(const Dev& d, hipStream_t st);
+// A checkpoint's arrays in device memory (NULL: not part of it).
+struct StatePack {
+  const Clock* clk;
+  const uint32_t *cell, *id;
+  const float4 *pv, *aux;
+  const uint16_t* inst;
+  const uint32_t* gslot;
+  const double* audit;
+  const float* e;
+  int n_audit;
+};
+void wc_enqueue_load_state(const Dev& d, const Bufs& b, const StatePack& p, hipStream_t st);
 // Reads of the host, packed on the device; clk: the clocks of instance i and
 // of instance 0 (host memory the GPU can write).
 // Fluid state of instance i in id order, FP64: x, y, vx, vy, rho (device).
