@@ -126,7 +126,7 @@ struct wcsph_ctx {
   std::vector<InstParams> hp;
   std::vector<HostInst> geo;
   long long n_fluid = 0;
-  int n_slots = 0, n_cells = 0, n_ghost = 0, n_gblk = 0;
+  int n_slots = 0, n_cells = 0, n_ghost = 0, n_gblk = 0, n_sblk = 0;
   int diag_every = 0;
   Dev d{};
   Bufs b{};
@@ -138,7 +138,9 @@ struct wcsph_ctx {
   size_t n_tiles = 0;
   uint32_t* d_gslot_save = nullptr;
   std::vector<uint32_t> h_wallcount, h_wrank;
-  std::vector<int4> h_gblk;
+  std::vector<int4> h_gblk, h_sblk;
+  std::vector<uint32_t> h_witem, h_wcell, h_wplace;
+  std::vector<float2> h_wpos;
   hipGraph_t graph = nullptr;       // one step
   hipGraphExec_t gexec = nullptr;
   hipGraph_t graph_k = nullptr;     // steps_k steps and a diagnostic record
@@ -619,7 +621,7 @@ bool two_way(const wcsph_ctx* c) {
 // One step of the context's scheme; a leapfrog step reads bucket set `set`.
 void enqueue_one_step(wcsph_ctx* c, int set) {
   if (c->scheme == 1) wc_enqueue_step_lf(c->d, c->b, c->n_gblk, c->batch, set, c->st);
-  else wc_enqueue_step(c->d, c->b, c->n_gblk, c->batch, two_way(c), c->audit, c->st);
+  else wc_enqueue_step(c->d, c->b, c->d.merged ? c->n_sblk : c->n_gblk, c->batch, two_way(c), c->audit, c->st);
 }
 void capture_pair(wcsph_ctx* c, int set, hipGraph_t* g1, hipGraphExec_t* e1, hipGraph_t* gk, hipGraphExec_t* ek) {
   hipGraph_t g = nullptr;
@@ -642,6 +644,64 @@ void capture(wcsph_ctx* c) {
   capture_pair(c, 0, &c->graph, &c->gexec, &c->graph_k, &c->gexec_k);
   // scheme 1 alternates the bucket sets from step to step
   if (c->scheme == 1) capture_pair(c, 1, &c->graph1, &c->gexec1, &c->graph_k1, &c->gexec_k1);
+}
+
+// Ghosts in the sort's launch instead of a launch of their own: a single
+// instance up to WC_MERGE_SLOTS slots. There the two launches are chains of
+// dependent loads on a nearly idle chip and run side by side; us a step, own
+// launch -> merged: 45.6 -> 42.6 at 28,352 particles, 53.4 -> 50.0 at 71,752,
+// 69.7 -> 67.7 at 134,752. Above it the tiles fill the chip, and the ghost
+// blocks' LDS costs them waves: 79.3 -> 79.7 at 179,552, 186 -> 199 at 719,552;
+// so it does in a batch (16 instances, 530,000 particles: 196 -> 238). The
+// leapfrog's ghosts need the summed density of its own pass.
+bool merge_ghosts(const wcsph_ctx* c) {
+  return !c->batch && c->scheme == 0 && c->n_slots <= WC_MERGE_SLOTS;
+}
+// Block table of these ghosts: runs of at most 16 items (wall ghosts in cell
+// order, ring ghosts, probes) whose cells, with one cell around them, fit
+// WC_GHOST_REGION cells. The ring moves: a run of ring ghosts is as long as
+// keeps its extent within three cells wherever it lies.
+void ghost_blocks(wcsph_ctx* c) {
+  const InstParams& q = c->hp[0];
+  std::vector<uint32_t> key(q.nw);
+  std::vector<float2> pos(q.nw);
+  std::vector<int> order(q.nw);
+  for (int k = 0; k < q.nw; ++k) {
+    encode(q, c->geo[0].wx[k], c->geo[0].wy[k], key[k], pos[k].x, pos[k].y);
+    order[k] = k;
+  }
+  std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return key[a] < key[b]; });
+  for (int g : order) {
+    c->h_witem.push_back((uint32_t)g);
+    c->h_wcell.push_back(key[g]);
+    c->h_wpos.push_back(pos[g]);
+    c->h_wplace.push_back(c->h_wrank[q.gmap0 + g]);
+  }
+  auto runs = [&](int n, int kind, auto&& cell) {
+    for (int a = 0; a < n;) {
+      int x0 = 1 << 30, x1 = -1, y0 = 1 << 30, y1 = -1, e = a;
+      for (; e < n && e - a < 16; ++e) {
+        const int l = (int)cell(e) - q.cell_off, x = l % q.ncx, y = l / q.ncx;
+        const int u0 = std::min(x0, x), u1 = std::max(x1, x), v0 = std::min(y0, y), v1 = std::max(y1, y);
+        if (e > a && (u1 - u0 + 3) * (v1 - v0 + 3) > WC_GHOST_REGION) break;
+        x0 = u0;
+        x1 = u1;
+        y0 = v0;
+        y1 = v1;
+      }
+      c->h_sblk.push_back(make_int4(0, a, e - a, kind));
+      a = e;
+    }
+  };
+  // ring ghosts first: theirs are the longest blocks
+  if (q.nd > 0) {
+    const double chord = 2.0 * M_PI * q.R / q.nd;  // (no shorter than the distance of neighbours)
+    const int len = (int)std::min(16.0, std::max(1.0, 1.0 + std::floor(3.0 * q.dcd / std::max(chord, 1e-300))));
+    for (int a = 0; a < q.nd; a += len) c->h_sblk.push_back(make_int4(0, q.nw + a, std::min(len, q.nd - a), 1));
+  }
+  runs(q.nw, 0, [&](int k) { return c->h_wcell[k]; });
+  runs(q.n_probes, 2, [&](int k) { return q.probe_cell[k]; });
+  c->n_sblk = (int)c->h_sblk.size();
 }
 
 void build(wcsph_ctx* c, const wcsph_params* params, int n_inst) {
@@ -694,6 +754,8 @@ void build(wcsph_ctx* c, const wcsph_params* params, int n_inst) {
     for (int k0 = 0; k0 < q.n_probes; k0 += gq) c->h_gblk.push_back(make_int4(i, k0, std::min(gq, q.n_probes - k0), 2));
   }
   c->n_gblk = (int)c->h_gblk.size();
+  c->d.merged = merge_ghosts(c) ? 1 : 0;
+  if (c->d.merged) ghost_blocks(c);
   for (uint32_t w : c->h_wallcount)
     require(w <= WC_BUCKET / 2, "too many wall ghosts in one cell (ghost_layers too large for h/dx)");
   // device memory
@@ -721,7 +783,8 @@ void build(wcsph_ctx* c, const wcsph_params* params, int n_inst) {
   d.n_slots = c->n_slots;
   d.n_cells = c->n_cells;
   d.n_ghost = c->n_ghost;
-  d.count = dalloc_n<uint32_t>(c, c->n_cells);
+  d.count_a = dalloc_n<uint32_t>(c, c->n_cells);
+  d.count_b = dalloc_n<uint32_t>(c, c->n_cells);
   d.start = dalloc_n<uint32_t>(c, c->n_cells + 1);
   c->d_wallcount = dalloc_n<uint32_t>(c, c->n_cells);
   d.wallcount = c->d_wallcount;
@@ -752,6 +815,34 @@ void build(wcsph_ctx* c, const wcsph_params* params, int n_inst) {
   c->d_gslot_save = dalloc_n<uint32_t>(c, c->n_ghost);
   uint32_t* wrank = dalloc_n<uint32_t>(c, c->n_ghost);
   d.wrank = wrank;
+  if (d.merged) {
+    int4* sblk = dalloc_n<int4>(c, c->n_sblk);
+    uint32_t *witem = dalloc_n<uint32_t>(c, c->n_ghost), *wcell = dalloc_n<uint32_t>(c, c->n_ghost);
+    uint32_t* wplace = dalloc_n<uint32_t>(c, c->n_ghost);
+    d.wplace = wplace;
+    float2* wpos = dalloc_n<float2>(c, c->n_ghost);
+    d.sblk = sblk;
+    d.witem = witem;
+    d.wcell = wcell;
+    d.wpos = wpos;
+    HC(hipMemcpyAsync(sblk, c->h_sblk.data(), c->h_sblk.size() * sizeof(int4), hipMemcpyHostToDevice, c->st));
+    HC(hipMemcpyAsync(witem, c->h_witem.data(), c->h_witem.size() * 4, hipMemcpyHostToDevice, c->st));
+    HC(hipMemcpyAsync(wcell, c->h_wcell.data(), c->h_wcell.size() * 4, hipMemcpyHostToDevice, c->st));
+    HC(hipMemcpyAsync(wplace, c->h_wplace.data(), c->h_wplace.size() * 4, hipMemcpyHostToDevice, c->st));
+    HC(hipMemcpyAsync(wpos, c->h_wpos.data(), c->h_wpos.size() * 8, hipMemcpyHostToDevice, c->st));
+    d.rcell_a = dalloc_n<uint32_t>(c, WC_MAX_RING);
+    d.rcell_b = dalloc_n<uint32_t>(c, WC_MAX_RING);
+    d.rslot_a = dalloc_n<uint32_t>(c, WC_MAX_RING);
+    d.rslot_b = dalloc_n<uint32_t>(c, WC_MAX_RING);
+    d.rpos_a = dalloc_n<float2>(c, WC_MAX_RING);
+    d.rpos_b = dalloc_n<float2>(c, WC_MAX_RING);
+    d.deval_a = dalloc_n<DiskEval>(c, 1);
+    d.deval_b = dalloc_n<DiskEval>(c, 1);
+    d.n_sblk = c->n_sblk;
+    d.gvmax = dalloc_n<float>(c, c->n_sblk + 1);
+    d.gvstep = (uint32_t*)(d.gvmax + c->n_sblk);
+    HC(hipMemsetAsync(d.gvmax, 0, (size_t)(c->n_sblk + 1) * 4, c->st));
+  }
   int4* gblk = dalloc_n<int4>(c, c->n_gblk);
   d.gblk = gblk;
   d.hist_t = dalloc_n<double>(c, (size_t)n_inst * WC_HIST_CAP);
@@ -809,6 +900,7 @@ void build(wcsph_ctx* c, const wcsph_params* params, int n_inst) {
     HC(hipMemcpyAsync(c->d_wall_tot, wt.data(), n_tiles * 4, hipMemcpyHostToDevice, c->st));
     // set b is re-armed by the first sort; set a is armed with every fill of bucket a
     HC(hipMemcpyAsync(d.tot_b, wt.data(), n_tiles * 4, hipMemcpyHostToDevice, c->st));
+    HC(hipMemcpyAsync(d.count_b, c->h_wallcount.data(), (size_t)c->n_cells * 4, hipMemcpyHostToDevice, c->st));
     sync(c);  // the host vector goes out of scope
   }
   sync(c);
@@ -1046,14 +1138,14 @@ void replay_taped_step(wcsph_ctx* c, int k) {
   dA.gslot = A.tA[k].gslot;
   dA.tape_pos = A.pA[k];
   dA.tape_vel = A.vA[k];
-  wc_enqueue_eval(dA, bt, c->n_gblk, EV_A, c->st);
+  wc_enqueue_eval(dA, bt, dA.merged ? c->n_sblk : c->n_gblk, EV_A, c->st);
   HC(hipGetLastError());
   Dev dB = c->d;
   dB.start = A.tB[k].start;
   dB.gslot = A.tB[k].gslot;
   dB.tape_pos = A.pB[k];
   dB.tape_vel = A.vB[k];
-  wc_enqueue_eval(dB, bt, c->n_gblk, EV_B, c->st);
+  wc_enqueue_eval(dB, bt, dB.merged ? c->n_sblk : c->n_gblk, EV_B, c->st);
   HC(hipGetLastError());
 }
 void replay_taped(wcsph_ctx* c, int n) {

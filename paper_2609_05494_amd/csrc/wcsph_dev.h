@@ -25,6 +25,8 @@
 #define WC_DIAG_BLOCKS 256     // diagnostic partial sums per instance
 #define WC_BUCKET 64           // capacity of one cell bucket (particles per cell)
 #define WC_SORT_TILE 64        // cells per block of the sort kernel
+#define WC_MERGE_SLOTS 131072  // ghosts go into the sort's launch up to so many slots (measured: merge_ghosts)
+#define WC_GHOST_REGION 64     // cells that a ghost block of the sort's launch stages at most
 #define WC_NB_CAP 64           // neighbour ids per particle in the neighbour-list export
 #define WC_KIN_ROWS 1024       // rows of a tabulated disk motion per instance
 #define WC_TEST_UNITS 256      // test coordinates of the pair pass: units per cell edge
@@ -126,20 +128,29 @@ struct Buf {
   float* e;         // scheme 1: specific internal energy (NULL otherwise)
 };
 
+// The disk at the time of an evaluation, left by the pass before it, and the
+// probe-history row of the step.
+struct DiskEval {
+  double xd, vd, ad;
+  long long row;
+};
+
 // Everything a kernel may touch (passed by value).
 struct Dev {
   const InstParams* prm;
   Clock* clk;
   int n_inst, n_slots, n_cells, n_ghost;
-  uint32_t* count;            // per cell: bucket fill for the next sort
+  uint32_t* count_a;          // per cell: fill of bucket set a / b
+  uint32_t* count_b;
   uint32_t* start;            // per cell + 1: exclusive scan of count
-  const uint32_t* wallcount;  // per cell: static wall ghosts (pre-fill of count)
+  const uint32_t* wallcount;  // per cell: static wall ghosts (pre-fill of the counts)
   // cell buckets [n_cells][WC_BUCKET] of slots, filled for the next sort:
   // bucket_a by eval B (and at load) for eval A, bucket_b by eval A for eval B
   uint32_t* bucket_a;
   uint32_t* bucket_b;
   // entries per sort tile of the bucket set a / b, filled with the buckets;
-  // the static wall-ghost entries they are re-armed with
+  // the static wall-ghost entries they are re-armed with. (A sort re-arms the
+  // counts and totals of the set it does not read.)
   uint32_t* tot_a;
   uint32_t* tot_b;
   const uint32_t* wall_tot;
@@ -151,6 +162,22 @@ struct Dev {
   float2* gpos;               // per ghost: offset inside that cell
   const uint32_t* wrank;      // per ghost: static bucket rank of a wall ghost
   const int4* gblk;           // ghost-kernel block table: (inst, first item, count, kind)
+  // ghosts in the sort's launch (merged != 0): block table (as gblk; wall items
+  // in cell order); per wall item its ghost index, cell and offset in the cell;
+  // the ring placed for the next predictor (a) and corrector (b) sort, with
+  // the disk at that time; max |v| of the ghosts for the step's dt
+  int merged;
+  const int4* sblk;
+  const uint32_t* witem;
+  const uint32_t* wcell;
+  const uint32_t* wplace;       // (its place in the cell's bucket)
+  const float2* wpos;
+  uint32_t *rcell_a, *rcell_b, *rslot_a, *rslot_b;  // [WC_MAX_RING]
+  float2 *rpos_a, *rpos_b;
+  DiskEval *deval_a, *deval_b;
+  float* gvmax;               // [n_sblk] per ghost block of the predictor
+  int n_sblk;
+  uint32_t* gvstep;           // their maximum (float bits)
   double* hist_t;             // [n_inst][WC_HIST_CAP]
   double* hist_dt;
   float* hist_p;              // [n_inst][WC_HIST_CAP][WC_MAX_PROBES]

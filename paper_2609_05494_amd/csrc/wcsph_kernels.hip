@@ -7,7 +7,9 @@
 //              order, per-particle EOS P = p/rho^2 and c); its first block
 //              advances the clock and the prescribed disk kinematics
 //   k_ghost    Adami-Shepard ghost state on walls and ring, probes (eval A),
-//              v_max of the ghosts (eval A), work of the ring (eval B)
+//              v_max of the ghosts (eval A), work of the ring (eval B); for
+//              a single instance that does not fill the chip by blocks of
+//              k_sort's launch instead (ghost_block)
 //   k_pair     pair sums over the 3x3 cells (continuity + delta, pressure +
 //              AV + laminar, XSPH) fused with the predictor / corrector,
 //              density band, enforcement, new cell key; every slot goes
@@ -470,6 +472,16 @@ __device__ __forceinline__ T scalar_copy(const T* p) {
   __builtin_memcpy(&t, w, sizeof t);
   return t;
 }
+// This lane's share of the ghosts' max |v| of the step, where they are in the
+// sort's launch (a wave reads all).
+__device__ __forceinline__ float ghost_vmax(const Dev& d) {
+  float v = 0.0f;
+  for (int k0 = (int)(threadIdx.x & 63u); k0 < d.n_sblk; k0 += 4 * 64) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v = fmaxf(v, d.gvmax[min(k0 + 64 * k, d.n_sblk - 1)]);
+  }
+  return v;
+}
 __device__ __forceinline__ PairC pair_c(const InstParams* prm) {
   ConstParams& P = *(ConstParams*)prm;
   PairC c;
@@ -874,33 +886,115 @@ __device__ __forceinline__ double group_sum(double v) {
 struct Shep {
   float W, p, rx, ry, vx, vy;
 };
-template <int G, bool CUB>
-__device__ __forceinline__ Shep shepard(const Dev& d, const InstParams& P, const Buf& sb, uint32_t K, float ox,
-                                        float oy, int lane) {
-  Shep S = {0, 0, 0, 0, 0, 0};
-  for_candidates<G>(d, P, sb, K, lane, [&](const float4& pj, const float4& aj, uint32_t code) __attribute__((always_inline)) {
-    float rx, ry;  // r_g - r_j
-    rel_pos(P, ox, oy, pj, code, rx, ry);
-    const float r2 = rx * rx + ry * ry;
-    if (!(aj.w > 0.0f) || !(r2 < P.four_h2)) return;  // fluid in support only
-    float W, F;
-    if constexpr (CUB) cubic_spline(P, r2, W, F);
-    else wendland(P, r2, W, F);
-    const float pj_ = aj.y * aj.x * aj.x;  // p = P rho^2
-    S.W += W;
-    S.p += pj_ * W;
-    S.rx += aj.x * rx * W;
-    S.ry += aj.x * ry * W;
-    S.vx += pj.z * W;
-    S.vy += pj.w * W;
-  });
+// One candidate (state pj, aj, cell-shift code) added to the sums of a point
+// at offset (ox, oy) of its cell: fluid in support only.
+template <bool CUB>
+__device__ __forceinline__ void shepard_add(const InstParams& P, float ox, float oy, const float4& pj, const float4& aj,
+                                            uint32_t code, Shep& S) {
+  float rx, ry;  // r_g - r_j
+  rel_pos(P, ox, oy, pj, code, rx, ry);
+  const float r2 = rx * rx + ry * ry;
+  if (!(aj.w > 0.0f) || !(r2 < P.four_h2)) return;
+  float W, F;
+  if constexpr (CUB) cubic_spline(P, r2, W, F);
+  else wendland(P, r2, W, F);
+  const float pj_ = aj.y * aj.x * aj.x;  // p = P rho^2
+  S.W += W;
+  S.p += pj_ * W;
+  S.rx += aj.x * rx * W;
+  S.ry += aj.x * ry * W;
+  S.vx += pj.z * W;
+  S.vy += pj.w * W;
+}
+template <int G>
+__device__ __forceinline__ void shepard_sum(Shep& S) {
   S.W = group_sum<G>(S.W);
   S.p = group_sum<G>(S.p);
   S.rx = group_sum<G>(S.rx);
   S.ry = group_sum<G>(S.ry);
   S.vx = group_sum<G>(S.vx);
   S.vy = group_sum<G>(S.vy);
+}
+template <int G, bool CUB>
+__device__ __forceinline__ Shep shepard(const Dev& d, const InstParams& P, const Buf& sb, uint32_t K, float ox,
+                                        float oy, int lane) {
+  Shep S = {0, 0, 0, 0, 0, 0};
+  for_candidates<G>(d, P, sb, K, lane, [&](const float4& pj, const float4& aj, uint32_t code) __attribute__((always_inline)) {
+    shepard_add<CUB>(P, ox, oy, pj, aj, code, S);
+  });
+  shepard_sum<G>(S);
   return S;
+}
+
+// Adami ghost state from the Shepard sums; vw, aw: the disk's velocity and
+// acceleration (ring ghosts), axis: a wall ghost below the axis of the
+// axisymmetric form.
+struct GhostState {
+  float rho, P, c, vx, vy;
+};
+__device__ __forceinline__ GhostState ghost_state(const InstParams& P, const Shep& S, bool disk, bool axis, float vw,
+                                                  float aw) {
+  GhostState q;
+  const float vwx = disk ? vw : 0.0f;
+  const float awx = disk ? aw : 0.0f;
+  float p;
+  if (S.W > 0.0f) {
+    const float inv = 1.0f / S.W;
+    // body-force term (g - a_w) . sum rho_j (r_g - r_j) W
+    p = (S.p + (0.0f - awx) * S.rx + P.gy * S.ry) * inv;
+    q.vx = axis ? S.vx * inv : 2.0f * vwx - S.vx * inv;  // axis: the axial velocity is kept
+    q.vy = -S.vy * inv;
+  } else {
+    p = 0.0f;
+    q.vx = vwx;
+    q.vy = 0.0f;
+  }
+  p = fmaxf(p, P.p_cav);
+  if (P.eos_type == 1) {
+    // Mie-Grueneisen inverse: tension line, or the root in [0, 1/b) of
+    // s (1 - b mu)^2 = mu (1 + k1 mu), s = p / K; capped at mu_max
+    const float sp = p / P.mg_K;
+    float mu = sp;
+    if (P.ghost_rho_mode != 0 && sp > 0.0f)
+      mu = fminf(2.0f * sp / ((1.0f + 2.0f * P.mg_b * sp) + sqrtf(1.0f + 4.0f * sp * (P.mg_b + P.mg_k1))),
+                 P.mg_mu_max);
+    q.rho = P.rho0 * (1.0f + mu);
+    float pu;
+    mg_eos(P, mu, pu, q.c);
+  } else {
+    if (P.ghost_rho_mode == 0) q.rho = P.rho0 * (1.0f + p * P.inv_rho0c02);
+    else q.rho = P.rho0 * expf(P.inv_gamma * log1pf(p / P.B));
+    const float xg = (q.rho - P.rho0) / P.rho0, yg = 1.0f + xg;
+    q.c = P.gamma == 7.0f ? P.c0 * (yg * yg * yg) : P.c0 * expf(P.c_exp * log1pf(xg));
+  }
+  q.P = p / (q.rho * q.rho);
+  return q;
+}
+
+// One candidate's share of the x force of a ring ghost (state q, mass m,
+// radius yg) on its fluid neighbours.
+template <bool CUB>
+__device__ __forceinline__ void ring_force_add(const InstParams& P, float ox, float oy, float yg, float m,
+                                               const GhostState& q, const float4& pj, const float4& aj, uint32_t code,
+                                               float& fx) {
+  if (!(aj.w > 0.0f)) return;
+  float rx, ry;
+  rel_pos(P, ox, oy, pj, code, rx, ry);
+  rx = -rx;  // r_i - r_g
+  ry = -ry;
+  const float r2 = rx * rx + ry * ry;
+  if (!(r2 < P.four_h2)) return;
+  float W, F;
+  if constexpr (CUB) cubic_spline(P, r2, W, F);
+  else wendland(P, r2, W, F);
+  const float vr = (pj.z - q.vx) * rx + (pj.w - q.vy) * ry;
+  const float rsum = aj.x + q.rho, den = r2 + P.eta2h2;
+  const float inv = fast_rcp(den * rsum);
+  const float piav =
+      vr < 0.0f ? -P.alpha * (aj.z + q.c) * P.h * vr * inv + P.beta2h2 * vr * vr * inv * (rsum * inv) : 0.0f;
+  // (axisymmetric: the fluid particle's ring mass 2 pi m r in place of m)
+  const float mi = P.axisym ? aj.w * (6.283185307f * fmaxf(yg + ry, P.r_min)) : aj.w;
+  fx -= mi * m * (aj.y + q.P + piav) * F * rx;
 }
 
 }  // namespace
@@ -937,9 +1031,11 @@ __device__ void clock_commit(const Dev& d, int i) {
       }
     }
   } else if (MODE == EV_B) {
-    const double dt = step_dt(d, P, C);
+    uint32_t vb = C.vmax_bits;
+    if (d.merged) vb = max(vb, *d.gvstep);
+    const double dt = step_dt_bits(d, P, C, vb);
     C.dt = dt;
-    C.vmax_used = (double)__uint_as_float(C.vmax_bits);
+    C.vmax_used = (double)__uint_as_float(vb);
     C.vmax_bits = 0u;
     const long long row = (long long)i * WC_HIST_CAP + (C.step % WC_HIST_CAP);
     d.hist_t[row] = C.t;
@@ -975,9 +1071,10 @@ __device__ __forceinline__ void flag_overflow(const Dev& d) {
 struct Fill {
   uint32_t* bucket;
   uint32_t* tot;
+  uint32_t* count;
 };
-__device__ __forceinline__ Fill fill_a(const Dev& d) { return Fill{d.bucket_a, d.tot_a}; }
-__device__ __forceinline__ Fill fill_b(const Dev& d) { return Fill{d.bucket_b, d.tot_b}; }
+__device__ __forceinline__ Fill fill_a(const Dev& d) { return Fill{d.bucket_a, d.tot_a, d.count_a}; }
+__device__ __forceinline__ Fill fill_b(const Dev& d) { return Fill{d.bucket_b, d.tot_b, d.count_b}; }
 #define WC_TILE_SHIFT 6   // log2 WC_SORT_TILE
 static_assert(WC_SORT_TILE == 1 << WC_TILE_SHIFT, "tile shift");
 
@@ -985,7 +1082,7 @@ static_assert(WC_SORT_TILE == 1 << WC_TILE_SHIFT, "tile shift");
 // cell's fill counter); an overfull cell is flagged and the slot dropped
 // (its tile still counts it, so every later slot keeps its place).
 __device__ __forceinline__ void bucket_put(const Dev& d, const Fill& f, uint32_t K, uint32_t s) {
-  const uint32_t b = atomicAdd(&d.count[K], 1u);
+  const uint32_t b = atomicAdd(&f.count[K], 1u);
   if (b < WC_BUCKET) f.bucket[(size_t)K * WC_BUCKET + b] = s;
   else flag_overflow(d);
   atomicAdd(&f.tot[K >> WC_TILE_SHIFT], 1u);
@@ -1029,7 +1126,7 @@ __device__ __forceinline__ void bucket_put_wave(const Dev& d, const Fill& f, boo
   if (A == 0ull) return;
   const Run rk = lane_run(A, act, K);
   uint32_t b0 = 0;
-  if (rk.head) b0 = atomicAdd(&d.count[K], rk.len);
+  if (rk.head) b0 = atomicAdd(&f.count[K], rk.len);
   const Run rt = lane_run(A, act, K >> WC_TILE_SHIFT);
   if (rt.head) atomicAdd(&f.tot[K >> WC_TILE_SHIFT], rt.len);
   b0 = __shfl(b0, rk.h);
@@ -1049,7 +1146,9 @@ __device__ __forceinline__ void bucket_put_wall(const Dev& d, const InstParams& 
 
 // Disk-ring ghost k of instance inst for a disk centre at x = xc:
 // r_k = (xc, y0) + R (cos 2 pi k / nd, sin 2 pi k / nd), encoded, and put
-// into its bucket for the next sort.
+// into its bucket for the next sort and, where the ghosts are in that sort's
+// launch, into the ring's own arrays (MRG: 1 of the set a, 2 of b).
+template <int MRG>
 __device__ __forceinline__ void place_ring(const Dev& d, const InstParams& P, int inst, int k, double xc,
                                            const Buf& out, int s, const Fill& bucket) {
 #pragma clang fp contract(off)
@@ -1062,6 +1161,11 @@ __device__ __forceinline__ void place_ring(const Dev& d, const InstParams& P, in
   const uint32_t key = (uint32_t)(P.cell_off + cy * P.ncx + cx);
   out.cell[s] = key;
   out.pv[s] = make_float4(ox, oy, 0.0f, 0.0f);
+  if constexpr (MRG != 0) {
+    (MRG == 2 ? d.rcell_b : d.rcell_a)[k] = key;
+    (MRG == 2 ? d.rpos_b : d.rpos_a)[k] = make_float2(ox, oy);
+    (MRG == 2 ? d.rslot_b : d.rslot_a)[k] = (uint32_t)s;
+  }
   bucket_put(d, bucket, key, (uint32_t)s);
 }
 
@@ -1159,7 +1263,8 @@ __device__ __forceinline__ Gathered sort_finish(const Dev& d, const InstParams& 
   }
   return v;
 }
-template <bool BATCH>
+// (GH: a ghost's state comes from its block of the launch)
+template <bool BATCH, bool GH>
 __device__ __forceinline__ void sort_store(const Dev& d, const InstParams& P1, const Buf& out, uint32_t e,
                                            uint32_t dst, uint32_t K, const Gathered& v) {
   if (v.inst < 0 || dst >= (uint32_t)d.n_slots) {
@@ -1174,21 +1279,385 @@ __device__ __forceinline__ void sort_store(const Dev& d, const InstParams& P1, c
   }
   out.cell[dst] = K;
   out.id[dst] = v.id;
-  out.pv[dst] = v.pv;
-  out.aux[dst] = v.aux;
+  if (!GH || v.ghost < 0) {
+    out.pv[dst] = v.pv;
+    out.aux[dst] = v.aux;
+  }
   d.tc[dst] = v.tc;
   if constexpr (BATCH) out.inst[dst] = (uint16_t)v.inst;
   if (out.e) out.e[dst] = v.e;
   d.perm[dst] = e;
 }
 
-template <int MODE, bool BATCH, bool MG>
-__global__ __launch_bounds__(SORT_BLOCK) void k_sort(Dev d, Buf pre, Buf out) {
+// The ghosts in the sort's launch: Adami ghost state (walls and ring), probes
+// (predictor), the ghosts' v_max (predictor) and the ring's force (corrector),
+// from the unsorted state, beside the tiles that sort it. The two were
+// launches of 6 to 9 us one after the other, each a chain of four or five
+// dependent loads with the chip nearly idle; neither needs the other's result
+// (28,352 particles: 7.2 + 6.0 and 7.2 + 7.7 us, in one launch 9.8 and 11.3).
+// A block takes up to 16 items whose 3x3 cells fit a region of
+// WC_GHOST_REGION cells (the host's table sees to it); it stages the region's
+// buckets in LDS in sorted order (as the tiles rank them), with the EOS, and
+// 16 lanes per item walk the item's cells there, rows bottom to top, in the
+// order and by the lanes that a walk of the sorted arrays would take. A region
+// of more than GHOST_EC particles is staged in windows. A ghost's sorted slot,
+// which the tiles find too, is the entries before its tile and before its cell
+// plus its rank in its bucket.
+#define GHOST_EC 320
+struct GhostLds {
+  float4 pv[GHOST_EC], aux[GHOST_EC];
+  uint32_t n[WC_GHOST_REGION];
+  int box[4][4];
+  float vmax[4];
+  uint32_t dst[16];  // sorted slot of each item's ghost (~0: dropped, no ghost)
+};
+// Entry l of a region into place x of the staged window, with the EOS.
+template <bool MG>
+__device__ __forceinline__ void ghost_put(const Dev& d, const InstParams& P1, int ccx, int ccy, uint32_t x,
+                                          const Loaded& l, GhostLds& G) {
+  if (x >= (uint32_t)GHOST_EC) return;
+  const Gathered v = sort_finish<MG, false>(d, P1, ccx, ccy, l);
+  G.pv[x] = v.pv;
+  G.aux[x] = v.inst < 0 ? make_float4(1.0f, 0.0f, 0.0f, 0.0f) : v.aux;
+}
+// The entries i0, i0 + 4, ... of a cell's bucket (n entries, from region place
+// off on) that fall into the window from w0.
+template <bool MG>
+__device__ __forceinline__ void ghost_stage(const Dev& d, const Buf& pre, const InstParams& P1, int ccx, int ccy,
+                                            const uint32_t* raw, uint32_t n, uint32_t off, uint32_t i0, uint32_t w0,
+                                            GhostLds& G) {
+#pragma unroll 1
+  for (uint32_t i = i0; i < n; i += 4) {
+    const uint32_t ei = raw[i];
+    uint32_t ri = 0u;
+    for (uint32_t k = 0; k < n; ++k) ri += raw[k] < ei ? 1u : 0u;
+    if (off + ri - w0 < (uint32_t)GHOST_EC)
+      ghost_put<MG>(d, P1, ccx, ccy, off + ri - w0, sort_load<false>(d, pre, ei), G);
+  }
+}
+// An item's candidates: region ranges of its rows (start, middle cell, end of
+// the middle cell), candidates in the first, the first two and all rows.
+struct GhostRows {
+  uint32_t s0, m0, e0, s1, m1, e1, s2, m2, e2, n0, n01, nn;
+};
+// Candidate k of an item in the window from w0: its place there and its cell-
+// shift code; false when it is in a later window.
+__device__ __forceinline__ bool ghost_candidate(GhostRows R, uint32_t k, uint32_t w0, uint32_t& x, uint32_t& code) {
+  const bool in0 = k < R.n0, in1 = k < R.n01;
+  const uint32_t j = in0 ? R.s0 + k : (in1 ? R.s1 + (k - R.n0) : R.s2 + (k - R.n01));
+  const uint32_t jm = in0 ? R.m0 : (in1 ? R.m1 : R.m2), je = in0 ? R.e0 : (in1 ? R.e1 : R.e2);
+  x = j - w0;
+  code = (in0 ? 0u : (in1 ? 4u : 8u)) | (j < jm ? 0u : (j < je ? 1u : 2u));
+  return x < (uint32_t)GHOST_EC;
+}
+// Sorted slot of the ghost of item (l / 4) of block blk, by four lanes: the
+// entries of the tiles before its cell's, of the cells before it in its tile,
+// and below its own entry in its bucket. A ghost that its overfull cell
+// dropped has none (~0). The wave takes part in the block's first three
+// barriers on the way, with its loads in flight.
+__device__ __forceinline__ uint32_t ghost_slot(const Dev& d, const uint32_t* bucket, const uint32_t* count,
+                                               const uint32_t* tot, const uint32_t* rcell, const uint32_t* rslot,
+                                               int4 blk, int l) {
+  const int sub = l & 3, it = blk.y + min(l >> 2, blk.z - 1);
+  uint32_t K = 0u, place = 0u, e = 0u;
+  if (blk.w == 0) {
+    K = d.wcell[it];
+    place = d.wplace[it];
+  } else if (blk.w == 1) {
+    const int u = it - d.prm[0].nw;
+    K = rcell[u];
+    e = rslot[u];
+  }
+  __syncthreads();
+  if (blk.w == 0) e = bucket[(size_t)K * WC_BUCKET + place];
+  const int T0 = (int)(K / WC_SORT_TILE), K0 = T0 * WC_SORT_TILE;
+  const uint32_t n = min(count[K], (uint32_t)WC_BUCKET);
+  uint32_t before = 0u, found = 0u, b[SORT_SPEC], c[WC_SORT_TILE / 4];
+#pragma unroll
+  for (int k = 0; k < SORT_SPEC; ++k) b[k] = bucket[(size_t)K * WC_BUCKET + sub + 4 * k];
+#pragma unroll
+  for (int k = 0; k < WC_SORT_TILE / 4; ++k) c[k] = count[min(K0 + sub + 4 * k, (int)K)];
+  __syncthreads();
+  // the tiles before every item's by all lanes, the rest by the item's four
+  int Tc = T0;
+#pragma unroll
+  for (int o = 4; o < 64; o <<= 1) Tc = min(Tc, __shfl_xor(Tc, o));
+  uint32_t common = 0u;
+#pragma unroll 1
+  for (int u0 = l; u0 < Tc; u0 += 64 * 8) {
+    uint32_t v[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) v[k] = tot[min(u0 + 64 * k, Tc - 1)];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) common += u0 + 64 * k < Tc ? v[k] : 0u;
+  }
+#pragma unroll 1
+  for (int u0 = Tc + sub; u0 < T0; u0 += 4 * 8) {
+    uint32_t v[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) v[k] = tot[min(u0 + 4 * k, T0 - 1)];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) before += u0 + 4 * k < T0 ? v[k] : 0u;
+  }
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) common += __shfl_xor(common, o);
+#pragma unroll
+  for (int k = 0; k < WC_SORT_TILE / 4; ++k)
+    before += K0 + sub + 4 * k < (int)K ? min(c[k], (uint32_t)WC_BUCKET) : 0u;
+#pragma unroll
+  for (int k = 0; k < SORT_SPEC; ++k) {
+    const bool in = (uint32_t)(sub + 4 * k) < n;
+    before += in & (b[k] < e) ? 1u : 0u;
+    found |= in & (b[k] == e) ? 1u : 0u;
+  }
+  for (uint32_t i = sub + 4 * SORT_SPEC; i < n; i += 4) {
+    const uint32_t x = bucket[(size_t)K * WC_BUCKET + i];
+    before += x < e ? 1u : 0u;
+    found |= x == e ? 1u : 0u;
+  }
+  before += __shfl_xor(before, 1);
+  before += __shfl_xor(before, 2);
+  found |= __shfl_xor(found, 1);
+  found |= __shfl_xor(found, 2);
+  __syncthreads();
+  return found != 0u && blk.w != 2 ? common + before : ~0u;
+}
+template <int MODE, bool MG, bool CUB>
+__device__ __forceinline__ void ghost_block(const Dev& d, const Buf& pre, const Buf& out, int b, uint32_t* s_raw,
+                                            uint32_t* s_off, GhostLds& G) {
+  constexpr int GL = WC_GHOST_LANES;
+  static_assert(GL == 16 && WC_GHOST_REGION == WC_SORT_TILE && SORT_BLOCK == 320, "shapes of a ghost block");
+  const int t = (int)threadIdx.x;
+  const int4 blk = d.sblk[b];
+  const int kind = blk.w;
+  if (MODE == EV_B && kind == 2) return;  // (probes are of the predictor's state)
+  constexpr bool set_b = MODE == EV_B;
+  const uint32_t* bucket = set_b ? d.bucket_b : d.bucket_a;
+  const uint32_t* count = set_b ? d.count_b : d.count_a;
+  if (t >= 256) {
+    // the last wave: the sorted slots of the items' ghosts
+    G.dst[(t - 256) >> 2] = ghost_slot(d, bucket, count, set_b ? d.tot_b : d.tot_a, set_b ? d.rcell_b : d.rcell_a,
+                                       set_b ? d.rslot_b : d.rslot_a, blk, t - 256);
+    __syncthreads();  // the block's fourth barrier (a wave that ended is not waited for at later ones)
+    return;
+  }
+  const InstParams P = scalar_copy(d.prm);
+  const DiskEval E = *(set_b ? d.deval_b : d.deval_a);
+  const int item = t / GL, lane = t % GL;
+  const bool act = item < blk.z;
+  const bool disk = kind == 1;
+  // the item: its cell and offset (an idle item repeats the block's first)
+  const int it = blk.y + (act ? item : 0);
+  uint32_t K;
+  float2 pg;
+  int g = it;
+  if (kind == 0) {
+    g = (int)d.witem[it];
+    K = d.wcell[it];
+    pg = d.wpos[it];
+  } else if (kind == 1) {
+    const int u = it - P.nw;
+    K = (set_b ? d.rcell_b : d.rcell_a)[u];
+    pg = (set_b ? d.rpos_b : d.rpos_a)[u];
+  } else {
+    const InstParams& Pp = d.prm[0];
+    K = Pp.probe_cell[it];
+    pg = make_float2(Pp.probe_ox[it], Pp.probe_oy[it]);
+  }
+  int cx, cy;
+  cell_xy(P, K, cx, cy);
+  // the region: the bounding box of the items' cells and one cell around it
+  {
+    int x0 = cx, x1 = cx, y0 = cy, y1 = cy;
+    for (int o = GL; o < 64; o <<= 1) {
+      x0 = min(x0, __shfl_xor(x0, o));
+      x1 = max(x1, __shfl_xor(x1, o));
+      y0 = min(y0, __shfl_xor(y0, o));
+      y1 = max(y1, __shfl_xor(y1, o));
+    }
+    if ((t & 63) == 0) {
+      int* B = G.box[t >> 6];
+      B[0] = x0;
+      B[1] = x1;
+      B[2] = y0;
+      B[3] = y1;
+    }
+  }
+  __syncthreads();
+  int rx0 = G.box[0][0], rx1 = G.box[0][1], ry0 = G.box[0][2], ry1 = G.box[0][3];
+#pragma unroll
+  for (int w = 1; w < 4; ++w) {
+    rx0 = min(rx0, G.box[w][0]);
+    rx1 = max(rx1, G.box[w][1]);
+    ry0 = min(ry0, G.box[w][2]);
+    ry1 = max(ry1, G.box[w][3]);
+  }
+  rx0 = max(rx0 - 1, 0);
+  rx1 = min(rx1 + 1, P.ncx - 1);
+  ry0 = max(ry0 - 1, 0);
+  ry1 = min(ry1 + 1, P.ncy - 1);
+  const int rw = rx1 - rx0 + 1, nc = min(rw * (ry1 - ry0 + 1), WC_GHOST_REGION);
+  // four lanes per cell, as in the tiles
+  const int c = t >> 2, sub = t & 3;
+  const int ccy = ry0 + c / rw, ccx = rx0 + c % rw;
+  const uint32_t Kc = (uint32_t)(P.cell_off + ccy * P.ncx + ccx);
+  uint32_t n = 0u, e[SORT_SPEC], r[SORT_SPEC];
+  Loaded lv[SORT_SPEC];
+  if (c < nc) {
+    n = min(count[Kc], (uint32_t)WC_BUCKET);
+#pragma unroll
+    for (int u = 0; u < SORT_SPEC; ++u) e[u] = bucket[(size_t)Kc * WC_BUCKET + sub + 4 * u];
+  } else {
+#pragma unroll
+    for (int u = 0; u < SORT_SPEC; ++u) e[u] = 0u;
+  }
+  uint32_t* raw = s_raw + c * WC_BUCKET;
+#pragma unroll
+  for (int u = 0; u < SORT_SPEC; ++u)
+    if ((uint32_t)(sub + 4 * u) < n) raw[sub + 4 * u] = e[u];
+#pragma unroll
+  for (int u = 0; u < SORT_SPEC; ++u) lv[u] = sort_load<false>(d, pre, (uint32_t)(sub + 4 * u) < n ? e[u] : 0u);
+  for (uint32_t i = sub + 4 * SORT_SPEC; i < n; i += 4) raw[i] = bucket[(size_t)Kc * WC_BUCKET + i];
+  if (sub == 0) G.n[c] = n;
+  wave_sync();  // the buckets of this wave's cells are in LDS
+#pragma unroll
+  for (int u = 0; u < SORT_SPEC; ++u) r[u] = 0u;
+  for (uint32_t k = 0; k < n; ++k) {
+    const uint32_t x = raw[k];
+#pragma unroll
+    for (int u = 0; u < SORT_SPEC; ++u) r[u] += x < e[u] ? 1u : 0u;
+  }
+  __syncthreads();
+  if (t < 64) {  // region offsets of the cells
+    const uint32_t cnt = G.n[t];
+    uint32_t incl = cnt;
+    for (int o = 1; o < 64; o <<= 1) {
+      const uint32_t u = __shfl_up(incl, o);
+      if (t >= o) incl += u;
+    }
+    s_off[t] = incl - cnt;
+    if (t == 63) s_off[64] = incl;
+  }
+  __syncthreads();
+  const uint32_t total = s_off[64], off = s_off[c];
+  // the item's rows: region ranges of its (up to) three cells each
+  // (a row beside the grid is empty; the region holds every other)
+  const int xl = max(cx - 1, rx0) - rx0, xm = cx - rx0, xr = min(cx + 1, rx1) - rx0 + 1;
+  const bool ok0 = cy - 1 >= ry0, ok2 = cy + 1 <= ry1;
+  const int b1 = (cy - ry0) * rw, b0 = ok0 ? b1 - rw : 0, b2 = ok2 ? b1 + rw : 0;
+  GhostRows R;
+  R.s0 = s_off[min(b0 + xl, 64)];
+  R.m0 = s_off[min(b0 + xm, 64)];
+  R.e0 = s_off[min(b0 + xm + 1, 64)];
+  R.s1 = s_off[min(b1 + xl, 64)];
+  R.m1 = s_off[min(b1 + xm, 64)];
+  R.e1 = s_off[min(b1 + xm + 1, 64)];
+  R.s2 = s_off[min(b2 + xl, 64)];
+  R.m2 = s_off[min(b2 + xm, 64)];
+  R.e2 = s_off[min(b2 + xm + 1, 64)];
+  R.n0 = ok0 ? s_off[min(b0 + xr, 64)] - R.s0 : 0u;
+  R.n01 = R.n0 + (s_off[min(b1 + xr, 64)] - R.s1);
+  R.nn = R.n01 + (ok2 ? s_off[min(b2 + xr, 64)] - R.s2 : 0u);
+  // the first window: the state of its entries is on its way already
+#pragma unroll
+  for (int u = 0; u < SORT_SPEC; ++u)
+    if ((uint32_t)(sub + 4 * u) < n) ghost_put<MG>(d, P, ccx, ccy, off + r[u], lv[u], G);
+  ghost_stage<MG>(d, pre, P, ccx, ccy, raw, n, off, (uint32_t)(sub + 4 * SORT_SPEC), 0u, G);
+  __syncthreads();
+  // lane l of an item takes its candidates l, l + GL, ...; `staged`: the
+  // window that stands in LDS
+  uint32_t staged = 0u;
+  auto window = [&](uint32_t w0) __attribute__((always_inline)) {
+    if (w0 == staged) return;
+    __syncthreads();  // the previous window is no longer read
+    ghost_stage<MG>(d, pre, P, ccx, ccy, raw, n, off, (uint32_t)sub, w0, G);
+    __syncthreads();
+    staged = w0;
+  };
+  Shep S = {0, 0, 0, 0, 0, 0};
+  uint32_t k = (uint32_t)lane, x, code;
+#pragma unroll 1
+  for (uint32_t w0 = 0u; w0 < total; w0 += GHOST_EC) {
+    window(w0);
+    for (; k < R.nn && ghost_candidate(R, k, w0, x, code); k += GL)
+      shepard_add<CUB>(P, pg.x, pg.y, G.pv[x], G.aux[x], code, S);
+  }
+  shepard_sum<GL>(S);
+  if (kind == 2) {
+    if (act && lane == 0) {
+      const long long row = E.row % WC_HIST_CAP;
+      d.hist_p[row * WC_MAX_PROBES + it] = S.W > 0.0f ? S.p / S.W : 0.0f;
+    }
+    return;
+  }
+  // axisymmetric form: a wall ghost below the axis mirrors the fluid (slip)
+  // and is off (zero mass, at rest) inside the sphere
+  bool axis = false, dead = false;
+  if (P.axisym && !disk) {
+    const double yg = P.y_lo + (double)cy * P.dcd + (double)pg.y;
+    axis = yg < 0.0;
+    if (axis && P.nd > 0) {
+      const double xg = P.x_lo + (double)cx * P.dcd + (double)pg.x;
+      const double ux = xg - E.xd, uy = yg - P.disk_y0;
+      dead = ux * ux + uy * uy < P.R * P.R;  // the same on every lane of the item
+    }
+  }
+  GhostState q = ghost_state(P, S, disk, axis, (float)E.vd, (float)E.ad);
+  const float m = disk ? P.m_disk : P.m_wall;
+  float vmag = 0.0f;
+  if (act && lane == 0) {
+    float4 gp = make_float4(pg.x, pg.y, 0.0f, 0.0f), ga = make_float4(P.rho0, 0.0f, P.c0, -0.0f);
+    if (!dead) {
+      gp = make_float4(pg.x, pg.y, q.vx, q.vy);
+      ga = make_float4(q.rho, q.P, q.c, -m);
+      vmag = fast_sqrt(q.vx * q.vx + q.vy * q.vy);
+    }
+    const uint32_t dst = G.dst[item];
+    if (dst < (uint32_t)d.n_slots) {
+      out.pv[dst] = gp;
+      out.aux[dst] = ga;
+    }
+  }
+  if constexpr (MODE == EV_B) {
+    if (disk) {
+      // x force of this ring ghost on its fluid neighbours (pressure + AV)
+      float fx = 0.0f;
+      const float yg = (float)(P.y_lo + (double)cy * P.dcd) + pg.y;  // the ghost's radius (axisymmetric)
+      k = (uint32_t)lane;
+#pragma unroll 1
+      for (uint32_t w0 = 0u; w0 < total; w0 += GHOST_EC) {
+        window(w0);
+        for (; k < R.nn && ghost_candidate(R, k, w0, x, code); k += GL)
+          ring_force_add<CUB>(P, pg.x, pg.y, yg, m, q, G.pv[x], G.aux[x], code, fx);
+      }
+      const double f = group_sum<GL>((double)fx);
+      if (act && lane == 0) d.wb_part[g - P.nw] = f;
+    }
+  } else {
+    // the block's maximum (no atomics on one address: the pair pass reads all)
+    const float w = wave_max(vmag);
+    if ((t & 63) == 0) G.vmax[t >> 6] = w;
+    __syncthreads();
+    if (t == 0) d.gvmax[b] = fmaxf(fmaxf(G.vmax[0], G.vmax[1]), fmaxf(G.vmax[2], G.vmax[3]));
+  }
+}
+
+// GH: with the ghosts (see ghost_block): blocks 1 .. n_tiles sort, the blocks
+// after them compute ghosts and probes.
+template <int MODE, bool BATCH, bool MG, bool GH, bool CUB>
+__global__ __launch_bounds__(SORT_BLOCK) void k_sort(Dev d, Buf pre, Buf out, int n_tiles) {
   constexpr int T = WC_SORT_TILE;
   __shared__ uint32_t s_off[T + 1];  // exclusive offsets of the tile's cells, total at [T]
   __shared__ uint32_t s_base;        // sorted slots before this tile
   __shared__ uint32_t s_raw[T * WC_BUCKET];
   const int t = threadIdx.x;
+  if constexpr (GH) {
+    __shared__ GhostLds sG;
+    if ((int)blockIdx.x > n_tiles) {
+      ghost_block<MODE, MG, CUB>(d, pre, out, (int)blockIdx.x - 1 - n_tiles, s_raw, s_off, sG);
+      return;
+    }
+  }
   if (blockIdx.x == 0) {
     if (t < 64) {
       for (int i = t; i < d.n_inst; i += 64) clock_commit<MODE>(d, i);
@@ -1217,6 +1686,7 @@ __global__ __launch_bounds__(SORT_BLOCK) void k_sort(Dev d, Buf pre, Buf out) {
   // a leapfrog step, else a
   const bool set_b = MODE == EV_B || (MODE == EV_L && d.lf_set != 0);
   const uint32_t* bucket = set_b ? d.bucket_b : d.bucket_a;
+  const uint32_t* count = set_b ? d.count_b : d.count_a;
   // cell lanes: lane sub of cell c owns the entries sub + 4 u of its bucket
   const int ct = t - 64, c = ct >> 2, sub = ct & 3;
   // a single instance's constants (through the scalar cache; not changed by the launch)
@@ -1232,7 +1702,7 @@ __global__ __launch_bounds__(SORT_BLOCK) void k_sort(Dev d, Buf pre, Buf out) {
     // entry totals of the tiles before it (filled with the buckets)
     const int K = tile * T + t;
     const uint32_t* tot = set_b ? d.tot_b : d.tot_a;
-    const uint32_t cnt_raw = d.count[min(K, d.n_cells - 1)];  // in flight during the prefix
+    const uint32_t cnt_raw = count[min(K, d.n_cells - 1)];  // in flight during the prefix
     // SORT_PRE loads in flight per lane and round (an index past the
     // preceding tiles reads the last of them and adds nothing), so the last
     // tiles wait for one round of latency, not one per 64 tiles
@@ -1262,7 +1732,7 @@ __global__ __launch_bounds__(SORT_BLOCK) void k_sort(Dev d, Buf pre, Buf out) {
   } else {
     const int K = tile * T + c;
     if (K < d.n_cells) {
-      n = min(d.count[K], (uint32_t)WC_BUCKET);
+      n = min(count[K], (uint32_t)WC_BUCKET);
 #pragma unroll
       for (int u = 0; u < SORT_SPEC; ++u) e[u] = bucket[(size_t)K * WC_BUCKET + sub + 4 * u];
     } else {
@@ -1302,7 +1772,7 @@ __global__ __launch_bounds__(SORT_BLOCK) void k_sort(Dev d, Buf pre, Buf out) {
   __syncthreads();  // offsets and the tile's base
   if (t < 64) {
     const int K = tile * T + t;
-    if (K < d.n_cells) d.count[K] = d.wallcount[K];  // re-arm for the next sort (every count was read)
+    if (K < d.n_cells) (set_b ? d.count_a : d.count_b)[K] = d.wallcount[K];  // re-arm the other set's count
     // a cell that took more entries than its bucket (flagged when filled)
     // leaves a gap in the tile's slot range, and the particles it dropped
     // leave the slots past the last tile unfilled from then on: both are
@@ -1311,7 +1781,7 @@ __global__ __launch_bounds__(SORT_BLOCK) void k_sort(Dev d, Buf pre, Buf out) {
     // a finite state that no later kernel moves or counts
     const uint32_t* tot = set_b ? d.tot_b : d.tot_a;
     const uint32_t stored = s_off[T];
-    const uint32_t end = tile == (int)gridDim.x - 2 ? (uint32_t)d.n_slots - s_base : tot[tile];
+    const uint32_t end = tile == n_tiles - 1 ? (uint32_t)d.n_slots - s_base : tot[tile];
     const uint32_t kin = (uint32_t)min(tile * T + T - 1, d.n_cells - 1);
     for (uint32_t g = stored + (uint32_t)t; g < end; g += 64) {
       const uint32_t dst = s_base + g;
@@ -1330,13 +1800,13 @@ __global__ __launch_bounds__(SORT_BLOCK) void k_sort(Dev d, Buf pre, Buf out) {
   const uint32_t base = s_base + s_off[c], K = (uint32_t)(tile * T + c);
 #pragma unroll
   for (int u = 0; u < SORT_SPEC; ++u)
-    if ((uint32_t)(sub + 4 * u) < n) sort_store<BATCH>(d, P1, out, e[u], base + r[u], K, gv[u]);
+    if ((uint32_t)(sub + 4 * u) < n) sort_store<BATCH, GH>(d, P1, out, e[u], base + r[u], K, gv[u]);
   const uint32_t* raw = s_raw + c * WC_BUCKET;
   for (uint32_t i = sub + 4 * SORT_SPEC; i < n; i += 4) {
     const uint32_t ei = raw[i];
     uint32_t ri = 0u;
     for (uint32_t k = 0; k < n; ++k) ri += raw[k] < ei ? 1u : 0u;
-    sort_store<BATCH>(d, P1, out, ei, base + ri, K, sort_finish<MG, BATCH>(d, P1, cx, cy, sort_load<BATCH>(d, pre, ei)));
+    sort_store<BATCH, GH>(d, P1, out, ei, base + ri, K, sort_finish<MG, BATCH>(d, P1, cx, cy, sort_load<BATCH>(d, pre, ei)));
   }
 }
 
@@ -1406,45 +1876,12 @@ __global__ __launch_bounds__(WC_GHOST_BLOCK) void k_ghost(Dev d, Buf sb) {
       }
     } else {
       const Shep S = shepard<GL, CUB>(d, P, sb, K, pg.x, pg.y, lane);
-      const float vwx = disk ? (float)C.vd : 0.0f;
-      const float awx = disk ? (float)C.ad : 0.0f;
-      float p, vgx, vgy;
-      if (S.W > 0.0f) {
-        const float inv = 1.0f / S.W;
-        // body-force term (g - a_w) . sum rho_j (r_g - r_j) W
-        p = (S.p + (0.0f - awx) * S.rx + P.gy * S.ry) * inv;
-        vgx = axis ? S.vx * inv : 2.0f * vwx - S.vx * inv;  // axis: the axial velocity is kept
-        vgy = -S.vy * inv;
-      } else {
-        p = 0.0f;
-        vgx = vwx;
-        vgy = 0.0f;
-      }
-      p = fmaxf(p, P.p_cav);
-      float rg, cg;
-      if (P.eos_type == 1) {
-        // Mie-Grueneisen inverse: tension line, or the root in [0, 1/b) of
-        // s (1 - b mu)^2 = mu (1 + k1 mu), s = p / K; capped at mu_max
-        const float sp = p / P.mg_K;
-        float mu = sp;
-        if (P.ghost_rho_mode != 0 && sp > 0.0f)
-          mu = fminf(2.0f * sp / ((1.0f + 2.0f * P.mg_b * sp) + sqrtf(1.0f + 4.0f * sp * (P.mg_b + P.mg_k1))),
-                     P.mg_mu_max);
-        rg = P.rho0 * (1.0f + mu);
-        float pu;
-        mg_eos(P, mu, pu, cg);
-      } else {
-        if (P.ghost_rho_mode == 0) rg = P.rho0 * (1.0f + p * P.inv_rho0c02);
-        else rg = P.rho0 * expf(P.inv_gamma * log1pf(p / P.B));
-        const float xg = (rg - P.rho0) / P.rho0, yg = 1.0f + xg;
-        cg = P.gamma == 7.0f ? P.c0 * (yg * yg * yg) : P.c0 * expf(P.c_exp * log1pf(xg));
-      }
-      const float Pg = p / (rg * rg);
+      const GhostState q = ghost_state(P, S, disk, axis, (float)C.vd, (float)C.ad);
       const float m = disk ? P.m_disk : P.m_wall;
       if (lane == 0) {
-        sb.pv[s] = make_float4(pg.x, pg.y, vgx, vgy);
-        sb.aux[s] = make_float4(rg, Pg, cg, -m);
-        vmag = fast_sqrt(vgx * vgx + vgy * vgy);
+        sb.pv[s] = make_float4(pg.x, pg.y, q.vx, q.vy);
+        sb.aux[s] = make_float4(q.rho, q.P, q.c, -m);
+        vmag = fast_sqrt(q.vx * q.vx + q.vy * q.vy);
       }
       if ((MODE == EV_B || MODE == EV_L) && disk) {
         // x force of this ring ghost on its fluid neighbours (pressure + AV)
@@ -1453,24 +1890,7 @@ __global__ __launch_bounds__(WC_GHOST_BLOCK) void k_ghost(Dev d, Buf sb) {
         cell_xy(P, K, rcx, rcy);
         const float yg = (float)(P.y_lo + (double)rcy * P.dcd) + pg.y;  // the ghost's radius (axisymmetric)
         for_candidates<GL>(d, P, sb, K, lane, [&](const float4& pj, const float4& aj, uint32_t code) __attribute__((always_inline)) {
-          if (!(aj.w > 0.0f)) return;
-          float rx, ry;
-          rel_pos(P, pg.x, pg.y, pj, code, rx, ry);
-          rx = -rx;  // r_i - r_g
-          ry = -ry;
-          const float r2 = rx * rx + ry * ry;
-          if (!(r2 < P.four_h2)) return;
-          float W, F;
-          if constexpr (CUB) cubic_spline(P, r2, W, F);
-          else wendland(P, r2, W, F);
-          const float vr = (pj.z - vgx) * rx + (pj.w - vgy) * ry;
-          const float rsum = aj.x + rg, den = r2 + P.eta2h2;
-          const float inv = fast_rcp(den * rsum);
-          const float piav =
-              vr < 0.0f ? -P.alpha * (aj.z + cg) * P.h * vr * inv + P.beta2h2 * vr * vr * inv * (rsum * inv) : 0.0f;
-          // (axisymmetric: the fluid particle's ring mass 2 pi m r in place of m)
-          const float mi = P.axisym ? aj.w * (6.283185307f * fmaxf(yg + ry, P.r_min)) : aj.w;
-          fx -= mi * m * (aj.y + Pg + piav) * F * rx;
+          ring_force_add<CUB>(P, pg.x, pg.y, yg, m, q, pj, aj, code, fx);
         });
         const double f = group_sum<GL>((double)fx);
         if (lane == 0) d.wb_part[inst * WC_MAX_RING + (g - P.nw)] = f;
@@ -1559,6 +1979,8 @@ __device__ __forceinline__ double eos_e_el(const InstParams& P, double r) {
 template <int MODE, bool BATCH, bool AUD, int VAR>
 __global__ __launch_bounds__(PAIR_BLOCK, (AUD || MODE == EV_EXPORT) ? 1 : PAIR_MINW)
 void k_pair(Dev d, Buf sb, Buf base, Buf out) {
+  constexpr bool MRG = (VAR & 16) != 0;  // the ghosts are in the sorts' launches
+  float vg = 0.0f;  // this lane's share of the ghosts' max |v| (second phase)
   // the first phase's LDS, and in its place after a barrier the hand-over of
   // each slot from the first phase to the second
   struct HandOver {
@@ -1600,6 +2022,8 @@ void k_pair(Dev d, Buf sb, Buf base, Buf out) {
     // fetched now, used after the pair sums
     uint32_t eb = 0u;
     if (MODE == EV_B && q == 0 && inr) eb = d.perm[s];
+    if constexpr (MRG && MODE == EV_A)
+      if (threadIdx.x < PAIR_SLOTS) vg = ghost_vmax(d);
     PairAcc acc = {};
     AudAcc aud = {};
     PairC G0;
@@ -1656,6 +2080,8 @@ void k_pair(Dev d, Buf sb, Buf base, Buf out) {
   if constexpr (!BATCH) {
     P1 = scalar_copy(d.prm);
     C1 = scalar_copy(d.clk);
+    if constexpr (MRG && MODE == EV_A)
+      C1.vmax_bits = max(C1.vmax_bits, (uint32_t)__builtin_amdgcn_readfirstlane(__float_as_int(wave_max(vg))));
   }
   Clock* clk = d.clk;
   const InstParams& P = BATCH ? d.prm[inst] : P1;
@@ -1687,7 +2113,7 @@ void k_pair(Dev d, Buf sb, Buf base, Buf out) {
         double vc, ac;
         disk_at(P, C, C.t + 0.5 * step_dt(d, P, C), xc, vc, ac);
       }
-      place_ring(d, P, inst, ring, xc, out, s, bucket);
+      place_ring<!MRG ? 0 : (MODE == EV_A ? 2 : 1)>(d, P, inst, ring, xc, out, s, bucket);
     } else {
       const uint32_t K = (uint32_t)(P.cell_off + scy * P.ncx + scx);
       out.cell[s] = K;
@@ -1892,6 +2318,21 @@ void k_pair(Dev d, Buf sb, Buf base, Buf out) {
       }
     }
   }
+  if constexpr (MRG && (MODE == EV_A || MODE == EV_B)) {
+    // the ghosts' v_max for the next commit of the clock, and the disk of the
+    // ghosts in the next sort (at t + dt/2, or the new state's and its probe row)
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      DiskEval& E = MODE == EV_A ? *d.deval_b : *d.deval_a;
+      if constexpr (MODE == EV_A) {
+        *d.gvstep = C.vmax_bits;
+        disk_at(P, C, C.t + 0.5 * step_dt(d, P, C), E.xd, E.vd, E.ad);
+      } else {
+        C1.t_next = C1.t + C1.dt;
+        disk_newest(P, C1, E.xd, E.vd, E.ad);
+        E.row = C.step + 1;
+      }
+    }
+  }
 }
 
 // Summation density of scheme 1 (eq. density-sum), in place on the sorted
@@ -2024,7 +2465,8 @@ __global__ __launch_bounds__(WC_BLOCK) void k_init(Dev d, Buf X) {
     } else if (local >= P.nf + P.nw) {
       double xc, vc, ac;
       disk_newest(P, d.clk[inst], xc, vc, ac);
-      place_ring(d, P, inst, local - P.nf - P.nw, xc, X, s, fill_a(d));
+      if (!BATCH && d.merged) place_ring<1>(d, P, inst, local - P.nf - P.nw, xc, X, s, fill_a(d));
+      else place_ring<0>(d, P, inst, local - P.nf - P.nw, xc, X, s, fill_a(d));
     } else {
       bucket_put_wall(d, P, fill_a(d), X.cell[s], local - P.nf, (uint32_t)s);
     }
@@ -2032,6 +2474,13 @@ __global__ __launch_bounds__(WC_BLOCK) void k_init(Dev d, Buf X) {
   // fluid slots into their buckets, one counter update per run of equal keys
   bucket_put_wave(d, fill_a(d), fl, fl ? X.cell[s] : 0u, (uint32_t)s);
   vmax_update<BATCH>(d.clk, inst, fl, v);
+  if (d.merged) {
+    if (s == 0) {  // the disk of the next predictor evaluation and its probe row
+      DiskEval& E = *d.deval_a;
+      disk_newest(d.prm[0], d.clk[0], E.xd, E.vd, E.ad);
+      E.row = d.clk[0].step + 1;
+    }
+  }
   if (!BATCH && s < d.n_vpart) d.vmax_part[s] = 0.0f;  // the loaded state's max is in the clock
 }
 
@@ -2158,7 +2607,7 @@ __global__ __launch_bounds__(64) void k_diag_final(Dev d) {
 
 // The sort counters of an unfilled bucket set a: the static wall-ghost entries.
 __device__ __forceinline__ void arm_a(const Dev& d, int u) {
-  if (u < d.n_cells) d.count[u] = d.wallcount[u];
+  if (u < d.n_cells) d.count_a[u] = d.wallcount[u];
   if (u < (d.n_cells + WC_SORT_TILE - 1) / WC_SORT_TILE) d.tot_a[u] = d.wall_tot[u];
 }
 __global__ __launch_bounds__(WC_BLOCK) void k_arm(Dev d) { arm_a(d, blockIdx.x * WC_BLOCK + threadIdx.x); }
@@ -2299,6 +2748,7 @@ static void launch_ghost(const Dev& d, int n_gblk, const Buf& sb, hipStream_t st
 // The pair pass of the context's scheme variant: bit 0 the quadratic AV
 // term (some instance has beta > 0), bit 1 the cubic spline kernel; scheme 1
 // (d.var bit 3) sums the internal-energy rate in place of the density rate.
+// (V4 bit 4: ghosts in the sort's launch)
 template <int MODE, bool BATCH, bool AUD, int V4>
 static void launch_pair_v(const Dev& d, const Buf& sb, const Buf& base, const Buf& out, hipStream_t st) {
   const dim3 g(NQ(d.n_slots)), b(PAIR_BLOCK);
@@ -2316,6 +2766,9 @@ static void launch_pair(const Dev& d, const Buf& sb, const Buf& base, const Buf&
     if (d.var & 8) launch_pair_v<MODE, BATCH, AUD, 4>(d, sb, base, out, st);
     else launch_pair_v<MODE, BATCH, AUD, 0>(d, sb, base, out, st);
   } else {
+    if constexpr (!BATCH) {
+      if (d.merged) return launch_pair_v<MODE, false, AUD, 16>(d, sb, base, out, st);
+    }
     launch_pair_v<MODE, BATCH, AUD, 0>(d, sb, base, out, st);
   }
 }
@@ -2328,29 +2781,41 @@ static void launch_dens(const Dev& d, const Buf& sb, bool count, hipStream_t st)
   else k_dens<BATCH, 0><<<g, b, 0, st>>>(d, sb, count ? 1 : 0);
 }
 
-template <bool BATCH>
-static void eval_sort(const Dev& d, hipStream_t st, int mode, const Buf& pre, const Buf& out) {
-  const int nt = (d.n_cells + WC_SORT_TILE - 1) / WC_SORT_TILE + 1;  // the clock block, then the tiles
-  if (d.var & 4) {
-    if (mode == EV_A) k_sort<EV_A, BATCH, true><<<nt, SORT_BLOCK, 0, st>>>(d, pre, out);
-    else if (mode == EV_B) k_sort<EV_B, BATCH, true><<<nt, SORT_BLOCK, 0, st>>>(d, pre, out);
-    else if (mode == EV_L) k_sort<EV_L, BATCH, true><<<nt, SORT_BLOCK, 0, st>>>(d, pre, out);
-    else k_sort<EV_EXPORT, BATCH, true><<<nt, SORT_BLOCK, 0, st>>>(d, pre, out);
-  } else {
-    if (mode == EV_A) k_sort<EV_A, BATCH, false><<<nt, SORT_BLOCK, 0, st>>>(d, pre, out);
-    else if (mode == EV_B) k_sort<EV_B, BATCH, false><<<nt, SORT_BLOCK, 0, st>>>(d, pre, out);
-    else if (mode == EV_L) k_sort<EV_L, BATCH, false><<<nt, SORT_BLOCK, 0, st>>>(d, pre, out);
-    else k_sort<EV_EXPORT, BATCH, false><<<nt, SORT_BLOCK, 0, st>>>(d, pre, out);
+// The sort of an evaluation; GH: with the ghosts (nb blocks) in its launch.
+template <int MODE, bool BATCH, bool MG, bool GH, bool CUB>
+static void launch_sort(const Dev& d, hipStream_t st, int nb, const Buf& pre, const Buf& out) {
+  const int nt = (d.n_cells + WC_SORT_TILE - 1) / WC_SORT_TILE;  // the clock block, the tiles, the ghosts
+  k_sort<MODE, BATCH, MG, GH, CUB><<<1 + nt + (GH ? nb : 0), SORT_BLOCK, 0, st>>>(d, pre, out, nt);
+}
+template <int MODE, bool BATCH>
+static void sort_only(const Dev& d, hipStream_t st, const Buf& pre, const Buf& out) {
+  if (d.var & 4) launch_sort<MODE, BATCH, true, false, false>(d, st, 0, pre, out);
+  else launch_sort<MODE, BATCH, false, false, false>(d, st, 0, pre, out);
+}
+// Sort and ghosts of a predictor or corrector evaluation: one launch (nb
+// blocks of the table d.sblk) or two (nb of d.gblk), see merge_ghosts.
+template <int MODE, bool BATCH>
+static void sort_ghosts(const Dev& d, hipStream_t st, int nb, const Buf& pre, const Buf& out) {
+  if constexpr (!BATCH) {
+    if (d.merged) {
+      switch (d.var & 6) {
+        case 0: launch_sort<MODE, false, false, true, false>(d, st, nb, pre, out); break;
+        case 2: launch_sort<MODE, false, false, true, true>(d, st, nb, pre, out); break;
+        case 4: launch_sort<MODE, false, true, true, false>(d, st, nb, pre, out); break;
+        default: launch_sort<MODE, false, true, true, true>(d, st, nb, pre, out); break;
+      }
+      return;
+    }
   }
+  sort_only<MODE, BATCH>(d, st, pre, out);
+  launch_ghost<MODE, BATCH>(d, nb, out, st);
 }
 
 template <bool BATCH>
 static void enqueue_step_t(const Dev& d, const Bufs& b, int n_gblk, bool two_way, bool audit, hipStream_t st) {
-  eval_sort<BATCH>(d, st, EV_A, b.X, b.Y);
-  launch_ghost<EV_A, BATCH>(d, n_gblk, b.Y, st);
+  sort_ghosts<EV_A, BATCH>(d, st, n_gblk, b.X, b.Y);
   launch_pair<EV_A, BATCH>(d, b.Y, b.Y, b.Z, st);
-  eval_sort<BATCH>(d, st, EV_B, b.Z, b.W);
-  launch_ghost<EV_B, BATCH>(d, n_gblk, b.W, st);
+  sort_ghosts<EV_B, BATCH>(d, st, n_gblk, b.Z, b.W);
   if (two_way) k_disk<<<d.n_inst, 64, 0, st>>>(d);
   if (!BATCH && audit) launch_pair<EV_B, false, true>(d, b.W, b.Y, b.X, st);
   else launch_pair<EV_B, BATCH>(d, b.W, b.Y, b.X, st);
@@ -2363,7 +2828,7 @@ template <bool BATCH>
 static void enqueue_lf_t(const Dev& d, const Bufs& b, int n_gblk, int set, hipStream_t st) {
   Dev dl = d;
   dl.lf_set = set;
-  eval_sort<BATCH>(dl, st, EV_L, b.X, b.Y);
+  sort_only<EV_L, BATCH>(dl, st, b.X, b.Y);
   launch_dens<BATCH>(dl, b.Y, true, st);
   launch_ghost<EV_L, BATCH>(dl, n_gblk, b.Y, st);
   k_clock_lf<<<d.n_inst, 64, 0, st>>>(dl);
@@ -2402,8 +2867,8 @@ void wc_enqueue_diag(const Dev& d, const Bufs& b, bool sorted, hipStream_t st) {
 
 // Eval-A sort of X into Y without advancing the clock (test hooks).
 void wc_enqueue_export_sort(const Dev& d, const Bufs& b, bool batch, hipStream_t st) {
-  if (batch) eval_sort<true>(d, st, EV_EXPORT, b.X, b.Y);
-  else eval_sort<false>(d, st, EV_EXPORT, b.X, b.Y);
+  if (batch) sort_only<EV_EXPORT, true>(d, st, b.X, b.Y);
+  else sort_only<EV_EXPORT, false>(d, st, b.X, b.Y);
 }
 
 void wc_enqueue_export_ghosts(const Dev& d, const Bufs& b, int n_gblk, hipStream_t st) {
@@ -2447,12 +2912,10 @@ void wc_enqueue_neigh(const Dev& d, const Bufs& b, hipStream_t st) {
 
 void wc_enqueue_eval(const Dev& d, const Bufs& b, int n_gblk, int mode, hipStream_t st) {
   if (mode == EV_A) {
-    eval_sort<false>(d, st, EV_A, b.X, b.Y);
-    launch_ghost<EV_A, false>(d, n_gblk, b.Y, st);
+    sort_ghosts<EV_A, false>(d, st, n_gblk, b.X, b.Y);
     launch_pair<EV_A, false>(d, b.Y, b.Y, b.Z, st);
   } else {
-    eval_sort<false>(d, st, EV_B, b.Z, b.W);
-    launch_ghost<EV_B, false>(d, n_gblk, b.W, st);
+    sort_ghosts<EV_B, false>(d, st, n_gblk, b.Z, b.W);
     launch_pair<EV_B, false>(d, b.W, b.Y, b.X, st);
   }
 }

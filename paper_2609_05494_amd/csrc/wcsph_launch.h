@@ -11,6 +11,7 @@ struct Bufs {
   Buf X, Y, Z, W;
 };
 
+// n_gblk: entries of the ghosts' block table (d.sblk where d.merged, else d.gblk)
 // two_way: some instance has a two-way coupled disk (kin_mode 2)
 // audit: single-instance energy audit in the second pair pass
 void wc_enqueue_step(const Dev& d, const Bufs& b, int n_gblk, bool batch, bool two_way, bool audit,
