@@ -23,6 +23,7 @@
 #include "wcsph_adjoint.h"
 #include "wcsph_launch.h"
 #include "wcsph_kin.h"
+#include "wcsph_wave.h"
 
 namespace {
 
@@ -52,15 +53,22 @@ __device__ __forceinline__ void cxy(const InstParams& P, uint32_t K, int& cx, in
   cx = local - cy * P.ncx;
 }
 
-__device__ __forceinline__ double block_sum(double v, double* sh) {
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+// The block's sums of N values, added to o[0 .. N) (fixed order), whose old
+// values `old` threads 0 .. N - 1 read when the kernel began.
+template <int N>
+__device__ __forceinline__ void block_add(const double (&v)[N], double* o, double old) {
+  __shared__ double sh[N][4];
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
+    double t = v[k];
+    for (int m = 32; m > 0; m >>= 1) t += __shfl_xor(t, m);
+    if ((threadIdx.x & 63) == 0) sh[k][threadIdx.x >> 6] = t;
+  }
   __syncthreads();
-  double t = 0.0;
-  if (threadIdx.x == 0)
-    for (int w = 0; w < (int)(blockDim.x >> 6); ++w) t += sh[w];
-  __syncthreads();
-  return t;
+  if (threadIdx.x < N) {
+    const double* w = sh[threadIdx.x];
+    o[threadIdx.x] = old + (w[0] + w[1] + w[2] + w[3]);
+  }
 }
 
 // Ghost density, P and c as functions of the ghost pressure (linear branch)
@@ -192,17 +200,27 @@ __device__ __forceinline__ void adj_enforce_slot(const Dev& d, const InstParams&
 struct TRow {
   uint32_t rs, ms, me, re;
 };
-__device__ __forceinline__ TRow trow(const TapeEval& te, const InstParams& P, int cx, int cy, int dy) {
-  TRow r = {0u, 0u, 0u, 0u};
-  const int yy = cy + dy;
-  if (yy < 0 || yy >= P.ncy) return r;
+// The cell-start loads of the three rows complete together (the empty asm
+// statement takes them as operands) and without branches: a row outside the
+// grid reads the nearest row and is then empty.
+__device__ __forceinline__ void trows(const TapeEval& te, const InstParams& P, int cx, int cy, TRow& r0, TRow& r1,
+                                      TRow& r2) {
   const int xlo = max(cx - 1, 0), xhi = min(cx + 1, P.ncx - 1);
-  const uint32_t k0 = (uint32_t)(P.cell_off + yy * P.ncx);
-  r.rs = te.start[k0 + xlo];
-  r.ms = te.start[k0 + cx];
-  r.me = te.start[k0 + cx + 1];
-  r.re = te.start[k0 + xhi + 1];
-  return r;
+  uint32_t v[3][4];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const uint32_t* st = te.start + (P.cell_off + min(max(cy + k - 1, 0), P.ncy - 1) * P.ncx);
+    v[k][0] = st[xlo];
+    v[k][1] = st[cx];
+    v[k][2] = st[cx + 1];
+    v[k][3] = st[xhi + 1];
+  }
+#pragma unroll
+  for (int k = 0; k < 3; ++k) asm("" : "+v"(v[k][0]), "+v"(v[k][1]), "+v"(v[k][2]), "+v"(v[k][3]));
+  const bool b = cy > 0, t = cy < P.ncy - 1;
+  r0 = b ? TRow{v[0][0], v[0][1], v[0][2], v[0][3]} : TRow{0u, 0u, 0u, 0u};
+  r1 = TRow{v[1][0], v[1][1], v[1][2], v[1][3]};
+  r2 = t ? TRow{v[2][0], v[2][1], v[2][2], v[2][3]} : TRow{0u, 0u, 0u, 0u};
 }
 // candidate counts below rows 1 and 2, and in all three rows
 struct TCount {
@@ -227,9 +245,8 @@ __device__ __forceinline__ void tcand(const TRow& r0, const TRow& r1, const TRow
 #ifndef ADJ_FG
 #define ADJ_FG 8  // lanes per fluid slot in the fluid adjoint kernel
 #endif
-#ifndef ADJ_LCAP
-#define ADJ_LCAP 16  // entries of a lane's hit list in the fluid adjoint kernel
-#endif
+#define ADJ_CH 16  // candidates a lane tests per chunk, ADJ_FL of them with their loads in flight
+#define ADJ_FL 8
 
 template <int G>
 __device__ __forceinline__ float gsum(float v) {
@@ -252,19 +269,7 @@ __device__ __forceinline__ float gsum(float v) {
 // adjoint pointers, t_enf, hdt), so neither waits for the other.
 __global__ __launch_bounds__(256) void k_adj_ghost(Dev d, AdjPtrs a, TapeEval te, double t_eval, int n_gb,
                                                    double t_enf, float hdt, int acc_enf) {
-  __shared__ double shd[4];
-  // the instance's constants in LDS: read there in the candidate loop and
-  // the enforcement transpose, where from global memory the compiler waited
-  // for each field in turn
-  __shared__ InstParams sP;
-  {
-    constexpr int NP = (int)(sizeof(InstParams) / 4);
-    static_assert(sizeof(InstParams) % 4 == 0 && NP <= 256, "copy");
-    if ((int)threadIdx.x < NP)
-      reinterpret_cast<uint32_t*>(&sP)[threadIdx.x] = reinterpret_cast<const uint32_t*>(d.prm)[threadIdx.x];
-    __syncthreads();
-  }
-  const InstParams& P = sP;
+  const InstParams P = scalar_copy(d.prm);
   if ((int)blockIdx.x >= n_gb) {
     adj_enforce_slot(d, P, a, te, ((int)blockIdx.x - n_gb) * 256 + (int)threadIdx.x, t_enf, hdt, acc_enf);
     return;
@@ -272,7 +277,8 @@ __global__ __launch_bounds__(256) void k_adj_ghost(Dev d, AdjPtrs a, TapeEval te
   const int item = (int)((blockIdx.x * 256 + threadIdx.x) / AG_L);
   const int lane = (int)(threadIdx.x % AG_L);
   const int ng = P.nw + P.nd;
-  double c0bar = 0.0;
+  double c0bar = 0.0, old = 0.0;
+  if (threadIdx.x == 0) old = a.theta_part[(size_t)blockIdx.x * 3 + 2];
   const PairK<float> k = pair_k(P);
   if (item < ng) {
     const int t = item;
@@ -289,7 +295,8 @@ __global__ __launch_bounds__(256) void k_adj_ghost(Dev d, AdjPtrs a, TapeEval te
     const float mg = -ag.w;
     int cx, cy;
     cxy(P, K, cx, cy);
-    const TRow r0 = trow(te, P, cx, cy, -1), r1 = trow(te, P, cx, cy, 0), r2 = trow(te, P, cx, cy, 1);
+    TRow r0, r1, r2;
+    trows(te, P, cx, cy, r0, r1, r2);
     const TCount blk = tcount(r0, r1, r2);
     float gr = 0, gP = 0, gc = 0, gvx = 0, gvy = 0;
     float SW = 0, Sp = 0, Srx = 0, Sry = 0, Svx = 0, Svy = 0;
@@ -359,25 +366,21 @@ __global__ __launch_bounds__(256) void k_adj_ghost(Dev d, AdjPtrs a, TapeEval te
       c0bar += (double)(gr * gd.drho_dc0 + gP * gd.dP_dc0 + gc * (gd.dc_dc0 + gd.dc_drho * gd.drho_dc0));
       // v_g = 2 v_w - S_v / S_W; p_g = max(p~, p_cav)
       pbar = (SW > 0.0f && pt >= P.p_cav) ? pb : 0.0f;
-      float* o = a.gadj + (size_t)s * 10;
-      o[0] = pbar;
-      o[1] = SW > 0.0f ? gvx : 0.0f;
-      o[2] = SW > 0.0f ? gvy : 0.0f;
-      o[3] = SW;
-      o[4] = pt;
-      o[5] = vax;
-      o[6] = vay;
-      o[7] = ax_;
-      o[8] = ay_;
-      o[9] = 0.0f;
+      float4* o = a.gadj + (size_t)s * 3;
+      o[0] = make_float4(pbar, SW > 0.0f ? gvx : 0.0f, SW > 0.0f ? gvy : 0.0f, SW);
+      o[1] = make_float4(pt, vax, vay, ax_);
+      o[2] = make_float4(ay_, 0.0f, 0.0f, 0.0f);
     }
   } else if (item < ng + P.n_probes) {
     // probe Shepard sums at state n
     const int kk = item - ng;
-    const uint32_t K = P.probe_cell[kk];
+    const InstParams& Q = d.prm[0];  // (indexed per item)
+    const uint32_t K = Q.probe_cell[kk];
+    const float pox = Q.probe_ox[kk], poy = Q.probe_oy[kk];
     int cx, cy;
     cxy(P, K, cx, cy);
-    const TRow r0 = trow(te, P, cx, cy, -1), r1 = trow(te, P, cx, cy, 0), r2 = trow(te, P, cx, cy, 1);
+    TRow r0, r1, r2;
+    trows(te, P, cx, cy, r0, r1, r2);
     const TCount blk = tcount(r0, r1, r2);
     float SW = 0, Sp = 0;
     for (uint32_t c = (uint32_t)lane; c < blk.n; c += AG_L) {
@@ -388,7 +391,7 @@ __global__ __launch_bounds__(256) void k_adj_ghost(Dev d, AdjPtrs a, TapeEval te
       float4 pj = te.pv[j];
       asm("" : "+v"(aj.x), "+v"(aj.y), "+v"(aj.z), "+v"(aj.w), "+v"(pj.x), "+v"(pj.y), "+v"(pj.z), "+v"(pj.w));
       if (!(aj.w > 0.0f)) continue;
-      const float rx = P.probe_ox[kk] - (pj.x + (float)dx * P.dc), ry = P.probe_oy[kk] - (pj.y + (float)dy * P.dc);
+      const float rx = pox - (pj.x + (float)dx * P.dc), ry = poy - (pj.y + (float)dy * P.dc);
       const float r2 = rx * rx + ry * ry;
       if (!(r2 < P.four_h2)) continue;
       const float q = sqrtf(r2) * P.inv_h, sq = 1.0f - 0.5f * q, s2 = sq * sq;
@@ -403,8 +406,8 @@ __global__ __launch_bounds__(256) void k_adj_ghost(Dev d, AdjPtrs a, TapeEval te
       a.padj[2 * kk + 1] = SW > 0.0f ? Sp / SW : 0.0f;
     }
   }
-  const double tot = block_sum(c0bar, shd);
-  if (threadIdx.x == 0) a.theta_part[(size_t)blockIdx.x * 3 + 2] += tot;
+  const double th[1] = {c0bar};
+  block_add(th, a.theta_part + (size_t)blockIdx.x * 3 + 2, old);
 }
 
 // Fluid adjoints (pull form) for every fluid slot j of the taped
@@ -413,189 +416,207 @@ __global__ __launch_bounds__(256) void k_adj_ghost(Dev d, AdjPtrs a, TapeEval te
 // through the Shepard sums, the XSPH identity and (probe_seed != 0) the
 // probe terms; then the EOS chain. Output by particle id into lam_base
 // (added, or set when accumulate == 0).
-__global__ __launch_bounds__(256) void k_adj_fluid(Dev d, AdjPtrs a, TapeEval te, float probe_seed,
+//
+// Bound by one wave's own chain of loads and terms: the grid is about one
+// round of waves (28,352 particles: 4 per SIMD; 6,600: one). So every load
+// that does not depend on another is issued at once (constants through the
+// scalar cache, the slot's state, the cell starts, eight candidates a lane),
+// and the hits of a slot are dealt evenly to its lanes: three or four pair
+// terms in a row where the longest of 64 candidate-position lists had six.
+// 19.8 -> 16.0 us a launch at 28,352 particles, 13.7 -> 11.5 at 6,600.
+// Sixteen lanes a slot: 22 us at 28,352; four: 18.
+__global__ __launch_bounds__(256, 4) void k_adj_fluid(Dev d, AdjPtrs a, TapeEval te, float probe_seed,
                                                     int accumulate, int block0) {
   // ADJ_FG lanes per slot (lane g of the group) share its 3x3 candidates
-  __shared__ double shd[4];
-  __shared__ uint32_t s_hits[ADJ_LCAP * 256];
-  const InstParams& P = d.prm[0];
-  const int s = (int)((blockIdx.x * 256 + threadIdx.x) / ADJ_FG);
-  const int g = (int)(threadIdx.x % ADJ_FG);
+  constexpr int FG = ADJ_FG;
+  __shared__ uint32_t s_hits[256 / FG][FG * ADJ_CH];
+  const InstParams P = scalar_copy(d.prm);
+  const int bid = xcd_block(blockIdx.x, gridDim.x);
+  const int s = (int)((bid * 256 + threadIdx.x) / FG);
+  const int g = (int)(threadIdx.x % FG);
   const int N = d.n_slots;
   const PairK<float> k = pair_k(P);
-  double th_a = 0.0, th_d = 0.0, th_c = 0.0;
-  if (s < N) {
-    const float4 ai = te.aux[s];
-    const int id = (int)te.id[s] - P.id0;
-    if (ai.w > 0.0f && id >= 0 && id < P.nf) {
-      const float4 pi = te.pv[s];
-      const uint32_t K = te.cell[s];
-      const float* ls = a.lam_s;
-      const float4 l4 = reinterpret_cast<const float4*>(ls)[s];
-      const float lD = l4.x, lax = l4.y, lay = l4.z, lVx = l4.w, lVy = ls[4 * N + s];
-      const EosD<float> ei = eos_d<float>(ai.x, P.rho0, P.c0, P.gamma, P.p_cav, d_pow);
-      // the XSPH identity term V = v + ... enters once (lane 0)
-      float urx = 0, ury = 0, uvx = g == 0 ? lVx : 0.0f, uvy = g == 0 ? lVy : 0.0f, ur = 0, uP = 0, uc = 0,
-            uc0 = 0;
-      int cx, cy;
-      cxy(P, K, cx, cy);
-      const TRow r0 = trow(te, P, cx, cy, -1), r1 = trow(te, P, cx, cy, 0), r2 = trow(te, P, cx, cy, 1);
-      const TCount blk = tcount(r0, r1, r2);
-      // the in-support candidates go into a lane-private list in LDS (slot,
-      // cell shift); the pair terms run over the list, so a wave runs them as
-      // often as its longest list, not once per candidate position. Chunks of
-      // ADJ_LCAP candidates per lane keep every list within its room; the
-      // terms are summed in candidate order
-      uint32_t* my = s_hits + threadIdx.x;
-      const float4* ls4 = reinterpret_cast<const float4*>(ls);
-      for (uint32_t c0 = (uint32_t)g; c0 < blk.n; c0 += ADJ_FG * ADJ_LCAP) {
-        int cnt = 0;
-        const uint32_t c1 = min(blk.n, c0 + ADJ_FG * ADJ_LCAP);
-        // four candidates' positions in flight at once (past the chunk's
-        // end a lane reads its first candidate again and records nothing)
-        for (uint32_t cb = c0; cb < c1; cb += ADJ_FG * 4) {
-          uint32_t jq[4];
-          int dxq[4], dyq[4];
-          float2 pq[4];
+  double th[3] = {0.0, 0.0, 0.0};
+  double old = 0.0;
+  if (threadIdx.x < 3) old = a.theta_part[(size_t)(block0 + bid) * 3 + threadIdx.x];
+  // the slot's state in one round trip (the empty asm statement takes every
+  // loaded value; else the compiler defers what only fluid slots use)
+  const float* ls = a.lam_s;
+  const float4* ls4 = reinterpret_cast<const float4*>(ls);
+  const int sc = min(s, N - 1);
+  float4 ai = te.aux[sc], pi = te.pv[sc], l4 = ls4[sc];
+  float lVy = ls[4 * N + sc];
+  uint32_t K = te.cell[sc], idr = te.id[sc];
+  asm("" : "+v"(ai.x), "+v"(ai.y), "+v"(ai.z), "+v"(ai.w), "+v"(pi.x), "+v"(pi.y), "+v"(pi.z), "+v"(pi.w), "+v"(lVy),
+      "+v"(K), "+v"(idr));
+  const int id = (int)idr - P.id0;
+  if (s < N && ai.w > 0.0f && id >= 0 && id < P.nf) {
+    const float lD = l4.x, lax = l4.y, lay = l4.z, lVx = l4.w;
+    // the XSPH identity term V = v + ... enters once (lane 0)
+    float urx = 0, ury = 0, uvx = g == 0 ? lVx : 0.0f, uvy = g == 0 ? lVy : 0.0f, ur = 0, uP = 0, uc = 0, uc0 = 0;
+    int cx, cy;
+    cxy(P, K, cx, cy);
+    TRow r0, r1, r2;
+    trows(te, P, cx, cy, r0, r1, r2);
+    const EosD<float> ei = eos_d<float>(ai.x, P.rho0, P.c0, P.gamma, P.p_cav, d_pow);
+    const TCount blk = tcount(r0, r1, r2);
+    uint32_t* hl = s_hits[threadIdx.x / FG];
+    for (uint32_t c0 = (uint32_t)g; c0 - (uint32_t)g < blk.n; c0 += FG * ADJ_CH) {
+      // the lane tests candidates c0, c0 + FG, ... (past the end it reads its
+      // own slot and records nothing)
+      uint32_t M = 0u;
+#pragma unroll 1
+      for (int b = 0; b < ADJ_CH && c0 - (uint32_t)g + FG * b < blk.n; b += ADJ_FL) {
+        uint32_t jq[ADJ_FL];
+        int dxq[ADJ_FL], dyq[ADJ_FL];
+        float2 pq[ADJ_FL];
 #pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            const uint32_t c = cb + ADJ_FG * (uint32_t)u;
-            tcand(r0, r1, r2, blk, c < c1 ? c : c0, jq[u], dxq[u], dyq[u]);
-            const float4 pc = te.pv[jq[u]];
-            pq[u] = make_float2(pc.x, pc.y);
-          }
-          asm("" : "+v"(pq[0].x), "+v"(pq[0].y), "+v"(pq[1].x), "+v"(pq[1].y), "+v"(pq[2].x), "+v"(pq[2].y),
-              "+v"(pq[3].x), "+v"(pq[3].y));
-#pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            if (cb + ADJ_FG * (uint32_t)u >= c1) break;
-            const float rxc = (pi.x - pq[u].x) - (float)dxq[u] * P.dc;
-            const float ryc = (pi.y - pq[u].y) - (float)dyq[u] * P.dc;
-            const bool hit = jq[u] != (uint32_t)s && rxc * rxc + ryc * ryc < P.four_h2;
-            my[cnt * 256] = (jq[u] << 4) | ((uint32_t)(dyq[u] + 1) << 2) | (uint32_t)(dxq[u] + 1);
-            cnt += hit ? 1 : 0;
-          }
+        for (int u = 0; u < ADJ_FL; ++u) {
+          const uint32_t c = c0 + FG * (uint32_t)(b + u);
+          tcand(r0, r1, r2, blk, c, jq[u], dxq[u], dyq[u]);
+          if (c >= blk.n) jq[u] = (uint32_t)s;
+          pq[u] = *reinterpret_cast<const float2*>(te.pv + jq[u]);
         }
-        // the next hit's state is loaded while this one's terms are computed
-        // (an empty list loads the lane's own slot, always in range)
-        uint32_t cn = cnt > 0 ? my[0] : ((uint32_t)s << 4);
-        float4 pn = te.pv[cn >> 4], an = te.aux[cn >> 4], ln = ls4[cn >> 4];
-        float lyn = ls[4 * N + (cn >> 4)];
-        for (int kk = 0; kk < cnt; ++kk) {
-          const uint32_t code = cn;
-          const uint32_t j = code >> 4;
-          const int dx = (int)(code & 3u) - 1, dy = (int)((code >> 2) & 3u) - 1;
-          const float4 pj = pn, aj = an, lj = ln;
-          const float lyj = lyn;
-          cn = my[min(kk + 1, cnt - 1) * 256];
-          pn = te.pv[cn >> 4];
-          an = te.aux[cn >> 4];
-          ln = ls4[cn >> 4];
-          lyn = ls[4 * N + (cn >> 4)];
-          const float rx = (pi.x - pj.x) - (float)dx * P.dc;  // r_s - r_j
-          const float ry = (pi.y - pj.y) - (float)dy * P.dc;
-          const float r2 = rx * rx + ry * ry;
-          const bool jfl = aj.w > 0.0f;
-          // own rates: phi(s, j)
-          PairIn<float> in;
-          in.rx = rx; in.ry = ry; in.vx = pi.z - pj.z; in.vy = pi.w - pj.w;
-          in.ra = ai.x; in.rb = aj.x; in.Pa = ai.y; in.Pb = aj.y; in.ca = ai.z; in.cb = aj.z;
-          in.mb = fabsf(aj.w); in.fl = jfl ? 1.0f : 0.0f;
-          PairGrad<float> gg;
-          pair_vjp(in, k, lD, lax, lay, lVx, lVy, gg, d_sqrt, d_rcp);
-          urx += gg.rx; ury += gg.ry; uvx += gg.vx; uvy += gg.vy; ur += gg.ra; uP += gg.P; uc += gg.c;
-          th_a += (double)gg.alpha;
-          th_d += (double)gg.delta;
-          th_c += (double)gg.c0x;
-          if (jfl) {
-            // the neighbour's rates: phi(j, s), r = r_j - r_s
-            PairIn<float> jn;
-            jn.rx = -rx; jn.ry = -ry; jn.vx = pj.z - pi.z; jn.vy = pj.w - pi.w;
-            jn.ra = aj.x; jn.rb = ai.x; jn.Pa = aj.y; jn.Pb = ai.y; jn.ca = aj.z; jn.cb = ai.z;
-            jn.mb = ai.w; jn.fl = 1.0f;
-            PairGrad<float> h;
-            pair_vjp(jn, k, lj.x, lj.y, lj.z, lj.w, lyj, h, d_sqrt, d_rcp);
-            urx -= h.rx; ury -= h.ry; uvx -= h.vx; uvy -= h.vy; ur += h.rb; uP += h.P; uc += h.c;
-          } else {
-            // ghost j: this particle enters the ghost's Shepard sums
-            const float* gq = a.gadj + (size_t)j * 10;
-            const float SW = gq[3];
-            if (SW > 0.0f) {
-              const float pbar = gq[0], vbx = gq[1], vby = gq[2], pt = gq[4], vax = gq[5], vay = gq[6];
-              const float gx = gq[7], gy = gq[8];
-              const float ddx = -rx, ddy = -ry;  // d = r_g - r_s
-              const float q = sqrtf(r2) * P.inv_h, sq = 1.0f - 0.5f * q, s2 = sq * sq;
-              const float W = P.sigma * s2 * s2 * (2.0f * q + 1.0f);
-              const float F = -P.fgrad * s2 * sq;
-              const float ad_ = gx * ddx + gy * ddy;
-              const float iw = 1.0f / SW;
-              ur += pbar * (ei.dp + ad_) * W * iw;
-              const float cf = -(ei.p + ai.x * ad_ - pt) * F * iw;
-              const float vv = vbx * (pi.z - vax) + vby * (pi.w - vay);
-              urx += pbar * (cf * ddx - ai.x * W * iw * gx) + vv * F * ddx * iw;
-              ury += pbar * (cf * ddy - ai.x * W * iw * gy) + vv * F * ddy * iw;
-              uvx -= vbx * W * iw;
-              uvy -= vby * W * iw;
-              uc0 += pbar * ei.dpdc0 * W * iw;
-            }
-          }
+#pragma unroll
+        for (int u = 0; u < ADJ_FL; ++u) asm("" : "+v"(pq[u].x), "+v"(pq[u].y));
+#pragma unroll
+        for (int u = 0; u < ADJ_FL; ++u) {
+          const float rx = (pi.x - pq[u].x) - (float)dxq[u] * P.dc;
+          const float ry = (pi.y - pq[u].y) - (float)dyq[u] * P.dc;
+          M |= jq[u] != (uint32_t)s && rx * rx + ry * ry < P.four_h2 ? 1u << (b + u) : 0u;
         }
       }
-      if (probe_seed != 0.0f && g == 0) {
-        for (int kk = 0; kk < P.n_probes; ++kk) {
-          const float SW = a.padj[2 * kk];
-          if (!(SW > 0.0f)) continue;
-          int px, py;
-          cxy(P, P.probe_cell[kk], px, py);
-          if (abs(px - cx) > 1 || abs(py - cy) > 1) continue;
-          const float ddx = (P.probe_ox[kk] + (float)(px - cx) * P.dc) - pi.x;  // d = r_k - r_s
-          const float ddy = (P.probe_oy[kk] + (float)(py - cy) * P.dc) - pi.y;
-          const float r2 = ddx * ddx + ddy * ddy;
-          if (!(r2 < P.four_h2)) continue;
-          const float q = sqrtf(r2) * P.inv_h, sq = 1.0f - 0.5f * q, s2 = sq * sq;
-          const float W = P.sigma * s2 * s2 * (2.0f * q + 1.0f);
-          const float F = -P.fgrad * s2 * sq;
-          const float iw = probe_seed / SW;
-          ur += ei.dp * W * iw;
-          urx += -(ei.p - a.padj[2 * kk + 1]) * F * ddx * iw;
-          ury += -(ei.p - a.padj[2 * kk + 1]) * F * ddy * iw;
-          uc0 += ei.dpdc0 * W * iw;
-        }
+      // the chunk's hits into the slot's list, lane after lane
+      const uint32_t cnt = (uint32_t)__popc(M);
+      uint32_t incl = cnt;
+#pragma unroll
+      for (int o = 1; o < FG; o <<= 1) {
+        const uint32_t v = __shfl_up(incl, o, FG);
+        if (g >= o) incl += v;
       }
-      // fixed-order quad sums
-      urx = gsum<ADJ_FG>(urx);
-      ury = gsum<ADJ_FG>(ury);
-      uvx = gsum<ADJ_FG>(uvx);
-      uvy = gsum<ADJ_FG>(uvy);
-      ur = gsum<ADJ_FG>(ur);
-      uP = gsum<ADJ_FG>(uP);
-      uc = gsum<ADJ_FG>(uc);
-      uc0 = gsum<ADJ_FG>(uc0);
-      if (g == 0) {
-        // EOS chain: P(rho; c0), c(rho; c0)
-        ur += uP * ei.dPdr + uc * ei.dcdr;
-        uc0 += uP * ei.dPdc0 + uc * ei.dcdc0;
-        th_c += (double)uc0;
-        const int n = P.nf;
-        float* lb = a.lam_base;
-        if (accumulate) {
-          // the five loads before any store (as in the enforcement transpose)
-          const float b0 = lb[id], b1 = lb[n + id], b2 = lb[2 * n + id], b3 = lb[3 * n + id], b4 = lb[4 * n + id];
-          lb[id] = b0 + urx; lb[n + id] = b1 + ury; lb[2 * n + id] = b2 + uvx; lb[3 * n + id] = b3 + uvy;
-          lb[4 * n + id] = b4 + ur;
+      const int hn = (int)__shfl(incl, FG - 1, FG);
+      wave_sync();  // the previous chunk's list is no longer read
+      for (uint32_t* hp = hl + (incl - cnt); M; M &= M - 1u) {
+        uint32_t j;
+        int dx, dy;
+        tcand(r0, r1, r2, blk, c0 + FG * (uint32_t)__builtin_ctz(M), j, dx, dy);
+        *hp++ = (j << 4) | ((uint32_t)(dy + 1) << 2) | (uint32_t)(dx + 1);
+      }
+      wave_sync();
+      // lane g's share: hits g, g + FG, ...; the next hit's state is loaded
+      // while this one's terms are computed (an empty share loads the lane's
+      // own slot, always in range)
+      uint32_t cn = g < hn ? hl[g] : ((uint32_t)s << 4);
+      float4 pn = te.pv[cn >> 4], an = te.aux[cn >> 4], ln = ls4[cn >> 4];
+      float lyn = ls[4 * N + (cn >> 4)];
+      for (int kk = g; kk < hn; kk += FG) {
+        const uint32_t code = cn;
+        const uint32_t j = code >> 4;
+        const int dx = (int)(code & 3u) - 1, dy = (int)((code >> 2) & 3u) - 1;
+        const float4 pj = pn, aj = an, lj = ln;
+        const float lyj = lyn;
+        cn = kk + FG < hn ? hl[kk + FG] : code;
+        pn = te.pv[cn >> 4];
+        an = te.aux[cn >> 4];
+        ln = ls4[cn >> 4];
+        lyn = ls[4 * N + (cn >> 4)];
+        const float rx = (pi.x - pj.x) - (float)dx * P.dc;  // r_s - r_j
+        const float ry = (pi.y - pj.y) - (float)dy * P.dc;
+        const float r2 = rx * rx + ry * ry;
+        const bool jfl = aj.w > 0.0f;
+        // own rates: phi(s, j)
+        PairIn<float> in;
+        in.rx = rx; in.ry = ry; in.vx = pi.z - pj.z; in.vy = pi.w - pj.w;
+        in.ra = ai.x; in.rb = aj.x; in.Pa = ai.y; in.Pb = aj.y; in.ca = ai.z; in.cb = aj.z;
+        in.mb = fabsf(aj.w); in.fl = jfl ? 1.0f : 0.0f;
+        PairGrad<float> gg;
+        pair_vjp(in, k, lD, lax, lay, lVx, lVy, gg, d_sqrt, d_rcp);
+        urx += gg.rx; ury += gg.ry; uvx += gg.vx; uvy += gg.vy; ur += gg.ra; uP += gg.P; uc += gg.c;
+        th[0] += (double)gg.alpha;
+        th[1] += (double)gg.delta;
+        th[2] += (double)gg.c0x;
+        if (jfl) {
+          // the neighbour's rates: phi(j, s), r = r_j - r_s
+          PairIn<float> jn;
+          jn.rx = -rx; jn.ry = -ry; jn.vx = pj.z - pi.z; jn.vy = pj.w - pi.w;
+          jn.ra = aj.x; jn.rb = ai.x; jn.Pa = aj.y; jn.Pb = ai.y; jn.ca = aj.z; jn.cb = ai.z;
+          jn.mb = ai.w; jn.fl = 1.0f;
+          PairGrad<float> h;
+          pair_vjp(jn, k, lj.x, lj.y, lj.z, lj.w, lyj, h, d_sqrt, d_rcp);
+          urx -= h.rx; ury -= h.ry; uvx -= h.vx; uvy -= h.vy; ur += h.rb; uP += h.P; uc += h.c;
         } else {
-          lb[id] = urx; lb[n + id] = ury; lb[2 * n + id] = uvx; lb[3 * n + id] = uvy; lb[4 * n + id] = ur;
+          // ghost j: this particle enters the ghost's Shepard sums
+          const float4* gq = a.gadj + (size_t)j * 3;
+          const float4 g0 = gq[0], g1 = gq[1];
+          const float gy = gq[2].x;
+          const float SW = g0.w;
+          if (SW > 0.0f) {
+            const float pbar = g0.x, vbx = g0.y, vby = g0.z, pt = g1.x, vax = g1.y, vay = g1.z, gx = g1.w;
+            const float ddx = -rx, ddy = -ry;  // d = r_g - r_s
+            const float q = sqrtf(r2) * P.inv_h, sq = 1.0f - 0.5f * q, s2 = sq * sq;
+            const float W = P.sigma * s2 * s2 * (2.0f * q + 1.0f);
+            const float F = -P.fgrad * s2 * sq;
+            const float ad_ = gx * ddx + gy * ddy;
+            const float iw = 1.0f / SW;
+            ur += pbar * (ei.dp + ad_) * W * iw;
+            const float cf = -(ei.p + ai.x * ad_ - pt) * F * iw;
+            const float vv = vbx * (pi.z - vax) + vby * (pi.w - vay);
+            urx += pbar * (cf * ddx - ai.x * W * iw * gx) + vv * F * ddx * iw;
+            ury += pbar * (cf * ddy - ai.x * W * iw * gy) + vv * F * ddy * iw;
+            uvx -= vbx * W * iw;
+            uvy -= vby * W * iw;
+            uc0 += pbar * ei.dpdc0 * W * iw;
+          }
         }
       }
     }
+    if (probe_seed != 0.0f) {
+      const InstParams& Q = d.prm[0];  // (indexed per lane)
+      for (int kk = g; kk < P.n_probes; kk += FG) {
+        const float SW = a.padj[2 * kk], pk = a.padj[2 * kk + 1];
+        int px, py;
+        cxy(P, Q.probe_cell[kk], px, py);
+        const float ddx = (Q.probe_ox[kk] + (float)(px - cx) * P.dc) - pi.x;  // d = r_k - r_s
+        const float ddy = (Q.probe_oy[kk] + (float)(py - cy) * P.dc) - pi.y;
+        const float r2 = ddx * ddx + ddy * ddy;
+        if (!(SW > 0.0f) || abs(px - cx) > 1 || abs(py - cy) > 1 || !(r2 < P.four_h2)) continue;
+        const float q = sqrtf(r2) * P.inv_h, sq = 1.0f - 0.5f * q, s2 = sq * sq;
+        const float W = P.sigma * s2 * s2 * (2.0f * q + 1.0f);
+        const float F = -P.fgrad * s2 * sq;
+        const float iw = probe_seed / SW;
+        ur += ei.dp * W * iw;
+        urx += -(ei.p - pk) * F * ddx * iw;
+        ury += -(ei.p - pk) * F * ddy * iw;
+        uc0 += ei.dpdc0 * W * iw;
+      }
+    }
+    // fixed-order sums of the group
+    urx = gsum<FG>(urx);
+    ury = gsum<FG>(ury);
+    uvx = gsum<FG>(uvx);
+    uvy = gsum<FG>(uvy);
+    ur = gsum<FG>(ur);
+    uP = gsum<FG>(uP);
+    uc = gsum<FG>(uc);
+    uc0 = gsum<FG>(uc0);
+    if (g == 0) {
+      // EOS chain: P(rho; c0), c(rho; c0)
+      ur += uP * ei.dPdr + uc * ei.dcdr;
+      uc0 += uP * ei.dPdc0 + uc * ei.dcdc0;
+      th[2] += (double)uc0;
+      const int n = P.nf;
+      float* lb = a.lam_base;
+      if (accumulate) {
+        // the five loads before any store (as in the enforcement transpose)
+        const float b0 = lb[id], b1 = lb[n + id], b2 = lb[2 * n + id], b3 = lb[3 * n + id], b4 = lb[4 * n + id];
+        lb[id] = b0 + urx; lb[n + id] = b1 + ury; lb[2 * n + id] = b2 + uvx; lb[3 * n + id] = b3 + uvy;
+        lb[4 * n + id] = b4 + ur;
+      } else {
+        lb[id] = urx; lb[n + id] = ury; lb[2 * n + id] = uvx; lb[3 * n + id] = uvy; lb[4 * n + id] = ur;
+      }
+    }
   }
-  const double ta = block_sum(th_a, shd), td = block_sum(th_d, shd), tc = block_sum(th_c, shd);
-  if (threadIdx.x == 0) {
-    double* o = a.theta_part + (size_t)(block0 + blockIdx.x) * 3;
-    o[0] += ta;
-    o[1] += td;
-    o[2] += tc;
-  }
+  block_add(th, a.theta_part + (size_t)(block0 + bid) * 3, old);
 }
 
 // theta += sum of the per-block running sums (FP64, fixed order: lane l

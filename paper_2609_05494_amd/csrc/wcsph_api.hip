@@ -1957,7 +1957,7 @@ wcsph_status wcsph_adj_backward(wcsph_ctx* ctx, double dJ, double* grad) {
     A.L1 = dalloc_n<float>(ctx, (size_t)5 * nf);
     A.Ls = dalloc_n<float>(ctx, (size_t)5 * nf);
     A.a.lam_s = dalloc_n<float>(ctx, (size_t)5 * ctx->n_slots);
-    A.a.gadj = dalloc_n<float>(ctx, (size_t)10 * ctx->n_slots);
+    A.a.gadj = dalloc_n<float4>(ctx, (size_t)3 * ctx->n_slots);
     A.a.padj = dalloc_n<float>(ctx, 2 * WC_MAX_PROBES);
     A.a.n_ghost_probe = q.nw + q.nd + q.n_probes;
     A.nblk = wc_adj_partial_blocks(A.a.n_ghost_probe, ctx->n_slots);

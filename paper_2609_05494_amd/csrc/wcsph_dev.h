@@ -222,7 +222,7 @@ struct AdjPtrs {
   float* lam_out;      // [5][nf] adjoint of the evaluation's output state (x, y, vx, vy, rho)
   float* lam_base;     // [5][nf] adjoint of the base / evaluated state
   float* lam_s;        // rate adjoints in sorted slot order: float4 (D, ax, ay, Vx) [n_slots], then Vy [n_slots]
-  float* gadj;         // [n_slots][10] ghost adjoint and Shepard data
+  float4* gadj;        // [n_slots][3] ghost adjoint and Shepard data (see k_adj_ghost)
   float* padj;         // [16][2] probe Shepard sums
   double2* pre_pos;    // taped pre-enforcement state of the evaluation
   float4* pre_vel;

@@ -24,6 +24,7 @@
 
 #include "wcsph_launch.h"
 #include "wcsph_kin.h"
+#include "wcsph_wave.h"
 
 // Shapes of the pair pass (UCAP, LCAP, RU) picked for this GPU by the
 // autotuner (paper_2609_05494_amd/autotune.py), when it has been run; the
@@ -39,14 +40,6 @@ template <bool BATCH>
 __device__ __forceinline__ int inst_at(const Buf& b, int s) {
   if constexpr (BATCH) return (int)b.inst[s];
   else return 0;
-}
-
-// Spread consecutive blocks over the 8 XCDs in contiguous chunks: hardware
-// dispatches block b to XCD b % 8, so logical chunk x (one L2) is served by
-// the blocks with b % 8 == x.
-__device__ __forceinline__ int xcd_block(int bid, int nblk) {
-  const int q = nblk >> 3, r = nblk & 7, x = bid & 7;
-  return x * q + min(x, r) + (bid >> 3);
 }
 
 __device__ __forceinline__ float fast_rcp(float x) { return __builtin_amdgcn_rcpf(x); }
@@ -455,23 +448,6 @@ struct PairC {
   float kc_sigma, kc_a, q_r2;
   int ncx, ncy, cell_off, cx_bits;
 };
-// (The parameter blocks do not change while a kernel runs: read through the
-// constant address space, a block that is the same on every lane comes
-// through the scalar cache wherever it is read.)
-typedef const __attribute__((address_space(4))) InstParams ConstParams;
-// A copy of a block that no one writes meanwhile (of the fields that are
-// used, when it is inlined), read through the constant address space.
-template <class T>
-__device__ __forceinline__ T scalar_copy(const T* p) {
-  static_assert(sizeof(T) % 8 == 0, "whole words");
-  typedef const __attribute__((address_space(4))) unsigned long long Word;
-  unsigned long long w[sizeof(T) / 8];
-#pragma unroll
-  for (int k = 0; k < (int)(sizeof(T) / 8); ++k) w[k] = ((Word*)p)[k];
-  T t;
-  __builtin_memcpy(&t, w, sizeof t);
-  return t;
-}
 // This lane's share of the ghosts' max |v| of the step, where they are in the
 // sort's launch (a wave reads all).
 __device__ __forceinline__ float ghost_vmax(const Dev& d) {
@@ -531,15 +507,6 @@ static_assert(UCAP == 128 && HCAP >= UCAP / 2 && HCAP <= 255, "one support test 
 #define QCOLS 8  // columns of a group: test coordinates stay below 2^11, every term and sum of the test below 2^24
 #define QORG 3   // origin column of the test coordinates (from the group's first)
 static_assert(PAIR_G == 4 && QN == 256, "test layout and exactness of the test terms");
-
-// Order the wave's LDS accesses: stores before this point are seen by every
-// lane's loads after it (accesses of one wave are performed in order; the
-// fences keep the compiler from moving them across).
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 // Every load of the wave is complete, those straight into LDS too (the
 // compiler's own barriers and fences need not wait for them): vmcnt(0).
