@@ -513,11 +513,15 @@ bool pin_invalid(wcsph_ctx* c) { return clocks_invalid(c, pin_clocks(c)[0], pin_
 // Refill the buckets of the next sort from the state in X (after the state,
 // the clocks or the disk law changed from the host).
 void arm_counts(wcsph_ctx* c) { wc_enqueue_arm(c->d, c->st); }
-void rearm(wcsph_ctx* c) {
-  arm_counts(c);
+// The buckets of the next sort from the state in X (counters armed before).
+void refill(wcsph_ctx* c) {
   wc_enqueue_init(c->d, c->b, c->batch, c->st);
   HC(hipGetLastError());
   c->lf_set = 0;  // bucket set a now holds the next sort's entries
+}
+void rearm(wcsph_ctx* c) {
+  arm_counts(c);
+  refill(c);
 }
 
 // Write the set-up (or a given fluid state for instance 0) into X in id
@@ -1064,18 +1068,25 @@ size_t ckpt_size(const wcsph_ctx* c) {
 void ckpt_copy(wcsph_ctx* c, char* blob, bool save) {
   const size_t N = c->n_slots;
   size_t off = 0;
-  auto mv = [&](void* dev, size_t bytes) {
-    if (save) HC(hipMemcpyAsync(blob + off, dev, bytes, hipMemcpyDeviceToDevice, c->st));
-    else HC(hipMemcpyAsync(dev, blob + off, bytes, hipMemcpyDeviceToDevice, c->st));
+  auto at = [&](size_t bytes) {
+    char* p = blob + off;
     off += (bytes + 15) & ~size_t(15);
+    return p;
   };
-  mv(c->b.X.cell, N * 4);
-  mv(c->b.X.id, N * 4);
-  mv(c->b.X.pv, N * 16);
-  mv(c->b.X.aux, N * 16);
-  mv(c->d_clk, c->n_inst * sizeof(Clock));
-  mv(c->d.gslot, (size_t)c->n_ghost * 4);
-  if (!save) rearm(c);
+  StatePack p{};
+  p.cell = reinterpret_cast<const uint32_t*>(at(N * 4));
+  p.id = reinterpret_cast<const uint32_t*>(at(N * 4));
+  p.pv = reinterpret_cast<const float4*>(at(N * 16));
+  p.aux = reinterpret_cast<const float4*>(at(N * 16));
+  p.clk = reinterpret_cast<const Clock*>(at(c->n_inst * sizeof(Clock)));
+  p.gslot = reinterpret_cast<const uint32_t*>(at((size_t)c->n_ghost * 4));
+  if (save) {
+    wc_enqueue_save_state(c->d, c->b, p, c->st);
+    HC(hipGetLastError());
+  } else {
+    wc_enqueue_load_state(c->d, c->b, p, c->st);  // (arms the sort counters too)
+    refill(c);
+  }
 }
 
 // The tape of steps [tape_steps, steps): one device block for all of them,
@@ -1633,9 +1644,7 @@ wcsph_status wcsph_load_state(wcsph_ctx* ctx, const void* buf, size_t n) {
     p.n_audit = (int)(len[7] / sizeof(double));
     p.e = reinterpret_cast<const float*>(at[8]);
     wc_enqueue_load_state(ctx->d, ctx->b, p, ctx->st);
-    wc_enqueue_init(ctx->d, ctx->b, ctx->batch, ctx->st);
-    HC(hipGetLastError());
-    ctx->lf_set = 0;
+    refill(ctx);
   } else {
     void* const dev[9] = {ctx->d_clk, ctx->b.X.cell, ctx->b.X.id, ctx->b.X.pv, ctx->b.X.aux, ctx->b.X.inst,
                           ctx->d.gslot, ctx->d.audit_part, ctx->b.X.e};

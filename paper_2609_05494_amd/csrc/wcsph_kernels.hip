@@ -2599,6 +2599,22 @@ __global__ __launch_bounds__(WC_BLOCK) void k_load_state(Dev d, Buf X, StatePack
   arm_a(d, u);
 }
 
+// The reverse, for checkpoints that stay on the device (a copy per array took
+// 4 to 5 us each, six of them a checkpoint).
+__global__ __launch_bounds__(WC_BLOCK) void k_save_state(Dev d, Buf X, StatePack b) {
+  const int u = blockIdx.x * WC_BLOCK + threadIdx.x;
+  if (u < d.n_slots) {
+    const_cast<uint32_t*>(b.cell)[u] = X.cell[u];
+    const_cast<uint32_t*>(b.id)[u] = X.id[u];
+    const_cast<float4*>(b.pv)[u] = X.pv[u];
+    const_cast<float4*>(b.aux)[u] = X.aux[u];
+  }
+  if (u < d.n_ghost) const_cast<uint32_t*>(b.gslot)[u] = d.gslot[u];
+  if (u < d.n_inst * (int)(sizeof(Clock) / 8))
+    reinterpret_cast<unsigned long long*>(const_cast<Clock*>(b.clk))[u] =
+        reinterpret_cast<const unsigned long long*>(d.clk)[u];
+}
+
 // What the host reads of a context, packed by one launch so that a read costs
 // one wait and not a blocking copy per field (about 15 us each). `clk`: the
 // clocks of instance i and of instance 0 (the validity flags), written by the
@@ -2856,6 +2872,11 @@ void wc_enqueue_load_state(const Dev& d, const Bufs& b, const StatePack& p, hipS
   const int n = std::max(std::max(std::max(d.n_slots, d.n_cells), std::max(d.n_ghost, p.n_audit)),
                          d.n_inst * (int)(sizeof(Clock) / 8));
   k_load_state<<<NB(n), WC_BLOCK, 0, st>>>(d, b.X, p);
+}
+
+void wc_enqueue_save_state(const Dev& d, const Bufs& b, const StatePack& p, hipStream_t st) {
+  const int n = std::max(std::max(d.n_slots, d.n_ghost), d.n_inst * (int)(sizeof(Clock) / 8));
+  k_save_state<<<NB(n), WC_BLOCK, 0, st>>>(d, b.X, p);
 }
 
 static_assert(2 * (sizeof(Clock) / 8) <= WC_BLOCK && sizeof(Clock) % 8 == 0, "clocks of a read");

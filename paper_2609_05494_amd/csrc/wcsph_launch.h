@@ -44,6 +44,8 @@ struct StatePack {
   int n_audit;
 };
 void wc_enqueue_load_state(const Dev& d, const Bufs& b, const StatePack& p, hipStream_t st);
+// The reverse: the state's arrays into the pack's places (no audit sums).
+void wc_enqueue_save_state(const Dev& d, const Bufs& b, const StatePack& p, hipStream_t st);
 // Reads of the host, packed on the device; clk: the clocks of instance i and
 // of instance 0 (host memory the GPU can write).
 // Fluid state of instance i in id order, FP64: x, y, vx, vy, rho (device).
