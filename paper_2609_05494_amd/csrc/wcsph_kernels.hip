@@ -1374,8 +1374,8 @@ __device__ __forceinline__ uint32_t ghost_slot(const Dev& d, const uint32_t* buc
 #pragma unroll
   for (int k = 0; k < SORT_SPEC; ++k) {
     const bool in = (uint32_t)(sub + 4 * k) < n;
-    before += in & (b[k] < e) ? 1u : 0u;
-    found |= in & (b[k] == e) ? 1u : 0u;
+    before += (in & (b[k] < e)) ? 1u : 0u;
+    found |= (in & (b[k] == e)) ? 1u : 0u;
   }
   for (uint32_t i = sub + 4 * SORT_SPEC; i < n; i += 4) {
     const uint32_t x = bucket[(size_t)K * WC_BUCKET + i];
@@ -1788,26 +1788,31 @@ __global__ __launch_bounds__(WC_GHOST_BLOCK) void k_ghost(Dev d, Buf sb) {
   // instance's ghost arrays with it: left to itself the compiler loads each
   // field where it is first used, one after the other
   int4 blk = d.gblk[blockIdx.x];
-  int gm = BATCH ? 0 : d.prm[0].gmap0;
   const uint32_t *gslot = d.gslot, *gcell = d.gcell;
   const float2* gpos = d.gpos;
-  asm("" : "+s"(blk.x), "+s"(blk.y), "+s"(blk.z), "+s"(blk.w), "+s"(gm), "+s"(gslot), "+s"(gcell), "+s"(gpos));
+  asm("" : "+s"(blk.x), "+s"(blk.y), "+s"(blk.z), "+s"(blk.w), "+s"(gslot), "+s"(gcell), "+s"(gpos));
   const int inst = BATCH ? blk.x : 0, kind = blk.w;
-  const InstParams& P = d.prm[inst];
-  if constexpr (BATCH) gm = P.gmap0;
-  Clock& C = d.clk[inst];
+  // the block's items are of one instance: its constants and clock through the
+  // scalar cache (no block writes what is read of the clock here but v_max);
+  // as vector loads each waited where it was first used: 7.4 and 5.6 us a
+  // launch at 179,552 particles, 6.5 and 4.9 so
+  const InstParams P = scalar_copy(d.prm + inst);
+  const Clock C = scalar_copy(d.clk + inst);
+  uint32_t* vmax = &d.clk[inst].vmax_bits;
+  const int gm = P.gmap0;
   const int t = threadIdx.x, item = t / GL, lane = t % GL;
   const bool act = item < blk.z;
   // first evaluation: the stored v_max (the fluid part is already in) read
   // now, so that its latency is hidden; a wave whose ghost maximum is not
   // above it skips the atomic
   constexpr bool FIRST = MODE == EV_A || MODE == EV_L;  // the step's first (or only) evaluation
-  const uint32_t vcheck = FIRST && kind != 2 ? __atomic_load_n(&C.vmax_bits, __ATOMIC_RELAXED) : 0u;
+  const uint32_t vcheck = FIRST && kind != 2 ? __atomic_load_n(vmax, __ATOMIC_RELAXED) : 0u;
   if (kind == 2) {
     // probes: Shepard average of the fluid pressure at fixed wall points
     if (FIRST && act) {
       const int k = blk.y + item;
-      const Shep S = shepard<GL, CUB>(d, P, sb, P.probe_cell[k], P.probe_ox[k], P.probe_oy[k], lane);
+      const InstParams& Q = d.prm[inst];  // (indexed per item)
+      const Shep S = shepard<GL, CUB>(d, P, sb, Q.probe_cell[k], Q.probe_ox[k], Q.probe_oy[k], lane);
       if (lane == 0) {
         const long long row = (long long)inst * WC_HIST_CAP + (C.step % WC_HIST_CAP);
         d.hist_p[row * WC_MAX_PROBES + k] = S.W > 0.0f ? S.p / S.W : 0.0f;
@@ -1867,7 +1872,7 @@ __global__ __launch_bounds__(WC_GHOST_BLOCK) void k_ghost(Dev d, Buf sb) {
   if (FIRST) {
     // the items of a block belong to one instance
     const float w = wave_max(vmag);
-    if ((t & 63) == 0 && w > 0.0f && __float_as_uint(w) > vcheck) atomicMax(&C.vmax_bits, __float_as_uint(w));
+    if ((t & 63) == 0 && w > 0.0f && __float_as_uint(w) > vcheck) atomicMax(vmax, __float_as_uint(w));
   }
 }
 #undef GL
@@ -2358,26 +2363,27 @@ __global__ __launch_bounds__(PAIR_BLOCK) void k_dens(Dev d, Buf sb, int count) {
 // velocity at t times dt, a fixed-order sum) and the new state's time.
 __global__ __launch_bounds__(64) void k_clock_lf(Dev d) {
   const int i = blockIdx.x;
-  const InstParams& P = d.prm[i];
+  const InstParams P = scalar_copy(d.prm + i);
+  const Clock O = scalar_copy(d.clk + i);  // as the ghost pass left it
   Clock& C = d.clk[i];
   double f = 0.0;
   for (int k = (int)threadIdx.x; k < P.nd; k += 64) f += d.wb_part[i * WC_MAX_RING + k];
   f = wave_sum(f);
   if (threadIdx.x != 0) return;
-  const double dt = step_dt(d, P, C);
-  C.dt_prev = C.dt;
+  const double dt = step_dt(d, P, O);
+  C.dt_prev = O.dt;
   C.dt = dt;
-  C.vmax_used = (double)__uint_as_float(C.vmax_bits);
+  C.vmax_used = (double)__uint_as_float(O.vmax_bits);
   C.vmax_bits = 0u;
-  const long long row = (long long)i * WC_HIST_CAP + (C.step % WC_HIST_CAP);
-  d.hist_t[row] = C.t;
+  const long long row = (long long)i * WC_HIST_CAP + (O.step % WC_HIST_CAP);
+  d.hist_t[row] = O.t;
   d.hist_dt[row] = dt;
   double xn, vn, an;
-  kinematics(P, C.t + dt, xn, vn, an);
+  kinematics(P, O.t + dt, xn, vn, an);
   C.xd_next = xn;
   C.vd_next = vn;
-  C.w_boundary += dt * f * C.vd;
-  C.t_next = C.t + dt;
+  C.w_boundary = O.w_boundary + dt * f * O.vd;
+  C.t_next = O.t + dt;
 }
 
 // Two-way coupled disk (kin_mode 2), one wave per instance between the
