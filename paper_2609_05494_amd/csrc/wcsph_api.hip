@@ -141,6 +141,7 @@ struct wcsph_ctx {
   std::vector<int4> h_gblk, h_sblk;
   std::vector<uint32_t> h_witem, h_wcell, h_wplace;
   std::vector<float2> h_wpos;
+  std::vector<char> h_gtab;
   hipGraph_t graph = nullptr;       // one step
   hipGraphExec_t gexec = nullptr;
   hipGraph_t graph_k = nullptr;     // steps_k steps and a diagnostic record
@@ -820,32 +821,42 @@ void build(wcsph_ctx* c, const wcsph_params* params, int n_inst) {
   uint32_t* wrank = dalloc_n<uint32_t>(c, c->n_ghost);
   d.wrank = wrank;
   if (d.merged) {
-    int4* sblk = dalloc_n<int4>(c, c->n_sblk);
-    uint32_t *witem = dalloc_n<uint32_t>(c, c->n_ghost), *wcell = dalloc_n<uint32_t>(c, c->n_ghost);
-    uint32_t* wplace = dalloc_n<uint32_t>(c, c->n_ghost);
-    d.wplace = wplace;
-    float2* wpos = dalloc_n<float2>(c, c->n_ghost);
-    d.sblk = sblk;
-    d.witem = witem;
-    d.wcell = wcell;
-    d.wpos = wpos;
-    HC(hipMemcpyAsync(sblk, c->h_sblk.data(), c->h_sblk.size() * sizeof(int4), hipMemcpyHostToDevice, c->st));
-    HC(hipMemcpyAsync(witem, c->h_witem.data(), c->h_witem.size() * 4, hipMemcpyHostToDevice, c->st));
-    HC(hipMemcpyAsync(wcell, c->h_wcell.data(), c->h_wcell.size() * 4, hipMemcpyHostToDevice, c->st));
-    HC(hipMemcpyAsync(wplace, c->h_wplace.data(), c->h_wplace.size() * 4, hipMemcpyHostToDevice, c->st));
-    HC(hipMemcpyAsync(wpos, c->h_wpos.data(), c->h_wpos.size() * 8, hipMemcpyHostToDevice, c->st));
-    d.rcell_a = dalloc_n<uint32_t>(c, WC_MAX_RING);
-    d.rcell_b = dalloc_n<uint32_t>(c, WC_MAX_RING);
-    d.rslot_a = dalloc_n<uint32_t>(c, WC_MAX_RING);
-    d.rslot_b = dalloc_n<uint32_t>(c, WC_MAX_RING);
-    d.rpos_a = dalloc_n<float2>(c, WC_MAX_RING);
-    d.rpos_b = dalloc_n<float2>(c, WC_MAX_RING);
-    d.deval_a = dalloc_n<DiskEval>(c, 1);
-    d.deval_b = dalloc_n<DiskEval>(c, 1);
+    // the tables and the work arrays of the ghosts in the sort's launch, as one
+    // block and one copy (a context's allocations and copies are what its
+    // creation waits for)
+    std::vector<char>& h = c->h_gtab;  // (kept until the copies are done)
+    auto place = [&](const void* src, size_t bytes) {
+      const size_t at = h.size();
+      h.resize(at + ((bytes + 63) & ~size_t(63)), 0);
+      if (src && bytes) std::memcpy(h.data() + at, src, bytes);
+      return at;
+    };
+    const size_t R = WC_MAX_RING;
+    const size_t o_sblk = place(c->h_sblk.data(), c->h_sblk.size() * sizeof(int4)),
+                 o_item = place(c->h_witem.data(), c->h_witem.size() * 4),
+                 o_cell = place(c->h_wcell.data(), c->h_wcell.size() * 4),
+                 o_place = place(c->h_wplace.data(), c->h_wplace.size() * 4),
+                 o_pos = place(c->h_wpos.data(), c->h_wpos.size() * 8), o_rcell = place(nullptr, 2 * R * 4),
+                 o_rslot = place(nullptr, 2 * R * 4), o_rpos = place(nullptr, 2 * R * 8),
+                 o_eval = place(nullptr, 2 * sizeof(DiskEval)), o_vmax = place(nullptr, (c->n_sblk + 1) * 4);
+    char* p = dalloc_n<char>(c, h.size());
+    d.sblk = reinterpret_cast<int4*>(p + o_sblk);
+    d.witem = reinterpret_cast<uint32_t*>(p + o_item);
+    d.wcell = reinterpret_cast<uint32_t*>(p + o_cell);
+    d.wplace = reinterpret_cast<uint32_t*>(p + o_place);
+    d.wpos = reinterpret_cast<float2*>(p + o_pos);
+    d.rcell_a = reinterpret_cast<uint32_t*>(p + o_rcell);
+    d.rcell_b = d.rcell_a + R;
+    d.rslot_a = reinterpret_cast<uint32_t*>(p + o_rslot);
+    d.rslot_b = d.rslot_a + R;
+    d.rpos_a = reinterpret_cast<float2*>(p + o_rpos);
+    d.rpos_b = d.rpos_a + R;
+    d.deval_a = reinterpret_cast<DiskEval*>(p + o_eval);
+    d.deval_b = d.deval_a + 1;
     d.n_sblk = c->n_sblk;
-    d.gvmax = dalloc_n<float>(c, c->n_sblk + 1);
-    d.gvstep = (uint32_t*)(d.gvmax + c->n_sblk);
-    HC(hipMemsetAsync(d.gvmax, 0, (size_t)(c->n_sblk + 1) * 4, c->st));
+    d.gvmax = reinterpret_cast<float*>(p + o_vmax);
+    d.gvstep = reinterpret_cast<uint32_t*>(d.gvmax + c->n_sblk);
+    HC(hipMemcpyAsync(p, h.data(), h.size(), hipMemcpyHostToDevice, c->st));
   }
   int4* gblk = dalloc_n<int4>(c, c->n_gblk);
   d.gblk = gblk;
