@@ -1794,8 +1794,8 @@ __global__ __launch_bounds__(WC_GHOST_BLOCK) void k_ghost(Dev d, Buf sb) {
   const int inst = BATCH ? blk.x : 0, kind = blk.w;
   // the block's items are of one instance: its constants and clock through the
   // scalar cache (no block writes what is read of the clock here but v_max);
-  // as vector loads each waited where it was first used: 7.4 and 5.6 us a
-  // launch at 179,552 particles, 6.5 and 4.9 so
+  // as vector loads each waited where it was first used (corrector 7.3
+  // -> 6.4 us a launch at 179,552 particles, 8.3 -> 7.1 at 719,552)
   const InstParams P = scalar_copy(d.prm + inst);
   const Clock C = scalar_copy(d.clk + inst);
   uint32_t* vmax = &d.clk[inst].vmax_bits;
@@ -1952,6 +1952,11 @@ template <int MODE, bool BATCH, bool AUD, int VAR>
 __global__ __launch_bounds__(PAIR_BLOCK, (AUD || MODE == EV_EXPORT) ? 1 : PAIR_MINW)
 void k_pair(Dev d, Buf sb, Buf base, Buf out) {
   constexpr bool MRG = (VAR & 16) != 0;  // the ghosts are in the sorts' launches
+  // the corrector's state n is gathered before the pair sums where the chip is
+  // not full (pair B 10.4 -> 10.0 us at 3,148 particles, 12.2 -> 11.8 at
+  // 28,352), after them where its registers would cost more than its latency
+  // (72.0 -> 73.2 us at 719,552)
+  constexpr bool PRE = MRG && MODE == EV_B;
   float vg = 0.0f;  // this lane's share of the ghosts' max |v| (second phase)
   // the first phase's LDS, and in its place after a barrier the hand-over of
   // each slot from the first phase to the second
@@ -1962,6 +1967,10 @@ void k_pair(Dev d, Buf sb, Buf base, Buf out) {
     float aud[AUD ? 4 : 1][PAIR_SLOTS];
     int inst[PAIR_SLOTS];
     uint32_t eb[PAIR_SLOTS];
+    // (PRE) state n of the slot's particle
+    float4 pb[PRE ? PAIR_SLOTS : 1];
+    float rb[PRE ? PAIR_SLOTS : 1];
+    uint32_t Kb[PRE ? PAIR_SLOTS : 1];
   };
   union Shared {
     PairLds uni[PAIR_BLOCK / 64];
@@ -2002,6 +2011,15 @@ void k_pair(Dev d, Buf sb, Buf base, Buf out) {
     if constexpr (!BATCH) {
       G0 = pair_c(d.prm);
     }
+    float4 pb0 = make_float4(0, 0, 0, 0);
+    float rb0 = 0.0f;
+    uint32_t Kb0 = 0u;
+    if (PRE && q == 0) {
+      eb = min(eb, (uint32_t)d.n_slots - 1u);
+      pb0 = at32(base.pv, eb);
+      rb0 = at32(base.aux, eb).x;
+      Kb0 = at32(base.cell, eb);
+    }
     if (MODE == EV_EXPORT && d.nb_ids != nullptr)
       pair_sums_wave<BATCH, AUD, VAR, true>(d, sb, G0, s0, inst, fluid, pi, ai, sh.uni[threadIdx.x >> 6], sS, acc, aud);
     else
@@ -2025,6 +2043,11 @@ void k_pair(Dev d, Buf sb, Buf base, Buf out) {
       sh.ho.m[k] = inr ? ai.w : 0.0f;
       sh.ho.inst[k] = inst;
       sh.ho.eb[k] = eb;
+      if constexpr (PRE) {
+        sh.ho.pb[k] = pb0;
+        sh.ho.rb[k] = rb0;
+        sh.ho.Kb[k] = Kb0;
+      }
     }
     if constexpr (AUD) {
       aud.av = slot_sum(aud.av);
@@ -2135,10 +2158,17 @@ void k_pair(Dev d, Buf sb, Buf base, Buf out) {
     } else {
       // state n of this particle: the sort of this evaluation took it from
       // slot perm[s] of the step's first sorted state
-      const uint32_t eb = sh.ho.eb[threadIdx.x];
-      const uint32_t Kb = at32(base.cell, eb);
-      pb = at32(base.pv, eb);
-      rb = at32(base.aux, eb).x;
+      uint32_t Kb;
+      if constexpr (PRE) {
+        Kb = sh.ho.Kb[threadIdx.x];
+        pb = sh.ho.pb[threadIdx.x];
+        rb = sh.ho.rb[threadIdx.x];
+      } else {
+        const uint32_t eb = sh.ho.eb[threadIdx.x];
+        Kb = at32(base.cell, eb);
+        pb = at32(base.pv, eb);
+        rb = at32(base.aux, eb).x;
+      }
       cell_xy(P, Kb, cx, cy);
     }
     float rn, rn_free, vx, vy, ox, oy, e_new = 0.0f;
