@@ -2391,11 +2391,13 @@ __global__ __launch_bounds__(PAIR_BLOCK) void k_dens(Dev d, Buf sb, int count) {
 // (t, dt), the disk at t + dt for the enforcement and the ring of the next
 // step, the ring's work over the step (its x force at t times the disk
 // velocity at t times dt, a fixed-order sum) and the new state's time.
+// (The constants come through the scalar cache; the clock does not, since it is
+// written here: ordinary loads, all issued before the first store.)
 __global__ __launch_bounds__(64) void k_clock_lf(Dev d) {
   const int i = blockIdx.x;
   const InstParams P = scalar_copy(d.prm + i);
-  const Clock O = scalar_copy(d.clk + i);  // as the ghost pass left it
   Clock& C = d.clk[i];
+  const Clock O = C;  // as the ghost pass left it
   double f = 0.0;
   for (int k = (int)threadIdx.x; k < P.nd; k += 64) f += d.wb_part[i * WC_MAX_RING + k];
   f = wave_sum(f);
