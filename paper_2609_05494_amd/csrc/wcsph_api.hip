@@ -588,8 +588,7 @@ void upload_state(wcsph_ctx* c, double t0, const double* fx, const double* fy, c
   HC(hipMemcpyAsync(c->d_clk, clk.data(), clk.size() * sizeof(Clock), hipMemcpyHostToDevice, c->st));
   if (c->d.audit_part)
     HC(hipMemsetAsync(c->d.audit_part, 0, (size_t)c->d.n_vpart * 6 * sizeof(double), c->st));
-  wc_enqueue_init(c->d, c->b, c->batch, c->st);
-  HC(hipGetLastError());
+  refill(c);
   c->steps = 0;
   for (int i = 0; i < c->n_inst; ++i) {
     c->hist_read[i] = 0;
