@@ -592,6 +592,14 @@ __device__ __forceinline__ uint32_t lane_id() {
   asm volatile("" : "+v"(l));
   return l;
 }
+// r_ij of a particle in column cxi of the group and a staged entry (offsets'
+// difference, then whole cells); returns r^2.
+__device__ __forceinline__ float hit_rel(float dc, float cxi, const float4& pi, const float4& pj, __half2 cj, float& rx,
+                                         float& ry) {
+  rx = fmaf(cxi - __low2float(cj), dc, pi.x - pj.x);
+  ry = fmaf(-__high2float(cj), dc, pi.y - pj.y);
+  return fmaf(rx, rx, ry * ry);
+}
 template <bool BATCH, bool AUD, int VAR, bool EXP = false>
 __device__ __forceinline__ void pair_sums_wave(const Dev& d, const Buf& sb, const PairC& G0, int s0, int inst,
                                                bool fluid, const float4& pi, const float4& ai, PairLds& U,
@@ -744,40 +752,41 @@ __device__ __forceinline__ void pair_sums_wave(const Dev& d, const Buf& sb, cons
       if (k < hn) {
         const uint8_t* hl = U.hit + (pl / PAIR_G) * HCAP;
         // two entries in flight (buffers a, b)
-        auto fetch = [&](uint32_t kk, float4& pj, float4& aj, __half2& cj, uint32_t& t) __attribute__((always_inline)) {
-          t = hl[min(kk, hn - 1u)];
+        auto fetch = [&](uint32_t kk, float4& pj, float4& aj, __half2& cj) __attribute__((always_inline)) {
+          const uint32_t t = hl[min(kk, hn - 1u)];
           pj = U.pv[t];
           aj = U.aux[t];
           cj = U.cell[t];
         };
-        auto body = [&](const float4& pj, const float4& aj, __half2 cj, uint32_t t) __attribute__((always_inline)) {
-          // offsets' difference, then whole cells
-          const float rx = fmaf(cxi - __low2float(cj), P.dc, pi.x - pj.x);
-          const float ry = fmaf(-__high2float(cj), P.dc, pi.y - pj.y);
-          const float r2 = fmaf(rx, rx, ry * ry);
-          if (r2 < P.four_h2) {
-            pair_body<AUD, VAR>(P, pi, rhoi, Pi, ci, rx, ry, r2, pj, aj, acc, aud);
-            if constexpr (EXP) {
-              const uint32_t u = u0 + t;
-              const uint32_t j = u + (u < ub1 ? ud0 : (u < ub2 ? ud1 : ud2));
-              const uint32_t f = at32(sb.id, ws + pl / PAIR_G) - (uint32_t)d.prm[0].id0;
-              const uint32_t c = atomicAdd(&d.nb_ids[f], 1u);
-              if (c < (uint32_t)WC_NB_CAP)
-                d.nb_ids[(size_t)d.prm[0].nf + (size_t)f * WC_NB_CAP + c] = at32(sb.id, j);
-            }
-          }
+        auto body = [&](const float4& pj, const float4& aj, __half2 cj) __attribute__((always_inline)) {
+          float rx, ry;
+          const float r2 = hit_rel(P.dc, cxi, pi, pj, cj, rx, ry);
+          if (r2 < P.four_h2) pair_body<AUD, VAR>(P, pi, rhoi, Pi, ci, rx, ry, r2, pj, aj, acc, aud);
         };
+        if constexpr (EXP) {
+          // (a loop of its own: within the pair law's the compiler kept the
+          // loop's state in scratch memory)
+          const uint32_t f = at32(sb.id, ws + pl / PAIR_G) - (uint32_t)d.prm[0].id0;
+          for (uint32_t kk = k; kk < hn; kk += PAIR_G) {
+            const uint32_t t = hl[kk], u = u0 + t;
+            float rx, ry;
+            if (!(hit_rel(P.dc, cxi, pi, U.pv[t], U.cell[t], rx, ry) < P.four_h2)) continue;
+            const uint32_t j = u + (u < ub1 ? ud0 : (u < ub2 ? ud1 : ud2));
+            const uint32_t c = atomicAdd(&d.nb_ids[f], 1u);
+            if (c < (uint32_t)WC_NB_CAP)
+              d.nb_ids[(size_t)d.prm[0].nf + (size_t)f * WC_NB_CAP + c] = at32(sb.id, j);
+          }
+        }
         float4 pa, aa, pb, ab;
         __half2 ca, cb;
-        uint32_t ta, tb;
-        fetch(k, pa, aa, ca, ta);
+        fetch(k, pa, aa, ca);
         for (;;) {
-          fetch(k + PAIR_G, pb, ab, cb, tb);
-          body(pa, aa, ca, ta);
+          fetch(k + PAIR_G, pb, ab, cb);
+          body(pa, aa, ca);
           k += PAIR_G;
           if (k >= hn) break;
-          fetch(k + PAIR_G, pa, aa, ca, ta);
-          body(pb, ab, cb, tb);
+          fetch(k + PAIR_G, pa, aa, ca);
+          body(pb, ab, cb);
           k += PAIR_G;
           if (k >= hn) break;
         }
@@ -1952,6 +1961,7 @@ template <int MODE, bool BATCH, bool AUD, int VAR>
 __global__ __launch_bounds__(PAIR_BLOCK, (AUD || MODE == EV_EXPORT) ? 1 : PAIR_MINW)
 void k_pair(Dev d, Buf sb, Buf base, Buf out) {
   constexpr bool MRG = (VAR & 16) != 0;  // the ghosts are in the sorts' launches
+  constexpr bool EXP = (VAR & 32) != 0;  // export of the neighbour lists
   // the corrector's state n is gathered before the pair sums where the chip is
   // not full (pair B 10.4 -> 10.0 us at 3,148 particles, 12.2 -> 11.8 at
   // 28,352), after them where its registers would cost more than its latency
@@ -2020,10 +2030,7 @@ void k_pair(Dev d, Buf sb, Buf base, Buf out) {
       rb0 = at32(base.aux, eb).x;
       Kb0 = at32(base.cell, eb);
     }
-    if (MODE == EV_EXPORT && d.nb_ids != nullptr)
-      pair_sums_wave<BATCH, AUD, VAR, true>(d, sb, G0, s0, inst, fluid, pi, ai, sh.uni[threadIdx.x >> 6], sS, acc, aud);
-    else
-      pair_sums_wave<BATCH, AUD, VAR>(d, sb, G0, s0, inst, fluid, pi, ai, sh.uni[threadIdx.x >> 6], sS, acc, aud);
+    pair_sums_wave<BATCH, AUD, VAR, EXP>(d, sb, G0, s0, inst, fluid, pi, ai, sh.uni[threadIdx.x >> 6], sS, acc, aud);
     // fixed-order combination of the slot's lane partial sums
     acc.D = slot_sum(acc.D);
     acc.ax = slot_sum(acc.ax);
@@ -2769,7 +2776,7 @@ static void launch_ghost(const Dev& d, int n_gblk, const Buf& sb, hipStream_t st
 // The pair pass of the context's scheme variant: bit 0 the quadratic AV
 // term (some instance has beta > 0), bit 1 the cubic spline kernel; scheme 1
 // (d.var bit 3) sums the internal-energy rate in place of the density rate.
-// (V4 bit 4: ghosts in the sort's launch)
+// (V4 bit 4: ghosts in the sort's launch; bit 5: export of the neighbour lists)
 template <int MODE, bool BATCH, bool AUD, int V4>
 static void launch_pair_v(const Dev& d, const Buf& sb, const Buf& base, const Buf& out, hipStream_t st) {
   const dim3 g(NQ(d.n_slots)), b(PAIR_BLOCK);
@@ -2784,8 +2791,16 @@ template <int MODE, bool BATCH, bool AUD = false>
 static void launch_pair(const Dev& d, const Buf& sb, const Buf& base, const Buf& out, hipStream_t st) {
   if constexpr (MODE == EV_L) launch_pair_v<MODE, BATCH, AUD, 4>(d, sb, base, out, st);
   else if constexpr (MODE == EV_EXPORT) {
-    if (d.var & 8) launch_pair_v<MODE, BATCH, AUD, 4>(d, sb, base, out, st);
-    else launch_pair_v<MODE, BATCH, AUD, 0>(d, sb, base, out, st);
+    // (the lists in instantiations of their own: both bodies in one kernel
+    // took 132 VGPRs and 400 B of scratch per lane; a launch at 179,552
+    // particles without lists 53.5 -> 19.5 us, with them 312 -> 190 us)
+    if (d.nb_ids != nullptr) {
+      if (d.var & 8) launch_pair_v<MODE, BATCH, AUD, 36>(d, sb, base, out, st);
+      else launch_pair_v<MODE, BATCH, AUD, 32>(d, sb, base, out, st);
+    } else {
+      if (d.var & 8) launch_pair_v<MODE, BATCH, AUD, 4>(d, sb, base, out, st);
+      else launch_pair_v<MODE, BATCH, AUD, 0>(d, sb, base, out, st);
+    }
   } else {
     if constexpr (!BATCH) {
       if (d.merged) return launch_pair_v<MODE, false, AUD, 16>(d, sb, base, out, st);
