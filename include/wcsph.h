@@ -361,6 +361,13 @@ wcsph_status wcsph_export_neighbour_lists_noalloc(wcsph_ctx* ctx, int* count, un
  * state is restored. */
 wcsph_status wcsph_time_pair_kernel(wcsph_ctx* ctx, int reps, float* avg_ms);
 
+/* Where the following steps of a single-instance context of scheme 0 compute
+ * the ghosts: own 1 in a launch of their own, 0 in the sort's launch (the
+ * context chooses by its size when it is created; the results are the same
+ * bit for bit). *was (may be NULL): the choice before. The state is left
+ * unchanged. */
+wcsph_status wcsph_set_ghost_launch(wcsph_ctx* ctx, int own, int* was);
+
 /* ---- coefficients and reverse sweep --------------------------------------- */
 
 /* Replace the Monaghan alpha, the delta-diffusion coefficient and the Tait

@@ -31,7 +31,7 @@ SYMBOLS = (
     "wcsph_synchronize", "wcsph_read_probes", "wcsph_read_diagnostics", "wcsph_get_fluid", "wcsph_get_disk",
     "wcsph_set_fluid", "wcsph_save_state", "wcsph_load_state", "wcsph_export_cells",
     "wcsph_export_rates", "wcsph_export_neighbours", "wcsph_export_neighbour_lists",
-    "wcsph_export_neighbour_lists_noalloc", "wcsph_time_pair_kernel",
+    "wcsph_export_neighbour_lists_noalloc", "wcsph_time_pair_kernel", "wcsph_set_ghost_launch",
     "wcsph_set_coefficients", "wcsph_adj_forward", "wcsph_adj_backward",
     "wcsph_get_internal_energy", "wcsph_export_density",
 )
@@ -162,6 +162,7 @@ def lib():
             "wcsph_export_neighbour_lists": [_V, _I, _U, C.c_int, C.c_int],
             "wcsph_export_neighbour_lists_noalloc": [_V, _I, _U, C.c_int, C.c_int],
             "wcsph_time_pair_kernel": [_V, C.c_int, _F],
+            "wcsph_set_ghost_launch": [_V, C.c_int, _I],
             "wcsph_set_coefficients": [_V, C.c_int, C.c_double, C.c_double, C.c_double],
             "wcsph_adj_forward": [_V, C.c_int, C.c_int, _D],
             "wcsph_adj_backward": [_V, C.c_double, _D],
@@ -415,6 +416,14 @@ class Solver:
         fn = lib().wcsph_export_neighbour_lists_noalloc if noalloc else lib().wcsph_export_neighbour_lists
         self._check(fn(self.handle, _p(cnt, C.c_int), _p(nbr, C.c_uint), max_per, nf))
         return [nbr[k, :cnt[k]].copy() for k in range(nf)]
+
+    def set_ghost_launch(self, own: bool) -> bool:
+        """Compute the ghosts of the following steps in a launch of their own,
+        or in the sort's launch (the same results bit for bit). Returns
+        whether they had a launch of their own before."""
+        was = C.c_int()
+        self._check(lib().wcsph_set_ghost_launch(self.handle, int(own), C.byref(was)))
+        return bool(was.value)
 
     # -- coefficients and reverse sweep ----------------------------------------
     def set_coefficients(self, alpha: float, delta: float, c0: float, inst: int = 0):

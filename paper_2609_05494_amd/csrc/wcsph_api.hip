@@ -667,6 +667,11 @@ bool merge_ghosts(const wcsph_ctx* c) {
 // keeps its extent within three cells wherever it lies.
 void ghost_blocks(wcsph_ctx* c) {
   const InstParams& q = c->hp[0];
+  c->h_sblk.clear();
+  c->h_witem.clear();
+  c->h_wcell.clear();
+  c->h_wplace.clear();
+  c->h_wpos.clear();
   std::vector<uint32_t> key(q.nw);
   std::vector<float2> pos(q.nw);
   std::vector<int> order(q.nw);
@@ -706,6 +711,47 @@ void ghost_blocks(wcsph_ctx* c) {
   runs(q.nw, 0, [&](int k) { return c->h_wcell[k]; });
   runs(q.n_probes, 2, [&](int k) { return q.probe_cell[k]; });
   c->n_sblk = (int)c->h_sblk.size();
+}
+
+// Their tables and work arrays on the device, as one block and one copy (a
+// context's allocations and copies are what its creation waits for).
+void merge_tables(wcsph_ctx* c) {
+  ghost_blocks(c);
+  Dev& d = c->d;
+  std::vector<char>& h = c->h_gtab;  // (kept until the copies are done)
+  h.clear();
+  auto place = [&](const void* src, size_t bytes) {
+    const size_t at = h.size();
+    h.resize(at + ((bytes + 63) & ~size_t(63)), 0);
+    if (src && bytes) std::memcpy(h.data() + at, src, bytes);
+    return at;
+  };
+  const size_t R = WC_MAX_RING;
+  const size_t o_sblk = place(c->h_sblk.data(), c->h_sblk.size() * sizeof(int4)),
+               o_item = place(c->h_witem.data(), c->h_witem.size() * 4),
+               o_cell = place(c->h_wcell.data(), c->h_wcell.size() * 4),
+               o_place = place(c->h_wplace.data(), c->h_wplace.size() * 4),
+               o_pos = place(c->h_wpos.data(), c->h_wpos.size() * 8), o_rcell = place(nullptr, 2 * R * 4),
+               o_rslot = place(nullptr, 2 * R * 4), o_rpos = place(nullptr, 2 * R * 8),
+               o_eval = place(nullptr, 2 * sizeof(DiskEval)), o_vmax = place(nullptr, (c->n_sblk + 1) * 4);
+  char* p = dalloc_n<char>(c, h.size());
+  d.sblk = reinterpret_cast<int4*>(p + o_sblk);
+  d.witem = reinterpret_cast<uint32_t*>(p + o_item);
+  d.wcell = reinterpret_cast<uint32_t*>(p + o_cell);
+  d.wplace = reinterpret_cast<uint32_t*>(p + o_place);
+  d.wpos = reinterpret_cast<float2*>(p + o_pos);
+  d.rcell_a = reinterpret_cast<uint32_t*>(p + o_rcell);
+  d.rcell_b = d.rcell_a + R;
+  d.rslot_a = reinterpret_cast<uint32_t*>(p + o_rslot);
+  d.rslot_b = d.rslot_a + R;
+  d.rpos_a = reinterpret_cast<float2*>(p + o_rpos);
+  d.rpos_b = d.rpos_a + R;
+  d.deval_a = reinterpret_cast<DiskEval*>(p + o_eval);
+  d.deval_b = d.deval_a + 1;
+  d.n_sblk = c->n_sblk;
+  d.gvmax = reinterpret_cast<float*>(p + o_vmax);
+  d.gvstep = reinterpret_cast<uint32_t*>(d.gvmax + c->n_sblk);
+  HC(hipMemcpyAsync(p, h.data(), h.size(), hipMemcpyHostToDevice, c->st));
 }
 
 void build(wcsph_ctx* c, const wcsph_params* params, int n_inst) {
@@ -759,7 +805,6 @@ void build(wcsph_ctx* c, const wcsph_params* params, int n_inst) {
   }
   c->n_gblk = (int)c->h_gblk.size();
   c->d.merged = merge_ghosts(c) ? 1 : 0;
-  if (c->d.merged) ghost_blocks(c);
   for (uint32_t w : c->h_wallcount)
     require(w <= WC_BUCKET / 2, "too many wall ghosts in one cell (ghost_layers too large for h/dx)");
   // device memory
@@ -819,44 +864,7 @@ void build(wcsph_ctx* c, const wcsph_params* params, int n_inst) {
   c->d_gslot_save = dalloc_n<uint32_t>(c, c->n_ghost);
   uint32_t* wrank = dalloc_n<uint32_t>(c, c->n_ghost);
   d.wrank = wrank;
-  if (d.merged) {
-    // the tables and the work arrays of the ghosts in the sort's launch, as one
-    // block and one copy (a context's allocations and copies are what its
-    // creation waits for)
-    std::vector<char>& h = c->h_gtab;  // (kept until the copies are done)
-    auto place = [&](const void* src, size_t bytes) {
-      const size_t at = h.size();
-      h.resize(at + ((bytes + 63) & ~size_t(63)), 0);
-      if (src && bytes) std::memcpy(h.data() + at, src, bytes);
-      return at;
-    };
-    const size_t R = WC_MAX_RING;
-    const size_t o_sblk = place(c->h_sblk.data(), c->h_sblk.size() * sizeof(int4)),
-                 o_item = place(c->h_witem.data(), c->h_witem.size() * 4),
-                 o_cell = place(c->h_wcell.data(), c->h_wcell.size() * 4),
-                 o_place = place(c->h_wplace.data(), c->h_wplace.size() * 4),
-                 o_pos = place(c->h_wpos.data(), c->h_wpos.size() * 8), o_rcell = place(nullptr, 2 * R * 4),
-                 o_rslot = place(nullptr, 2 * R * 4), o_rpos = place(nullptr, 2 * R * 8),
-                 o_eval = place(nullptr, 2 * sizeof(DiskEval)), o_vmax = place(nullptr, (c->n_sblk + 1) * 4);
-    char* p = dalloc_n<char>(c, h.size());
-    d.sblk = reinterpret_cast<int4*>(p + o_sblk);
-    d.witem = reinterpret_cast<uint32_t*>(p + o_item);
-    d.wcell = reinterpret_cast<uint32_t*>(p + o_cell);
-    d.wplace = reinterpret_cast<uint32_t*>(p + o_place);
-    d.wpos = reinterpret_cast<float2*>(p + o_pos);
-    d.rcell_a = reinterpret_cast<uint32_t*>(p + o_rcell);
-    d.rcell_b = d.rcell_a + R;
-    d.rslot_a = reinterpret_cast<uint32_t*>(p + o_rslot);
-    d.rslot_b = d.rslot_a + R;
-    d.rpos_a = reinterpret_cast<float2*>(p + o_rpos);
-    d.rpos_b = d.rpos_a + R;
-    d.deval_a = reinterpret_cast<DiskEval*>(p + o_eval);
-    d.deval_b = d.deval_a + 1;
-    d.n_sblk = c->n_sblk;
-    d.gvmax = reinterpret_cast<float*>(p + o_vmax);
-    d.gvstep = reinterpret_cast<uint32_t*>(d.gvmax + c->n_sblk);
-    HC(hipMemcpyAsync(p, h.data(), h.size(), hipMemcpyHostToDevice, c->st));
-  }
+  if (d.merged) merge_tables(c);
   int4* gblk = dalloc_n<int4>(c, c->n_gblk);
   d.gblk = gblk;
   d.hist_t = dalloc_n<double>(c, (size_t)n_inst * WC_HIST_CAP);
@@ -1851,6 +1859,22 @@ wcsph_status wcsph_time_pair_kernel(wcsph_ctx* ctx, int reps, float* avg_ms) {
   hipEventDestroy(e1);
   *avg_ms = ms / reps;
   guard.restore();
+  API_END(ctx)
+}
+
+wcsph_status wcsph_set_ghost_launch(wcsph_ctx* ctx, int own, int* was) {
+  API_BEGIN(ctx)
+  require(!ctx->batch && ctx->scheme == 0, "single-instance contexts of scheme 0 only");
+  if (was) *was = ctx->d.merged ? 0 : 1;
+  sync(ctx);
+  if (!own && !ctx->d.sblk) {
+    merge_tables(ctx);
+    sync(ctx);
+  }
+  ctx->d.merged = own ? 0 : 1;
+  rearm(ctx);  // (places the ring where the launch looks for it)
+  sync(ctx);
+  capture(ctx);
   API_END(ctx)
 }
 

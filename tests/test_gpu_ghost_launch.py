@@ -1,0 +1,113 @@
+"""Ghosts in the sort's launch against ghosts in a launch of their own, over
+every form and option that both serve: states, histories, every diagnostic
+(the audit's sums, the ring's work), impulse and gradient are the same bit for
+bit, also when the launch changes in the middle of a run."""
+import numpy as np
+import pytest
+
+import workloads
+
+pytestmark = pytest.mark.gpu
+
+wc = pytest.importorskip("paper_2609_05494_amd")
+
+FORMS = {
+    "plain": lambda c: c,
+    "no_disk": lambda c: dict(c, disk_R=0.0, n_disk_ghosts=0, init_mode=1),
+    "audit": lambda c: dict(c, audit=1),
+    "audit_cubic_beta": lambda c: dict(c, audit=1, kernel_type=1, beta=1.0),
+    "beta": lambda c: dict(c, beta=1.0),
+    "cubic": lambda c: dict(c, kernel_type=1),
+    "mg": workloads.mie_grueneisen,
+    "mg_inverse_cubic": lambda c: dict(workloads.mie_grueneisen(c), kernel_type=1, ghost_rho_mode=1),
+    "two_way": workloads.two_way,
+    "two_way_audit": lambda c: dict(workloads.two_way(c), audit=1),
+    "drag": lambda c: dict(c, kin_mode=1, kin_coef=3.0),
+    "axisym": workloads.axisymmetric,
+    "axisym_two_way": lambda c: workloads.axisymmetric(dict(c, kin_mode=2)),
+}
+
+
+def _same(a, b):
+    for u, v in zip(a.read_probes() + a.disk_state(), b.read_probes() + b.disk_state()):
+        assert np.array_equal(u, v)
+    da, db = a.read_diagnostics(), b.read_diagnostics()
+    for k in da:
+        assert np.array_equal(da[k], db[k]), k
+    (ta, fa), (tb, fb) = a.fluid(), b.fluid()
+    assert ta == tb
+    for u, v in zip(fa, fb):
+        assert np.array_equal(u, v)
+
+
+def _pair(cfg):
+    a, b = wc.Solver(cfg, "cuda:0"), wc.Solver(cfg, "cuda:0")
+    a.set_ghost_launch(False)
+    b.set_ghost_launch(True)
+    assert not a.set_ghost_launch(False) and b.set_ghost_launch(True)
+    return a, b
+
+
+@pytest.mark.parametrize("form", FORMS)
+def test_both_launches_give_the_same_run(form):
+    cfg = FORMS[form](workloads.C1())
+    print(f"[gpu] both ghost launches, {form}", flush=True)
+    a, b = _pair(cfg)
+    for s in (a, b):
+        s.step(67)  # past the 5 us ramp: a two-way disk is coupled by then
+    _same(a, b)
+    # the other way round from here, and back
+    for s, first in ((a, True), (b, False)):
+        s.set_ghost_launch(first)
+        s.step(14)
+        s.set_ghost_launch(not first)
+        s.step(9)
+    _same(a, b)
+    a.close()
+    b.close()
+
+
+def test_both_launches_follow_a_table_and_fixed_steps():
+    cfg = dict(workloads.C1(), kin_mode=3)
+    print("[gpu] both ghost launches, tabulated motion", flush=True)
+    a, b = _pair(cfg)
+    for s in (a, b):
+        s.set_kinematics_table([(0.0, 4e-3, 0.0, 4e7), (4e-6, 4.3e-3, 160.0, 1e7), (8e-6, 5.1e-3, 200.0, -1e6)])
+        s.step(30)
+        s.set_dt_table(np.full(40, 1.1e-7))
+        s.step(45)
+        s.set_coefficients(0.2, 0.05, 1500.0)
+        s.step(6)
+    _same(a, b)
+    a.close()
+    b.close()
+
+
+@pytest.mark.parametrize("ckpt", [7, 25])
+def test_both_launches_tape_the_same_run(ckpt):
+    cfg = workloads.C1()
+    print(f"[gpu] both ghost launches, adjoint, checkpoint every {ckpt}", flush=True)
+    a, b = _pair(cfg)
+    out = []
+    for s in (a, b):
+        s.step(60)
+        blob = s.save_state()
+        s.set_dt_table(np.full(25, 1.1e-7))
+        s.load_state(blob)
+        J = s.adj_forward(25, ckpt)
+        out.append(np.append(s.adj_backward(1.0), J))
+    assert np.all(np.isfinite(out[0])) and np.any(out[0][:3] != 0.0)
+    assert np.array_equal(*out)
+    _same(a, b)
+    a.close()
+    b.close()
+
+
+def test_contexts_with_one_ghost_launch_refuse_the_choice():
+    for cfg in ([workloads.tiny()], workloads.paper_scheme(workloads.tiny())):
+        s = wc.Solver(cfg, "cuda:0")
+        with pytest.raises(wc.WcsphError) as e:
+            s.set_ghost_launch(True)
+        assert e.value.status == wc.E_INVALID
+        s.step(2)
+        s.close()
