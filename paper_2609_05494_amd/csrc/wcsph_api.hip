@@ -650,28 +650,12 @@ void capture(wcsph_ctx* c) {
   if (c->scheme == 1) capture_pair(c, 1, &c->graph1, &c->gexec1, &c->graph_k1, &c->gexec_k1);
 }
 
-// Ghosts in the sort's launch instead of a launch of their own: a single
-// instance up to WC_MERGE_SLOTS slots. There the two launches are chains of
-// dependent loads on a nearly idle chip and run side by side; us a step, own
-// launch -> merged: 45.6 -> 42.6 at 28,352 particles, 53.4 -> 50.0 at 71,752,
-// 69.7 -> 67.7 at 134,752. Above it the tiles fill the chip, and the ghost
-// blocks' LDS costs them waves: 79.3 -> 79.7 at 179,552, 186 -> 199 at 719,552;
-// so it does in a batch (16 instances, 530,000 particles: 196 -> 238). The
-// leapfrog's ghosts need the summed density of its own pass.
-bool merge_ghosts(const wcsph_ctx* c) {
-  return !c->batch && c->scheme == 0 && c->n_slots <= WC_MERGE_SLOTS;
-}
 // Block table of these ghosts: runs of at most 16 items (wall ghosts in cell
 // order, ring ghosts, probes) whose cells, with one cell around them, fit
 // WC_GHOST_REGION cells. The ring moves: a run of ring ghosts is as long as
 // keeps its extent within three cells wherever it lies.
 void ghost_blocks(wcsph_ctx* c) {
   const InstParams& q = c->hp[0];
-  c->h_sblk.clear();
-  c->h_witem.clear();
-  c->h_wcell.clear();
-  c->h_wplace.clear();
-  c->h_wpos.clear();
   std::vector<uint32_t> key(q.nw);
   std::vector<float2> pos(q.nw);
   std::vector<int> order(q.nw);
@@ -713,10 +697,37 @@ void ghost_blocks(wcsph_ctx* c) {
   c->n_sblk = (int)c->h_sblk.size();
 }
 
+// Ghosts in the sort's launch instead of a launch of their own: a single
+// instance whose launch then has at most three blocks per compute unit. There
+// the two launches are chains of dependent loads on a nearly idle chip and run
+// side by side; beyond it blocks wait for others to end, and the ghost blocks'
+// LDS costs the tiles waves. The line is in blocks, not in slots, since the
+// cells per slot go with h/dx and the ghosts per slot with the channel's form.
+// us a step, own launch -> merged, at blocks (slots):
+//   h/dx 1.3, 2:1     673 (122,156) 64.5 -> 63.3, 766 (146,532) 69.4 -> 67.8,
+//                     794 (154,492) 71.3 -> 71.3, 826 (162,664) 73.7 -> 75.0,
+//                     975 (205,410) 81.6 -> 85.5
+//   h/dx 1.3, 5:1     779 (139,562) 67.6 -> 67.7, 840 (155,915) 71.3 -> 72.6
+//   h/dx 1.3, 20:1    629 (66,565) 52.3 -> 49.5, 809 (98,125) 58.4 -> 58.9,
+//                     911 (119,012) 65.6 -> 68.0
+//   h/dx 1.0, 2:1     748 (91,452) 53.0 -> 51.0, 797 (99,548) 55.2 -> 55.9,
+//                     843 (107,760) 58.3 -> 59.7
+//   6 ghost layers    1,017 (133,796) 68.3 -> 70.0
+//   r-z, 2:1          758 (139,358) 70.4 -> 70.4, 852 (164,286) 75.3 -> 76.7
+//   h/dx 2.0, 2:1     696 (207,336) 127.4 -> 121.6, 902 (308,933) 161.0 -> 158.6
+// (the last, of 16 particles a cell, gains beyond the line too). A batch keeps
+// the separate launch (16 instances, 530,000 particles: 196 -> 238), and so
+// does the leapfrog: its ghosts need the summed density of its own pass.
+bool merge_ghosts(wcsph_ctx* c) {
+  const int tiles = (c->n_cells + WC_SORT_TILE - 1) / WC_SORT_TILE;
+  if (c->batch || c->scheme != 0 || 1 + tiles > WC_MERGE_BLOCKS) return false;
+  ghost_blocks(c);
+  return 1 + tiles + c->n_sblk <= WC_MERGE_BLOCKS;
+}
 // Their tables and work arrays on the device, as one block and one copy (a
 // context's allocations and copies are what its creation waits for).
 void merge_tables(wcsph_ctx* c) {
-  ghost_blocks(c);
+  if (c->h_sblk.empty()) ghost_blocks(c);
   Dev& d = c->d;
   std::vector<char>& h = c->h_gtab;  // (kept until the copies are done)
   h.clear();

@@ -25,7 +25,7 @@
 #define WC_DIAG_BLOCKS 256     // diagnostic partial sums per instance
 #define WC_BUCKET 64           // capacity of one cell bucket (particles per cell)
 #define WC_SORT_TILE 64        // cells per block of the sort kernel
-#define WC_MERGE_SLOTS 131072  // ghosts go into the sort's launch up to so many slots (measured: merge_ghosts)
+#define WC_MERGE_BLOCKS 768    // ghosts go into the sort's launch up to so many blocks (measured: merge_ghosts)
 #define WC_GHOST_REGION 64     // cells that a ghost block of the sort's launch stages at most
 #define WC_NB_CAP 64           // neighbour ids per particle in the neighbour-list export
 #define WC_KIN_ROWS 1024       // rows of a tabulated disk motion per instance

@@ -111,3 +111,22 @@ def test_contexts_with_one_ghost_launch_refuse_the_choice():
         assert e.value.status == wc.E_INVALID
         s.step(2)
         s.close()
+
+
+# 763, 772, 759 and 770 blocks: either side of three per compute unit (768)
+@pytest.mark.parametrize("nx,h_over_dx,own", [(428, 1.0, False), (432, 1.0, True), (532, 1.3, False), (536, 1.3, True)])
+def test_choice_on_either_side_of_the_line(nx, h_over_dx, own):
+    cfg = workloads.base(nx * 1e-3, nx // 2 * 1e-3, 1e-3, 6e-3, 900.0)
+    cfg = dict(cfg, h_over_dx=h_over_dx, cell_size=workloads._cell_size(1e-3, h_over_dx))
+    print(f"[gpu] {nx}x{nx // 2}, h/dx {h_over_dx}", flush=True)
+    a, b, c = wc.Solver(cfg, "cuda:0"), wc.Solver(cfg, "cuda:0"), wc.Solver([cfg], "cuda:0")
+    assert b.set_ghost_launch(not own) == own
+    for s in (a, b, c):
+        s.step(23)
+    _same(c, a)
+    c.close()
+    d = wc.Solver(cfg, "cuda:0")
+    d.step(23)
+    _same(d, b)
+    for s in (a, b, d):
+        s.close()
