@@ -1250,8 +1250,10 @@ __device__ __forceinline__ void sort_store(const Dev& d, const InstParams& P1, c
   if (v.ghost >= 0) {
     const int gi = (BATCH ? d.prm[v.inst].gmap0 : P1.gmap0) + v.ghost;
     d.gslot[gi] = dst;
-    d.gcell[gi] = K;
-    d.gpos[gi] = make_float2(v.pv.x, v.pv.y);
+    if constexpr (!GH) {  // (for the ghosts' own launch)
+      d.gcell[gi] = K;
+      d.gpos[gi] = make_float2(v.pv.x, v.pv.y);
+    }
   }
   out.cell[dst] = K;
   out.id[dst] = v.id;
