@@ -16,7 +16,12 @@
  *  - Every function returns wcsph_status; nothing throws across the ABI.
  *  - Host pointers are caller-owned and only read/written during the call.
  *    Device memory is owned by the context; it is obtained through the
- *    caller's allocator (or hipMalloc when none is given) at create time.
+ *    caller's allocator (or hipMalloc when none is given) at create time,
+ *    1 MiB of it for the short reads and loads of the state.
+ *  - A context also holds 1 MiB of page-locked host memory (hipHostMalloc,
+ *    not the caller's allocator), through which its short reads and loads go.
+ *    Up to four such blocks of destroyed contexts are kept for the next ones
+ *    until the process ends. Where none can be had, create returns E_OOM.
  *  - Work is queued on the stream given at create (it must not be the
  *    legacy NULL stream: the step is captured into a HIP graph on it).
  *    wcsph_step returns without waiting; every read_* / get_* / export_*
@@ -215,7 +220,8 @@ typedef struct {
  * alloc: NULL -> hipMalloc/hipFree. stream: a hipStream_t, not NULL.
  * Errors: E_INVALID (dx <= 0, h_over_dx outside [1,2], cell_size < 2h,
  * disk outside the box, n_probes > 16, ...) before any allocation;
- * E_OOM / E_HIP afterwards (the partially built context is released). */
+ * E_OOM (device or page-locked host memory) / E_HIP afterwards (the partially
+ * built context is released). */
 wcsph_status wcsph_create(const wcsph_params* p, const wcsph_allocator* alloc, void* stream,
                           wcsph_ctx** out);
 

@@ -519,8 +519,8 @@ __device__ __forceinline__ void wait_loads() {
 // offset, vx, vy) and (rho, P, c, m), each entry's cell column and row from
 // the group's first column and its row, and the pass's hits: per slot of
 // the wave, entry indices. The test coordinates X, Y and X^2 + Y^2 stand in
-// the place of aux until the test has read them. (The size lets seven blocks
-// share a compute unit's LDS.)
+// the place of aux until the test has read them. (A block takes 25,344 B with
+// LCAP 24, so six share a compute unit's LDS; seven with LCAP 16.)
 struct PairLds {
   float4 pv[UCAP];
   union {
@@ -1804,7 +1804,8 @@ __global__ __launch_bounds__(WC_GHOST_BLOCK) void k_ghost(Dev d, Buf sb) {
   asm("" : "+s"(blk.x), "+s"(blk.y), "+s"(blk.z), "+s"(blk.w), "+s"(gslot), "+s"(gcell), "+s"(gpos));
   const int inst = BATCH ? blk.x : 0, kind = blk.w;
   // the block's items are of one instance: its constants and clock through the
-  // scalar cache (no block writes what is read of the clock here but v_max);
+  // scalar cache (no block writes what is read of this copy: v_max, which the
+  // pass raises, is read by an atomic load);
   // as vector loads each waited where it was first used (corrector 7.3
   // -> 6.4 us a launch at 179,552 particles, 8.3 -> 7.1 at 719,552)
   const InstParams P = scalar_copy(d.prm + inst);
@@ -1944,8 +1945,8 @@ __device__ __forceinline__ double eos_e_el(const InstParams& P, double r) {
   return P.eos_type == 1 ? mg_e_el(P, r) : tait_e_el(P, r);
 }
 
-// The pass is bound by VALU issue where the chip is full (94 % of a wave's
-// four-cycle issue slots at 720k particles) and by the wave's chain of loads
+// The pass is bound by VALU issue where the chip is full (92 % of the four-cycle
+// issue slots at 720k particles, 71 % at 180k) and by the wave's chain of loads
 // (slots, cell starts, entries) where it is not. Against the same pass with
 // each lane testing its own candidates one by one, summing its own hits (nine
 // rounds of the pair law for 20 neighbours over four lanes, now five or six)
@@ -1953,9 +1954,9 @@ __device__ __forceinline__ double eos_e_el(const InstParams& P, double r) {
 // of 1,088, and per launch 27.9 -> 24.4 us at 180k particles, 83 -> 71 us at
 // 720k, 75 -> 61 us for sixteen instances of 30k, 12.5 -> 10.1 us at 3k.
 // Blocks per compute unit that the register budget is held to: at most 80
-// VGPRs (67 are used; 23 to 25 KB of LDS per block then let six or seven
-// blocks share a compute unit). The audit and export variants keep the
-// compiler's budget.
+// VGPRs (64 to 78 are used, by variant; the 23 to 25 KB of LDS per block let
+// six or seven blocks share a compute unit). The audit and export variants keep
+// the compiler's budget (80 to 84 and 64 to 72, and 8 accumulation registers).
 #ifndef PAIR_MINW
 #define PAIR_MINW 6
 #endif

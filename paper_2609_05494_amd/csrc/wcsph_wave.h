@@ -16,8 +16,10 @@ __device__ __forceinline__ int xcd_block(int bid, int nblk) {
 // constant address space, a block that is the same on every lane comes
 // through the scalar cache wherever it is read.)
 typedef const __attribute__((address_space(4))) InstParams ConstParams;
-// A copy of a block that no one writes meanwhile (of the fields that are
-// used, when it is inlined), read through the constant address space.
+// A copy of a block that no one writes meanwhile, read through the constant
+// address space. (When it is inlined only the fields that are used are read;
+// the kernel itself must not write those either, since the compiler may load
+// them again at any place.)
 template <class T>
 __device__ __forceinline__ T scalar_copy(const T* p) {
   static_assert(sizeof(T) % 8 == 0, "whole words");
