@@ -26,7 +26,8 @@
 #define WC_BUCKET 64           // capacity of one cell bucket (particles per cell)
 #define WC_SORT_TILE 64        // cells per block of the sort kernel
 #define WC_MERGE_BLOCKS 768    // ghosts go into the sort's launch up to so many blocks (measured: merge_ghosts)
-#define WC_GHOST_REGION 64     // cells that a ghost block of the sort's launch stages at most
+#define WC_GHOST_REGION 64     // cells around the items of a ghost block of the sort's launch, at most
+#define WC_GHOST_STAGE 320     // particles of them that it holds in LDS at once
 #define WC_NB_CAP 64           // neighbour ids per particle in the neighbour-list export
 #define WC_KIN_ROWS 1024       // rows of a tabulated disk motion per instance
 #define WC_TEST_UNITS 256      // test coordinates of the pair pass: units per cell edge

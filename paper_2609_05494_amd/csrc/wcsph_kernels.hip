@@ -1278,12 +1278,11 @@ __device__ __forceinline__ void sort_store(const Dev& d, const InstParams& P1, c
 // buckets in LDS in sorted order (as the tiles rank them), with the EOS, and
 // 16 lanes per item walk the item's cells there, rows bottom to top, in the
 // order and by the lanes that a walk of the sorted arrays would take. A region
-// of more than GHOST_EC particles is staged in windows. A ghost's sorted slot,
+// of more than WC_GHOST_STAGE particles is staged in windows. A ghost's sorted slot,
 // which the tiles find too, is the entries before its tile and before its cell
 // plus its rank in its bucket.
-#define GHOST_EC 320
 struct GhostLds {
-  float4 pv[GHOST_EC], aux[GHOST_EC];
+  float4 pv[WC_GHOST_STAGE], aux[WC_GHOST_STAGE];
   uint32_t n[WC_GHOST_REGION];
   int box[4][4];
   float vmax[4];
@@ -1293,7 +1292,7 @@ struct GhostLds {
 template <bool MG>
 __device__ __forceinline__ void ghost_put(const Dev& d, const InstParams& P1, int ccx, int ccy, uint32_t x,
                                           const Loaded& l, GhostLds& G) {
-  if (x >= (uint32_t)GHOST_EC) return;
+  if (x >= (uint32_t)WC_GHOST_STAGE) return;
   const Gathered v = sort_finish<MG, false>(d, P1, ccx, ccy, l);
   G.pv[x] = v.pv;
   G.aux[x] = v.inst < 0 ? make_float4(1.0f, 0.0f, 0.0f, 0.0f) : v.aux;
@@ -1309,7 +1308,7 @@ __device__ __forceinline__ void ghost_stage(const Dev& d, const Buf& pre, const 
     const uint32_t ei = raw[i];
     uint32_t ri = 0u;
     for (uint32_t k = 0; k < n; ++k) ri += raw[k] < ei ? 1u : 0u;
-    if (off + ri - w0 < (uint32_t)GHOST_EC)
+    if (off + ri - w0 < (uint32_t)WC_GHOST_STAGE)
       ghost_put<MG>(d, P1, ccx, ccy, off + ri - w0, sort_load<false>(d, pre, ei), G);
   }
 }
@@ -1326,7 +1325,7 @@ __device__ __forceinline__ bool ghost_candidate(GhostRows R, uint32_t k, uint32_
   const uint32_t jm = in0 ? R.m0 : (in1 ? R.m1 : R.m2), je = in0 ? R.e0 : (in1 ? R.e1 : R.e2);
   x = j - w0;
   code = (in0 ? 0u : (in1 ? 4u : 8u)) | (j < jm ? 0u : (j < je ? 1u : 2u));
-  return x < (uint32_t)GHOST_EC;
+  return x < (uint32_t)WC_GHOST_STAGE;
 }
 // Sorted slot of the ghost of item (l / 4) of block blk, by four lanes: the
 // entries of the tiles before its cell's, of the cells before it in its tile,
@@ -1555,7 +1554,7 @@ __device__ __forceinline__ void ghost_block(const Dev& d, const Buf& pre, const 
   Shep S = {0, 0, 0, 0, 0, 0};
   uint32_t k = (uint32_t)lane, x, code;
 #pragma unroll 1
-  for (uint32_t w0 = 0u; w0 < total; w0 += GHOST_EC) {
+  for (uint32_t w0 = 0u; w0 < total; w0 += WC_GHOST_STAGE) {
     window(w0);
     for (; k < R.nn && ghost_candidate(R, k, w0, x, code); k += GL)
       shepard_add<CUB>(P, pg.x, pg.y, G.pv[x], G.aux[x], code, S);
@@ -1603,7 +1602,7 @@ __device__ __forceinline__ void ghost_block(const Dev& d, const Buf& pre, const 
       const float yg = (float)(P.y_lo + (double)cy * P.dcd) + pg.y;  // the ghost's radius (axisymmetric)
       k = (uint32_t)lane;
 #pragma unroll 1
-      for (uint32_t w0 = 0u; w0 < total; w0 += GHOST_EC) {
+      for (uint32_t w0 = 0u; w0 < total; w0 += WC_GHOST_STAGE) {
         window(w0);
         for (; k < R.nn && ghost_candidate(R, k, w0, x, code); k += GL)
           ring_force_add<CUB>(P, pg.x, pg.y, yg, m, q, G.pv[x], G.aux[x], code, fx);
