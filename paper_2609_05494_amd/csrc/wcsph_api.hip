@@ -652,11 +652,16 @@ void capture(wcsph_ctx* c) {
 
 // Block table of these ghosts: runs of at most 16 items (wall ghosts in cell
 // order, ring ghosts, probes) whose cells, with one cell around them, fit
-// WC_GHOST_REGION cells and, on the lattice, WC_GHOST_STAGE particles: a block
-// that stages its region in several windows is the launch's longest (probes of
-// both walls of a 79,558-particle channel of 20:1 at h/dx 2.0, 852 particles
-// in one block, made it 10.6 -> 36 us). The ring moves: a run of ring ghosts
-// is as long as keeps its extent within `span` cells wherever it lies.
+// WC_GHOST_REGION cells and hold, as far as the lattice and the ring can tell,
+// no more than the WC_GHOST_STAGE particles that a block stages at once: one
+// that stages its region in several windows is the launch's longest, and all
+// of a step waits for it (us a step, own launch -> merged, with such a block
+// and without: probes of both walls of a 20:1 channel at h/dx 2.0 88 -> 116,
+// 84; walls left and right of a ring of 150 ghosts in one run 60 -> 71, 56;
+// 30 particles a cell around 16 ring ghosts 92 -> 164, 85). So a run of wall
+// ghosts ends where the next one is not beside it, a probe has a block of its
+// own, and a run of ring ghosts is as long as keeps its extent within `span`
+// cells wherever it moves.
 void ghost_blocks(wcsph_ctx* c) {
   const InstParams& q = c->hp[0];
   std::vector<uint32_t> key(q.nw);
@@ -675,32 +680,39 @@ void ghost_blocks(wcsph_ctx* c) {
   }
   const double per_cell = q.dcd * q.dcd / (c->pin[0].dx * c->pin[0].dx);
   const int cells = std::min(WC_GHOST_REGION, std::max(9, (int)(WC_GHOST_STAGE / per_cell)));
-  auto runs = [&](int n, int kind, auto&& cell) {
-    for (int a = 0; a < n;) {
-      int x0 = 1 << 30, x1 = -1, y0 = 1 << 30, y1 = -1, e = a;
-      for (; e < n && e - a < 16; ++e) {
-        const int l = (int)cell(e) - q.cell_off, x = l % q.ncx, y = l / q.ncx;
-        const int u0 = std::min(x0, x), u1 = std::max(x1, x), v0 = std::min(y0, y), v1 = std::max(y1, y);
-        if (e > a && (u1 - u0 + 3) * (v1 - v0 + 3) > cells) break;
-        x0 = u0;
-        x1 = u1;
-        y0 = v0;
-        y1 = v1;
-      }
-      c->h_sblk.push_back(make_int4(0, a, e - a, kind));
-      a = e;
-    }
-  };
   // ring ghosts first: theirs are the longest blocks
   if (q.nd > 0) {
-    const double chord = 2.0 * M_PI * q.R / q.nd;  // (no shorter than the distance of neighbours)
-    // (an extent of `span` cells touches span + 1 of them on an axis, and one more on each side)
-    const double span = std::min(3.0, std::max(1.0, std::floor(std::sqrt((double)cells)) - 3.0));
-    const int len = (int)std::min(16.0, std::max(1.0, 1.0 + std::floor(span * q.dcd / std::max(chord, 1e-300))));
+    const double chord = std::max(2.0 * M_PI * q.R / q.nd, 1e-300);  // (no shorter than the distance of neighbours)
+    const double ring_cell = q.dcd / chord;                          // ring ghosts over a cell's edge
+    // an extent of `span` cells touches span + 1 of them on an axis, and one
+    // more on each side; the ring crosses that box once
+    auto held = [&](int span) {
+      const double side = span + 3;
+      return side * side * per_cell + std::min((double)q.nd, 1.4 * side * ring_cell);
+    };
+    int span = (int)std::min(3.0, std::ceil(15.0 / ring_cell));  // (16 items reach no further)
+    while (span > 0 && held(span) > WC_GHOST_STAGE) --span;
+    const int len = (int)std::min(16.0, 1.0 + std::floor(span * ring_cell));
     for (int a = 0; a < q.nd; a += len) c->h_sblk.push_back(make_int4(0, q.nw + a, std::min(len, q.nd - a), 1));
   }
-  runs(q.nw, 0, [&](int k) { return c->h_wcell[k]; });
-  runs(q.n_probes, 2, [&](int k) { return q.probe_cell[k]; });
+  for (int a = 0; a < q.nw;) {
+    int x0 = 1 << 30, x1 = -1, y0 = 1 << 30, y1 = -1, e = a, xp = 0, yp = 0;
+    for (; e < q.nw && e - a < 16; ++e) {
+      const int l = (int)c->h_wcell[e] - q.cell_off, x = l % q.ncx, y = l / q.ncx;
+      const int u0 = std::min(x0, x), u1 = std::max(x1, x), v0 = std::min(y0, y), v1 = std::max(y1, y);
+      const bool beside = std::abs(x - xp) <= 1 && y - yp <= 1;
+      if (e > a && (!beside || (u1 - u0 + 3) * (v1 - v0 + 3) > cells)) break;
+      x0 = u0;
+      x1 = u1;
+      y0 = v0;
+      y1 = v1;
+      xp = x;
+      yp = y;
+    }
+    c->h_sblk.push_back(make_int4(0, a, e - a, 0));
+    a = e;
+  }
+  for (int k = 0; k < q.n_probes; ++k) c->h_sblk.push_back(make_int4(0, k, 1, 2));
   c->n_sblk = (int)c->h_sblk.size();
 }
 
@@ -719,12 +731,17 @@ void ghost_blocks(wcsph_ctx* c) {
 //                     911 (119,012) 65.6 -> 68.0
 //   h/dx 1.0, 2:1     748 (91,452) 53.0 -> 51.0, 797 (99,548) 55.2 -> 55.9,
 //                     843 (107,760) 58.3 -> 59.7
+//   h/dx 1.6, 10:1    767 (111,155) 79.6 -> 75.3
+//   h/dx 1.6, 30:1    754 (59,820) 61.8 -> 57.1, 968 (92,412) 73.0 -> 74.8
+//   h/dx 2.0, 20:1    761 (85,070) 85.9 -> 80.0, 877 (111,512) 94.7 -> 94.7
 //   6 ghost layers    1,017 (133,796) 68.3 -> 70.0
 //   r-z, 2:1          758 (139,358) 70.4 -> 70.4, 852 (164,286) 75.3 -> 76.7
-//   h/dx 2.0, 2:1     696 (207,336) 127.4 -> 121.6, 902 (308,933) 161.0 -> 158.6
-// (the last, of 16 particles a cell, gains beyond the line too). A batch keeps
-// the separate launch (16 instances, 530,000 particles: 196 -> 238), and so
-// does the leapfrog: its ghosts need the summed density of its own pass.
+// From ten particles a cell on (h/dx 1.6) the gain goes on a little beyond the
+// line in some channels (10:1, 818 blocks 83.0 -> 79.8; 2:1, 817 100.9 -> 98.5,
+// but 877 106.4 -> 108.0; 20:1 with cells of 5 dx, 875 112.0 -> 117.0): not
+// taken. A batch keeps the separate launch (16 instances, 530,000 particles:
+// 196 -> 238), and so does the leapfrog: its ghosts need the summed density of
+// its own pass.
 bool merge_ghosts(wcsph_ctx* c) {
   const int tiles = (c->n_cells + WC_SORT_TILE - 1) / WC_SORT_TILE;
   if (c->batch || c->scheme != 0 || 1 + tiles > WC_MERGE_BLOCKS) return false;

@@ -1278,9 +1278,10 @@ __device__ __forceinline__ void sort_store(const Dev& d, const InstParams& P1, c
 // buckets in LDS in sorted order (as the tiles rank them), with the EOS, and
 // 16 lanes per item walk the item's cells there, rows bottom to top, in the
 // order and by the lanes that a walk of the sorted arrays would take. A region
-// of more than WC_GHOST_STAGE particles is staged in windows. A ghost's sorted slot,
-// which the tiles find too, is the entries before its tile and before its cell
-// plus its rank in its bucket.
+// of more than WC_GHOST_STAGE particles (a crowd; the table keeps the lattice's
+// below) is staged in windows. A ghost's sorted slot, which the tiles find too,
+// is the entries before its tile and before its cell plus its rank in its
+// bucket.
 struct GhostLds {
   float4 pv[WC_GHOST_STAGE], aux[WC_GHOST_STAGE];
   uint32_t n[WC_GHOST_REGION];

@@ -26,6 +26,9 @@ FORMS = {
     "two_way_audit": lambda c: dict(workloads.two_way(c), audit=1),
     "drag": lambda c: dict(c, kin_mode=1, kin_coef=3.0),
     "axisym": workloads.axisymmetric,
+    "wide": lambda c: dict(c, h_over_dx=2.0, cell_size=workloads._cell_size(c["dx"], 2.0), ghost_layers=4),
+    "dense_cells": lambda c: dict(c, cell_size=float(np.float32(5.5 * c["dx"])), n_disk_ghosts=40),
+    "crowded_ring": lambda c: dict(c, n_disk_ghosts=256),
     "axisym_two_way": lambda c: workloads.axisymmetric(dict(c, kin_mode=2)),
 }
 
@@ -134,15 +137,29 @@ def test_choice_on_either_side_of_the_line(nx, h_over_dx, own):
         s.close()
 
 
-def test_probes_on_both_walls_of_a_narrow_channel():
+def _channel(nx, ny, dx, h_over_dx=1.3, **kw):
+    cfg = workloads.base(nx * dx, ny * dx, dx, 12 * dx, 900.0)
+    return dict(cfg, h_over_dx=h_over_dx, **dict(dict(cell_size=workloads._cell_size(dx, h_over_dx)), **kw))
+
+
+CROWDS = {
+    # probes of both walls: 852 particles in one block, 88 -> 116 us a step
+    "narrow": _channel(1263, 63, 0.5e-3, 2.0, ghost_layers=4),
+    # left and right wall with the ring between them: 344, 60 -> 71 us
+    "ring": dict(workloads.tiny(), n_disk_ghosts=150),
+    # 30 particles a cell around a run of ring ghosts: 382, 92 -> 164 us
+    "dense": _channel(346, 173, 0.5e-3, cell_size=float(np.float32(2.75e-3))),
+}
+
+
+@pytest.mark.parametrize("crowd", CROWDS)
+def test_no_block_holds_up_the_launch(crowd):
     """A block of the sort's launch takes items whose surroundings it can stage
-    at once: in one block the probes of both walls of this channel (852
-    particles around them) made a step 88 -> 116 us; apart it is 84."""
-    dx = 0.5e-3
-    cfg = workloads.base(1263 * dx, 63 * dx, dx, 12 * dx, 900.0)
-    cfg = dict(cfg, h_over_dx=2.0, cell_size=workloads._cell_size(dx, 2.0), ghost_layers=4)
-    print("[gpu] narrow channel", flush=True)
-    s = wc.Solver(cfg, "cuda:0")
+    at once (320 particles). The figures above are a launch of their own ->
+    the sort's with such a block; without, the sort's launch is the faster."""
+    print(f"[gpu] {crowd}", flush=True)
+    s = wc.Solver(CROWDS[crowd], "cuda:0")
+    s.step(100)
     best = {}
     for own in (True, False) * 4:
         s.set_ghost_launch(own)
